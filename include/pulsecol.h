@@ -104,7 +104,8 @@ PULSECOL_API pulsecol_status pulsecol_validate_shape(const pulsecol_shape* shape
 
 /* Create a context on HIP device `device`: copies `shape`, allocates the scratch
  * (4*B*H*seq bytes of row statistics, 4*B*H*U*seq bytes of scores, 4*B*H*U*k_max bytes for the
- * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 256 bytes of counters).
+ * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 256 bytes of counters; bf16 shapes
+ * that do not fill the chip: up to 4 MiB for partial results of the scoring passes).
  * *out is set only on PULSECOL_OK. */
 PULSECOL_API pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape, int device);
 
@@ -209,9 +210,8 @@ PULSECOL_API pulsecol_status pulsecol_attn_dense(pulsecol_ctx* ctx, const void* 
 /* pulsecol_select(refresh != 0) for callers that cannot allocate device memory or hold a context
  * that did: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same computation and same idx_out[B, H, U, k] as pulsecol_select on a context of this shape, on
- * the CURRENT device; nothing is cached (there is no context to cache in).  The row statistics,
- * the scores and the work counters live in a static device array of 16 MiB + 256 bytes that each
- * GPU the library runs on holds until the process ends; its address is looked up at the first call
+ * the CURRENT device; nothing is cached (there is no context to cache in).  The row statistics
+ * and the scores live in a static device array of 16 MiB that each GPU the library runs on holds until the process ends; its address is looked up at the first call
  * on a device.  Limit: batch * heads * seq * (1 + U) <= 4 * 2^20 fp32 words (exactly the 64K-context,
  * 32-head, one-group-per-head shape), else PULSECOL_ERR_UNSUPPORTED with nothing launched.  The call
  * issues no hipMalloc / hipFree / hipMemset, only kernel launches on `stream`.  All calls on one GPU

@@ -159,20 +159,16 @@ struct AttnWave {
     static constexpr int HALF_BYTES = 32 * ROW_BYTES;
     static constexpr int ROWS_PER_CHUNK = 64 / PIECES;   // one direct-to-LDS load instruction moves 64 x 16 bytes
     static constexpr int CH = BN / ROWS_PER_CHUNK / 4;   // such instructions per wave and tile (per operand)
-    static constexpr bool HAS_V = (MODE != kLseOnly);
     static constexpr bool BLOCKS = (MODE == kBlock);       // block-sparse: a tile is one block of BN consecutive keys
     static constexpr bool GATHER = (MODE == kSparse || MODE == kBlock);
-    static constexpr int ODB = HAS_V ? DB : 1;
-    static constexpr int NPV = HAS_V ? 2 * DB : 0;       // V fragments (= MFMA pairs) of a half-step
+    static constexpr int NPV = 2 * DB;                   // V fragments (= MFMA pairs) of a half-step
     static constexpr int NP = KK + NPV;                  // MFMA pairs of a half-step
     static constexpr int NS = 2 * NP;                    // MFMA slots of a half-step
     static constexpr int EXP_TICKS = 34;                 // 32 values through a 3-stage pipeline
     // One wait per WAIT_PAIRS MFMA pairs, for the fragments of all of them (a wait costs issue
     // time); fragment reads run AHEAD pairs ahead of their use, so that the last fragment of a
     // group still has AHEAD - WAIT_PAIRS + 1 pairs to arrive.
-    // (The row pass has no P V stream behind which the next half-step's first fragments could be
-    // requested; it reads them right behind its barrier and waits for each by itself.)
-    static constexpr int WAIT_PAIRS = !HAS_V ? 1 : (KK >= 8 ? 4 : 2);
+    static constexpr int WAIT_PAIRS = KK >= 8 ? 4 : 2;
     static constexpr int AHEAD = WAIT_PAIRS + 2;
     // ticks issued before slot s: spread over all slots but the last one, so that the row sums
     // are complete (and their check can be computed) one slot before the half-step ends
@@ -198,7 +194,7 @@ struct AttnWave {
         return c;
     }
     // loads of the running iteration in flight at its barrier: everything older has to be complete
-    static constexpr int VM_PER_ISSUE = CH + (HAS_V ? v_loads_before_barrier() : 0);
+    static constexpr int VM_PER_ISSUE = CH + v_loads_before_barrier();
 
     // lane geometry
     int lane, wave, lq, lh;
@@ -214,7 +210,7 @@ struct AttnWave {
     const byte* idx;      // int32 column numbers of this head
     // registers that live across the whole kernel
     bf16x8 qf[2][KK];     // AGPRs
-    f32x16 o_acc[2][ODB]; // AGPRs
+    f32x16 o_acc[2][DB]; // AGPRs
     float c2;
     float mc[2];          // reference maximum in log2 units (raw maximum * c2), equal in both half-waves
     float l_run[2];       // per-lane partial row sum (this lane's keys only)
@@ -222,7 +218,7 @@ struct AttnWave {
     // (block-sparse) the row's offset inside its key block
     uint32_t koff[CH], voff[CH];
     uint32_t kaddr[KK];   // LDS byte offset (inside a tile slot, first half) of this lane's K fragment kk
-    uint32_t vaddr[ODB];  // same for the first 4-row group of the V fragment of d-block db
+    uint32_t vaddr[DB];  // same for the first 4-row group of the V fragment of d-block db
     int lrow;
     uint32_t lane_rows_off;   // byte offset, inside a tile's 64 column numbers, of this lane's CH consecutive ones
 
@@ -255,7 +251,7 @@ struct AttnWave {
         const int colpiece = ((lane >> 4) & 1) * 2 + ((j16 & 3) >> 1);
         const int inpiece = (j16 & 1) * 8;
 #pragma unroll
-        for (int db = 0; db < ODB; ++db)
+        for (int db = 0; db < DB; ++db)
             vaddr[db] = (uint32_t)(row0 * ROW_BYTES + inpiece + (((db * 4 + colpiece) ^ swizzle_v<PIECES>(row0)) << 4));
     }
 
@@ -354,13 +350,11 @@ struct AttnWave {
     }
     __device__ __forceinline__ void issue_v_tile(byte* __restrict__ vslot, const byte* __restrict__ Vg,
                                                  const rows_t& rows) const {
-        if (HAS_V) {
 #pragma unroll
-            for (int i = 0; i < CH; ++i)
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(Vg + row_offset(row_word(rows, i), voff[i])),
-                    (PULSECOL_LDS void*)(vslot + (wave * CH + i) * 1024), 16, 0, 0);
-        }
+        for (int i = 0; i < CH; ++i)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(Vg + row_offset(row_word(rows, i), voff[i])),
+                (PULSECOL_LDS void*)(vslot + (wave * CH + i) * 1024), 16, 0, 0);
     }
 
     // One load of the scheduled half-step in two parts, so that no slot gets more than two
@@ -391,9 +385,9 @@ struct AttnWave {
     __device__ __forceinline__ bf16x8 read_k(const byte* __restrict__ kslot, int half, int kk) const {
         return *(const bf16x8*)(kslot + half * HALF_BYTES + kaddr[kk]);
     }
-    // V fragment q of a half-step: rows hf*16 .. +15 of the half-tile, d-block db; q = hf*ODB + db
+    // V fragment q of a half-step: rows hf*16 .. +15 of the half-tile, d-block db; q = hf*DB + db
     __device__ __forceinline__ bf16x8 read_v(const byte* __restrict__ vslot, int half, int q) const {
-        const int hf = q / ODB, db = q % ODB;
+        const int hf = q / DB, db = q % DB;
         const byte* p = vslot + half * HALF_BYTES + hf * 16 * ROW_BYTES + vaddr[db];
         const bf16x4 lo = lds_read_tr(p);
         const bf16x4 hi = lds_read_tr(p + 8 * ROW_BYTES);
@@ -445,8 +439,8 @@ struct AttnWave {
         const int e = has_val ? i - 2 : 0, qb = e >> 4, r = e & 15;
         // value 0 of a query block opens its row sum (no instruction), value 1 is packed with it
         // straight out of the sum's register
-        const bool has_add = has_val && r > 0, first_pack = HAS_V && has_val && r == 1;
-        const bool has_pack = HAS_V && has_val && (r & 1) && r > 1;
+        const bool has_add = has_val && r > 0, first_pack = has_val && r == 1;
+        const bool has_pack = has_val && (r & 1) && r > 1;
         const int ti = has_fma ? i : 0, te = has_exp ? i - 1 : 0, xp = has_pack ? e - 1 : 0;
         uint32_t w = 0;
         if (has_fma) ep.t[i] = __builtin_fmaf(S[i >> 4][i & 15], c2, -mc[i >> 4]);
@@ -497,7 +491,7 @@ struct AttnWave {
     // Slow path: true maximum of the half-tile per query, reference moved up by a whole number
     // of log2 units, l and the accumulator scaled by that exact power of two, P recomputed.
     __device__ __forceinline__ void fix_reference(ExpPipe& ep, const f32x16 (&S)[2], bf16x8 (&P)[2][2]) {
-        if (HAS_V) mfma_settle_acc(o_acc);
+        mfma_settle_acc(o_acc);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             const float m2 = half_tile_max(S[qb]) * c2;        // same value in both half-waves
@@ -507,18 +501,16 @@ struct AttnWave {
                 const float alpha = first ? 0.f : fast_exp2(-steps);
                 mc[qb] = first ? m2 : mc[qb] + steps;
                 l_run[qb] *= alpha;
-                if (HAS_V) {
-                    // one block at a time, pinned inside this branch: the accumulator passes through
-                    // VGPRs, and all of it at once does not fit beside the rest of the loop's registers
+                // one block at a time, pinned inside this branch: the accumulator passes through
+                // VGPRs, and all of it at once does not fit beside the rest of the loop's registers
 #pragma unroll
-                    for (int db = 0; db < ODB; ++db) {
-                        f32x16 t = o_acc[qb][db];
-                        asm volatile("" : "+v"(t));
+                for (int db = 0; db < DB; ++db) {
+                    f32x16 t = o_acc[qb][db];
+                    asm volatile("" : "+v"(t));
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) t[r] *= alpha;
-                        o_acc[qb][db] = t;
-                        asm volatile("" : "+a"(o_acc[qb][db]));
-                    }
+                    for (int r = 0; r < 16; ++r) t[r] *= alpha;
+                    o_acc[qb][db] = t;
+                    asm volatile("" : "+a"(o_acc[qb][db]));
                 }
                 float rs = 0.f;
 #pragma unroll
@@ -527,10 +519,8 @@ struct AttnWave {
                     const float x1 = fast_exp2(__builtin_fmaf(S[qb][r + 1], c2, -mc[qb]));
                     rs += x0;
                     rs += x1;
-                    if (HAS_V) {
-                        P[qb][r >> 3][r & 7] = (__bf16)x0;
-                        P[qb][r >> 3][(r & 7) + 1] = (__bf16)x1;
-                    }
+                    P[qb][r >> 3][r & 7] = (__bf16)x0;
+                    P[qb][r >> 3][(r & 7) + 1] = (__bf16)x1;
                 }
                 ep.rs[qb] = rs;
             }
@@ -559,16 +549,14 @@ struct AttnWave {
         }
     }
     __device__ __forceinline__ void pv_all(const byte* vslot, int half, const bf16x8 (&P)[2][2]) {
-        if constexpr (HAS_V) {
-            bf16x8 a[NPV];
+        bf16x8 a[NPV];
 #pragma unroll
-            for (int q = 0; q < NPV; ++q) a[q] = read_v(vslot, half, q);
-            fence();
+        for (int q = 0; q < NPV; ++q) a[q] = read_v(vslot, half, q);
+        fence();
 #pragma unroll
-            for (int q = 0; q < NPV; ++q) {
-                mfma_pv(o_acc[0][q % ODB], a[q], P[0][q / ODB]);
-                mfma_pv(o_acc[1][q % ODB], a[q], P[1][q / ODB]);
-            }
+        for (int q = 0; q < NPV; ++q) {
+            mfma_pv(o_acc[0][q % DB], a[q], P[0][q / DB]);
+            mfma_pv(o_acc[1][q % DB], a[q], P[1][q / DB]);
         }
     }
 
@@ -594,7 +582,7 @@ struct AttnWave {
     // offset KW from the wave's base).  ROLE 1 = second half-step: issues the loads of a V tile
     // (offset VW) and holds the workgroup barrier, see steady_iter.
     template <int KOFF, int VOFF, bool HAS_NEXT, int NKOFF, int ROLE, int KW, int VW>
-    __device__ __forceinline__ void fast_step(const uint32_t (&kv)[KK], const uint32_t (&vv)[ODB],
+    __device__ __forceinline__ void fast_step(const uint32_t (&kv)[KK], const uint32_t (&vv)[DB],
                                               bf16x8 (&kpre)[AHEAD],
                                               int next_tile, const rows_t& krows, const rows_t& vrows,
                                               rows_t& rows_n,
@@ -616,7 +604,7 @@ struct AttnWave {
     }
     template <int KOFF, int VOFF, bool HAS_NEXT, int NKOFF, int ROLE, int KW, int VW, int... Ps>
     __device__ __forceinline__ void fast_pairs(std::integer_sequence<int, Ps...>,
-                                               const uint32_t (&kv)[KK], const uint32_t (&vv)[ODB],
+                                               const uint32_t (&kv)[KK], const uint32_t (&vv)[DB],
                                                bf16x8 (&fr)[NP + AHEAD], ExpPipe& ep,
                                                int next_tile, const rows_t& krows, const rows_t& vrows,
                                                rows_t& rows_n,
@@ -627,7 +615,7 @@ struct AttnWave {
     }
     // MFMA pair P of a fast half-step: two slots that share one A fragment.
     template <int P, int KOFF, int VOFF, bool HAS_NEXT, int NKOFF, int ROLE, int KW, int VW>
-    __device__ __forceinline__ void fast_pair(const uint32_t (&kv)[KK], const uint32_t (&vv)[ODB],
+    __device__ __forceinline__ void fast_pair(const uint32_t (&kv)[KK], const uint32_t (&vv)[DB],
                                               bf16x8 (&fr)[NP + AHEAD], ExpPipe& ep,
                                               int next_tile, const rows_t& krows, const rows_t& vrows,
                                               rows_t& rows_n,
@@ -656,12 +644,12 @@ struct AttnWave {
                 }
             } else {
                 constexpr int q = P - KK;
-                if (qb == 0 && WAITS) mfma_pv_after<NEWER>(o_acc[qb][q % ODB], fr[P], P_in[qb][q / ODB]);
-                else mfma_pv(o_acc[qb][q % ODB], fr[P], P_in[qb][q / ODB]);
+                if (qb == 0 && WAITS) mfma_pv_after<NEWER>(o_acc[qb][q % DB], fr[P], P_in[qb][q / DB]);
+                else mfma_pv(o_acc[qb][q % DB], fr[P], P_in[qb][q / DB]);
             }
             fence();
             if (qb == 0) {
-                if constexpr (ROLE == 1 && HAS_V && P == KK) {
+                if constexpr (ROLE == 1 && P == KK) {
                     // All K reads of this iteration are complete (their fragments have been
                     // consumed).  Everything loaded before this iteration's own loads has landed;
                     // after the barrier the other waves' shares are visible too, and the slots
@@ -672,20 +660,20 @@ struct AttnWave {
                 if constexpr (ROLE == 0 && P >= 1) {
                     if constexpr (k_addr_at(P - 1) >= 0) issue_load<k_addr_at(P - 1)>(K, dma_off);
                 }
-                if constexpr (ROLE == 1 && HAS_V && P >= 1) {
+                if constexpr (ROLE == 1 && P >= 1) {
                     if constexpr (v_addr_at(P - 1) >= 0) issue_load<v_addr_at(P - 1)>(V, dma_off);
                 }
                 if constexpr (PA < KK) {
                     fr[PA] = lds_read_b128_at<KOFF>(kv[PA]);
                 } else if constexpr (PA < NP) {
-                    constexpr int q = PA - KK, hf = q / ODB, db = q % ODB;
+                    constexpr int q = PA - KK, hf = q / DB, db = q % DB;
                     set_half(fr[PA], 0, lds_read_tr_at<VOFF + hf * 16 * ROW_BYTES>(vv[db]));
                 } else if constexpr (HAS_NEXT) {
                     fr[PA] = lds_read_b128_at<NKOFF>(kv[PA - NP]);
                 }
             } else {
                 if constexpr (PA >= KK && PA < NP) {
-                    constexpr int q = PA - KK, hf = q / ODB, db = q % ODB;
+                    constexpr int q = PA - KK, hf = q / DB, db = q % DB;
                     set_half(fr[PA], 1, lds_read_tr_at<VOFF + hf * 16 * ROW_BYTES + 8 * ROW_BYTES>(vv[db]));
                 }
                 if constexpr (ROLE == 0) {
@@ -693,7 +681,7 @@ struct AttnWave {
                     constexpr int j = k_addr_at(P);
                     if constexpr (j >= 0) dma_off = issue_addr<KW, j>(row_word(krows, j), koff[j]);
                 }
-                if constexpr (ROLE == 1 && HAS_V) {
+                if constexpr (ROLE == 1) {
                     constexpr int j = v_addr_at(P);
                     if constexpr (j >= 0) dma_off = issue_addr<VW, j>(row_word(vrows, j), voff[j]);
                 }
@@ -733,7 +721,7 @@ struct AttnWave {
     // that K(u+2), V(u+1) are visible to every wave before anything reads them -- and then
     // requests the first K fragments of the next iteration while its P V MFMAs run.
     template <int U4>
-    __device__ __forceinline__ void steady_iter(const uint32_t (&kv)[KK], const uint32_t (&vv)[ODB],
+    __device__ __forceinline__ void steady_iter(const uint32_t (&kv)[KK], const uint32_t (&vv)[DB],
                                                 bf16x8 (&kpre)[AHEAD], int next_tile,
                                                 const rows_t& krows, const rows_t& vrows, rows_t& rows_n,
                                                 f32x16 (&SA)[2], f32x16 (&SB)[2],
@@ -748,16 +736,9 @@ struct AttnWave {
         fast_step<KR, VR, true, KR + HALF_BYTES, 0, KW, VW>(kv, vv, kpre, next_tile, krows, vrows, rows_n, SB, SA, PA, PB);
         if (last) mask_last_tile(0, SA);
         // even: S(j) in SA, P(j-1) in PB -> S(j+1) in SB, P(j) in PA
-        fast_step<KR + HALF_BYTES, VR + HALF_BYTES, HAS_V, KN, 1, KW, VW>(kv, vv, kpre, next_tile, krows, vrows, rows_n,
+        fast_step<KR + HALF_BYTES, VR + HALF_BYTES, true, KN, 1, KW, VW>(kv, vv, kpre, next_tile, krows, vrows, rows_n,
                                                                          SA, SB, PB, PA);
         if (last) mask_last_tile(1, SB);
-        if (!HAS_V) {
-            // row pass: no P V stream to cover the barrier; synchronise at the end of the iteration
-            wait_vmcnt_at_most<VM_PER_ISSUE>();
-            __builtin_amdgcn_s_barrier();
-#pragma unroll
-            for (int i = 0; i < AHEAD; ++i) kpre[i] = lds_read_b128_at<KN>(kv[i]);
-        }
     }
 };
 
@@ -829,21 +810,19 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     using W = AttnWave<D, MODE>;
     constexpr int CH = W::CH;
     constexpr int KK = W::KK;
-    constexpr int ODB = W::ODB;
+    constexpr int DB = W::DB;
     constexpr int TILE_BYTES = W::TILE_BYTES;
-    constexpr bool HAS_V = W::HAS_V;
 
     // ONE shared array for all tile slots: with a single LDS object the alias scopes that the
     // restrict parameters give the direct-to-LDS loads are what the compiler's wait-count
     // insertion sees, and LDS reads of one slot do not wait for loads into another.
     // The Q block is turned around in LDS at the start of a query block: a wave's 64 Q rows are one
     // tile's worth of bytes and go through V slot `wave`, which is not needed yet at that point.
-    // (The row pass has no V slots; it loads its Q fragments directly.)
     // One more tile behind them is wave 0's share of the output staging area (the other waves use
     // K slots 1..3): K slot 0 then is free for the next query block's first tile at once.
-    __shared__ __attribute__((aligned(1024))) byte lds_all[(NBUF_K + (HAS_V ? NBUF_V + 1 : 0)) * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) byte lds_all[(NBUF_K + NBUF_V + 1) * TILE_BYTES];
     byte* const lds_k = lds_all;
-    byte* const lds_v = lds_all + (HAS_V ? NBUF_K * TILE_BYTES : 0);
+    byte* const lds_v = lds_all + NBUF_K * TILE_BYTES;
 
     // Fetch every kernel argument with the first batch of scalar loads: left to itself the compiler
     // loads them where they are first used, one memory round trip after another.
@@ -909,7 +888,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     // fit the vector cache.)  Each wave stages its own 64 rows.
     typename W::rows_t rows_k, rows_v, rows_n, rows_0, rows_1;
     static_assert(PRO_TILES == 3, "the prologue is written out for three tiles");
-    constexpr int Q_LOADS = HAS_V ? TILE_BYTES / 1024 : 0;        // direct-to-LDS loads of a wave's share of Q
+    constexpr int Q_LOADS = TILE_BYTES / 1024;      // direct-to-LDS loads of a wave's share of Q
     const byte* req_q = nullptr;          // the requested block's head of Q, and its first row for this wave
     int req_q0 = 0, req_n = p.n;          // ... and the rows of that head
     auto request_rows = [&](int q, int j) {
@@ -940,28 +919,26 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
         static_assert((4 * RPC) % PIECES == 0, "the swizzle of a row repeats every four loads");
     }
     auto request_q = [&](auto t0_c, auto t1_c) {
-        if constexpr (HAS_V) {
-            constexpr int t0 = decltype(t0_c)::value, t1 = decltype(t1_c)::value;
-            static_assert(t0 % 4 == 0 && t1 % 4 == 0, "whole groups of four loads");
-            constexpr int RPC = W::ROWS_PER_CHUNK;
-            const int row0 = req_q0 + wq.lane / W::PIECES;
+        constexpr int t0 = decltype(t0_c)::value, t1 = decltype(t1_c)::value;
+        static_assert(t0 % 4 == 0 && t1 % 4 == 0, "whole groups of four loads");
+        constexpr int RPC = W::ROWS_PER_CHUNK;
+        const int row0 = req_q0 + wq.lane / W::PIECES;
 #pragma unroll
-            for (int t = t0; t < t1; ++t) {
-                int row = row0 + t * RPC;
-                row = row < req_n ? row : req_n - 1;
-                uint32_t off;
-                if (t % 4 == 0) {
-                    asm volatile("s_add_i32 m0, %1, %2\n\tv_mad_u32_u24 %0, %3, %4, %5"
-                                 : "=v"(off) : "s"(qstage_lds), "s"((uint32_t)(t * 1024)), "v"(row), "s"(q_row_bytes), "v"(q_piece[0]));
-                } else {
-                    asm volatile("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(off) : "v"(row), "s"(q_row_bytes), "v"(q_piece[t % 4]));
-                }
-                switch (t % 4) {
-                    case 0: asm volatile("global_load_lds_dwordx4 %0, %1 offset:0" : : "v"(off), "s"(req_q) : "memory"); break;
-                    case 1: asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" : : "v"(off), "s"(req_q - 1024) : "memory"); break;
-                    case 2: asm volatile("global_load_lds_dwordx4 %0, %1 offset:2048" : : "v"(off), "s"(req_q - 2048) : "memory"); break;
-                    default: asm volatile("global_load_lds_dwordx4 %0, %1 offset:3072" : : "v"(off), "s"(req_q - 3072) : "memory"); break;
-                }
+        for (int t = t0; t < t1; ++t) {
+            int row = row0 + t * RPC;
+            row = row < req_n ? row : req_n - 1;
+            uint32_t off;
+            if (t % 4 == 0) {
+                asm volatile("s_add_i32 m0, %1, %2\n\tv_mad_u32_u24 %0, %3, %4, %5"
+                             : "=v"(off) : "s"(qstage_lds), "s"((uint32_t)(t * 1024)), "v"(row), "s"(q_row_bytes), "v"(q_piece[0]));
+            } else {
+                asm volatile("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(off) : "v"(row), "s"(q_row_bytes), "v"(q_piece[t % 4]));
+            }
+            switch (t % 4) {
+                case 0: asm volatile("global_load_lds_dwordx4 %0, %1 offset:0" : : "v"(off), "s"(req_q) : "memory"); break;
+                case 1: asm volatile("global_load_lds_dwordx4 %0, %1 offset:1024" : : "v"(off), "s"(req_q - 1024) : "memory"); break;
+                case 2: asm volatile("global_load_lds_dwordx4 %0, %1 offset:2048" : : "v"(off), "s"(req_q - 2048) : "memory"); break;
+                default: asm volatile("global_load_lds_dwordx4 %0, %1 offset:3072" : : "v"(off), "s"(req_q - 3072) : "memory"); break;
             }
         }
     };
@@ -989,15 +966,14 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     w.c2 = p.scale * kLog2e;                 // exp(z*scale) = exp2(z*c2)
     w.init_addresses();
     const int nhalf = w.nhalf;
-    byte* const qstage = lds_v + w.wave * TILE_BYTES;      // HAS_V only
+    byte* const qstage = lds_v + w.wave * TILE_BYTES;
 
     const int b = bh / p.heads, h = bh - b * p.heads;
     const int64_t head_off = q_of(bh);
     // grouped-query layout: query head h reads K/V head h / (heads / kv_heads)
     const int64_t kv_off = (int64_t)b * p.td_kv.sb + (int64_t)(h / (p.heads / p.kv_heads)) * p.td_kv.sh;
-    const __bf16* __restrict__ Q = (const __bf16*)p.q + head_off;
     w.K = (const byte*)((const __bf16*)p.k + kv_off);
-    w.V = HAS_V ? (const byte*)((const __bf16*)p.v + kv_off) : nullptr;
+    w.V = (const byte*)((const __bf16*)p.v + kv_off);
     w.idx = pattern_of(bh, qblk);
     w.mc[0] = w.mc[1] = -INFINITY;
     w.l_run[0] = w.l_run[1] = 0.f;
@@ -1009,34 +985,23 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     //   V(0), K(1), V(1), K(2)              -> the last two may be in flight -> first iteration
     //                                       -> its own barrier covers V(1), K(2)
     // (V(2) is loaded by the first iteration itself.)  Afterwards rows_v = tile 2, rows_k = tile 3.
-    if constexpr (!HAS_V) {
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-            int row = q0 + qb * 32 + w.lq;
-            row = row < n ? row : n - 1;
-            const __bf16* src = Q + (int64_t)row * p.td.sn + 8 * w.lh;
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) w.qf[qb][kk] = *(const bf16x8*)(src + kk * 16);
-        }
-    }
     if (!k0_on_its_way) w.issue_k_tile(lds_k, w.K, rows_0);      // else: issued from the epilogue of the block before
-    constexpr int LATER_LOADS = CH * (HAS_V ? 4 : 2);     // V(0), K(1), V(1), K(2): issued behind the first barrier
+    constexpr int LATER_LOADS = CH * 4;     // V(0), K(1), V(1), K(2): issued behind the first barrier
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int db = 0; db < ODB; ++db) {
+        for (int db = 0; db < DB; ++db) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) w.o_acc[qb][db][r] = 0.f;
             asm volatile("" : "+a"(w.o_acc[qb][db]));
         }
     wait_vmcnt_at_most<0>();
     fence();                        // the compiler does not know that the Q copy wrote what is read next
-    if constexpr (HAS_V) {          // all fragment reads, then one wait
+    // all fragment reads, then one wait
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) w.qf[qb][kk] = *(const bf16x8*)(qstage + qb * W::HALF_BYTES + w.kaddr[kk]);
-    }
+        for (int kk = 0; kk < KK; ++kk) w.qf[qb][kk] = *(const bf16x8*)(qstage + qb * W::HALF_BYTES + w.kaddr[kk]);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -1047,7 +1012,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     // in the memory pipe).
     w.issue_v_tile(lds_v, w.V, rows_0);
     w.issue_k_tile(lds_k + TILE_BYTES, w.K, rows_1);
-    w.issue_v_tile(lds_v + (HAS_V ? TILE_BYTES : 0), w.V, rows_1);
+    w.issue_v_tile(lds_v + TILE_BYTES, w.V, rows_1);
     w.issue_k_tile(lds_k + 2 * TILE_BYTES, w.K, rows_v);
 
     f32x16 SA[2], SB[2];
@@ -1076,13 +1041,13 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
         wait_vmcnt_at_most<LATER_LOADS / 2>();            // V(0) and K(1) have landed ...
         __builtin_amdgcn_s_barrier();                     // ... in every wave
         const uint32_t kbase = lds_address(lds_k), vbase = lds_address(lds_v);
-        uint32_t kv[KK], vv[ODB];      // fragment addresses inside slot 0; slots and halves are immediates
+        uint32_t kv[KK], vv[DB];      // fragment addresses inside slot 0; slots and halves are immediates
         constexpr int AHEAD = W::AHEAD;
         bf16x8 kpre[AHEAD];
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) kv[kk] = kbase + w.kaddr[kk];
 #pragma unroll
-        for (int db = 0; db < ODB; ++db) vv[db] = vbase + w.vaddr[db];
+        for (int db = 0; db < DB; ++db) vv[db] = vbase + w.vaddr[db];
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) kpre[i] = lds_read_b128_at<TILE_BYTES>(kv[i]);     // K tile 1
         // rows_k / rows_v / rows_n rotate by name: after an iteration, v <- k <- n
@@ -1117,7 +1082,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     if (threadIdx.x == 0) early_j = queues.take(cur_q);
     w.general_step(nhalf - 1, lds_k, lds_v, SB, SA, PA, PB);
 
-    w.pv_all(lds_v + (HAS_V ? (((nhalf - 1) >> 1) % NBUF_V) * TILE_BYTES : 0), (nhalf - 1) & 1, PB);
+    w.pv_all(lds_v + (((nhalf - 1) >> 1) % NBUF_V) * TILE_BYTES, (nhalf - 1) & 1, PB);
 
     // ---- epilogue: O = diag(l)^-1 acc, optional row log-sum-exp; hand-over to the next item.
     // In the accumulator a lane holds one query row in 8-byte runs: stored directly, every
@@ -1157,78 +1122,73 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     cur_j = __builtin_amdgcn_readfirstlane(lds_item[1]);
     const bool more = cur_j >= 0;
     if (more) request_rows(cur_q, cur_j);
-    if constexpr (HAS_V) {
-        constexpr int PIECES = W::PIECES, ROW_BYTES = W::ROW_BYTES, RPC = W::ROWS_PER_CHUNK;
-        static_assert(64 * ROW_BYTES <= TILE_BYTES && Q_LOADS % ODB == 0, "a wave's output tile fits one tile slot");
-        mfma_settle_acc(w.o_acc);
-        byte* const stage = lds_all + (w.wave == 0 ? NBUF_K + NBUF_V : w.wave) * TILE_BYTES;
-        const float inv[2] = {1.0f / l_tot[0], 1.0f / l_tot[1]};
-        static_assert((Q_LOADS / ODB) % 4 == 0, "whole groups of four loads per d-block");
-        const auto stage_db = [&](auto db_c) {
-            constexpr int db = decltype(db_c)::value;
+    constexpr int PIECES = W::PIECES, ROW_BYTES = W::ROW_BYTES, RPC = W::ROWS_PER_CHUNK;
+    static_assert(64 * ROW_BYTES <= TILE_BYTES && Q_LOADS % DB == 0, "a wave's output tile fits one tile slot");
+    mfma_settle_acc(w.o_acc);
+    byte* const stage = lds_all + (w.wave == 0 ? NBUF_K + NBUF_V : w.wave) * TILE_BYTES;
+    const float inv[2] = {1.0f / l_tot[0], 1.0f / l_tot[1]};
+    static_assert((Q_LOADS / DB) % 4 == 0, "whole groups of four loads per d-block");
+    const auto stage_db = [&](auto db_c) {
+        constexpr int db = decltype(db_c)::value;
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-                const int r = qb * 32 + w.lq;
+        for (int qb = 0; qb < 2; ++qb) {
+            const int r = qb * 32 + w.lq;
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    bf16x4 o4;
+            for (int r4 = 0; r4 < 4; ++r4) {
+                bf16x4 o4;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(w.o_acc[qb][db][r4 * 4 + e] * inv[qb]);
-                    *(bf16x4*)(stage + r * ROW_BYTES + (((db * 4 + r4) ^ (r & (PIECES - 1))) << 4) + 8 * w.lh) = o4;
-                }
+                for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(w.o_acc[qb][db][r4 * 4 + e] * inv[qb]);
+                *(bf16x4*)(stage + r * ROW_BYTES + (((db * 4 + r4) ^ (r & (PIECES - 1))) << 4) + 8 * w.lh) = o4;
             }
-            fence();
-        };
-        // piece db of the next block's Q copy
-        const auto request_q_piece = [&](auto db_c) {
-            constexpr int db = decltype(db_c)::value;
-            if (more) request_q(std::integral_constant<int, db * (Q_LOADS / ODB)>{}, std::integral_constant<int, (db + 1) * (Q_LOADS / ODB)>{});
-        };
-        stage_db(std::integral_constant<int, 0>{});
-        // The next block's first K tile goes out as soon as its row numbers are there (they were
-        // requested a d-block of staging ago; the compiler's wait for them drains the vector
-        // memory pipe, so nothing else is put in flight before it): K slot 0 is not part of the
-        // staging area and no wave reads K any more, and the tile lands while the stores queue.
-        k0_on_its_way = more;
-        if (more) {
-            int nbh, nqblk;
-            decode(cur_q, cur_j, nbh, nqblk);
-            const int nb = nbh / p.heads, nh = nbh - nb * p.heads;
-            const int64_t nkv = (int64_t)nb * p.td_kv.sb + (int64_t)(nh / (p.heads / p.kv_heads)) * p.td_kv.sh;
-            w.issue_k_tile(lds_k, (const byte*)((const __bf16*)p.k + nkv), rows_0);
-        }
-        request_q_piece(std::integral_constant<int, 0>{});
-        if constexpr (ODB > 1) { stage_db(std::integral_constant<int, 1>{}); request_q_piece(std::integral_constant<int, 1>{}); }
-        if constexpr (ODB > 2) {
-            stage_db(std::integral_constant<int, 2>{}); request_q_piece(std::integral_constant<int, 2>{});
-            stage_db(std::integral_constant<int, 3>{}); request_q_piece(std::integral_constant<int, 3>{});
-        }
-        // all reads first, then the stores: one LDS round trip instead of one per row group
-        u32x4 rows_out[OUT_GROUPS];
-#pragma unroll
-        for (int t = 0; t < OUT_GROUPS; ++t) {
-            const int r = t * RPC + out_lrow;
-            rows_out[t] = *(const u32x4*)(stage + r * ROW_BYTES + ((out_lpiece ^ (r & (PIECES - 1))) << 4));
         }
         fence();
+    };
+    // piece db of the next block's Q copy
+    const auto request_q_piece = [&](auto db_c) {
+        constexpr int db = decltype(db_c)::value;
+        if (more) request_q(std::integral_constant<int, db * (Q_LOADS / DB)>{}, std::integral_constant<int, (db + 1) * (Q_LOADS / DB)>{});
+    };
+    stage_db(std::integral_constant<int, 0>{});
+    // The next block's first K tile goes out as soon as its row numbers are there (they were
+    // requested a d-block of staging ago; the compiler's wait for them drains the vector
+    // memory pipe, so nothing else is put in flight before it): K slot 0 is not part of the
+    // staging area and no wave reads K any more, and the tile lands while the stores queue.
+    k0_on_its_way = more;
+    if (more) {
+        int nbh, nqblk;
+        decode(cur_q, cur_j, nbh, nqblk);
+        const int nb = nbh / p.heads, nh = nbh - nb * p.heads;
+        const int64_t nkv = (int64_t)nb * p.td_kv.sb + (int64_t)(nh / (p.heads / p.kv_heads)) * p.td_kv.sh;
+        w.issue_k_tile(lds_k, (const byte*)((const __bf16*)p.k + nkv), rows_0);
+    }
+    request_q_piece(std::integral_constant<int, 0>{});
+    if constexpr (DB > 1) { stage_db(std::integral_constant<int, 1>{}); request_q_piece(std::integral_constant<int, 1>{}); }
+    if constexpr (DB > 2) {
+        stage_db(std::integral_constant<int, 2>{}); request_q_piece(std::integral_constant<int, 2>{});
+        stage_db(std::integral_constant<int, 3>{}); request_q_piece(std::integral_constant<int, 3>{});
+    }
+    // all reads first, then the stores: one LDS round trip instead of one per row group
+    u32x4 rows_out[OUT_GROUPS];
 #pragma unroll
-        for (int t = 0; t < OUT_GROUPS; ++t) {
-            const int r = t * RPC + out_lrow;
-            if (q0 + r < n) *(u32x4*)(obase + t * group_stride) = rows_out[t];
-        }
+    for (int t = 0; t < OUT_GROUPS; ++t) {
+        const int r = t * RPC + out_lrow;
+        rows_out[t] = *(const u32x4*)(stage + r * ROW_BYTES + ((out_lpiece ^ (r & (PIECES - 1))) << 4));
+    }
+    fence();
+#pragma unroll
+    for (int t = 0; t < OUT_GROUPS; ++t) {
+        const int r = t * RPC + out_lrow;
+        if (q0 + r < n) *(u32x4*)(obase + t * group_stride) = rows_out[t];
     }
   }
 
 }
 
-// workgroups that one CU holds at a time (LDS and registers): the row pass fits two
-template <int MODE> constexpr int wg_per_cu() { return MODE == kLseOnly ? 2 : 1; }
-
 template <int D, int MODE>
 hipError_t launch(const AttnParams& p, hipStream_t s) {
     if (p.work == nullptr) return hipErrorInvalidValue;
     const int64_t items = (int64_t)((p.n + BM - 1) / BM) * p.batch * p.heads;
-    const int64_t resident = (int64_t)compute_units() * wg_per_cu<MODE>();
+    const int64_t resident = (int64_t)compute_units();               // LDS and registers: one workgroup per CU
     const int grid = (int)(items < resident ? items : resident);
     hipLaunchKernelGGL((attn_bf16_kernel<D, MODE>), dim3(grid), dim3(NTHREADS), 0, s, p);
     return hipGetLastError();
@@ -1252,13 +1212,11 @@ hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, AttnMode mode, hi
         if (mode == kSparse) return launch<128, kSparse>(p, s);
         if (mode == kBlock) return launch<128, kBlock>(p, s);
         if (mode == kDense) return launch<128, kDense>(p, s);
-        return launch<128, kLseOnly>(p, s);
     }
     if (head_dim == 64) {
         if (mode == kSparse) return launch<64, kSparse>(p, s);
         if (mode == kBlock) return launch<64, kBlock>(p, s);
         if (mode == kDense) return launch<64, kDense>(p, s);
-        return launch<64, kLseOnly>(p, s);
     }
     return hipErrorInvalidValue;
 }

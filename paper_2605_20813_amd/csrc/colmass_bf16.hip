@@ -1,21 +1,34 @@
-// Column softmax mass, bf16 inputs (Sec. 3.3, score equation):
-//   s_{u,j} = (1/|G_u|) sum_{i in G_u} exp(z_ij - lse_i),  z_ij = q_i . k_j * scale,
-// for the query groups G_u of a head (consecutive runs of group_size rows; one group = the
-// whole head on the hot path),
-// with the row log-sum-exp lse_i produced by the row pass (attn_bf16.hip, lse-only mode) and
-// handed over in log2 units, so that p_ij = exp2(z_ij * scale * log2(e) - lse2_i).
+// The two scoring passes of the identification step, bf16 inputs (Sec. 3.3, score equation):
+//   row pass     lse_i = log sum_j exp(z_ij),  z_ij = q_i . k_j * scale
+//   column pass  s_{u,j} = (1/|G_u|) sum_{i in G_u} exp(z_ij - lse_i)
+// for the query groups G_u of a head (consecutive runs of group_size rows; one group = the whole
+// head on the hot path).  The row pass hands its result over in log2 units, so that
+// p_ij = exp2(z_ij * scale * log2(e) - lse2_i).
 //
-// K-stationary: a workgroup owns 256 key columns (4 waves x 64); each wave keeps its K rows
-// in registers as the MFMA B operand and streams every 64-row Q tile of the head through
-// LDS as the A operand: direct-to-LDS loads into one of three tile slots, issued two tiles ahead of
-// their use, the rows' log-sum-exp values alongside.  In S[query][key] a lane owns one key column and its
-// 16 registers are 16 query rows, so the column sum is an in-lane sum (four interleaved partial
-// sums, each a short and a long accumulator) and the two half-waves meet once per group.
-// exp2(z*c - lse_i*log2e) takes lse_i per register row, read from LDS four at a time.
+// One structure for both.  A workgroup owns 256 stationary rows (4 waves x 64; query rows in the row
+// pass, key rows in the column pass), each wave's in registers as the MFMA B operand, and streams
+// 64-row tiles of the other tensor through LDS as the A operand: direct-to-LDS loads into one of three
+// tile slots, issued two tiles ahead of their use.  In S[streamed][stationary] a lane owns one
+// stationary row and its 16 registers are 16 streamed rows, so the sum over the streamed rows is an
+// in-lane sum (four interleaved partial sums, each a short and a long accumulator) and the two
+// half-waves meet once at the end (column pass: once per group).
+//   column pass: exp2(z*c - lse_i) takes lse_i per register row, read from LDS four at a time.
+//   row pass: exp2(z*c - ref) against one reference per lane, the maximum of the first 32 keys.  The
+//     sum is fp32 and keeps its relative precision however far later logits rise above the reference;
+//     only an overflow (some 2^127) has to be caught: a wave that ends with a sum that is not finite
+//     does its rows over with a running maximum.
 // P never leaves fp32 and there are no floating-point atomics: the result is bit-identical
 // from run to run.
-// Ordinary compiler-scheduled code; the only hand-placed instructions are the waits and barriers
-// that order the direct-to-LDS loads against the LDS reads.
+//
+// The streamed range of a head is cut into `splits` runs of whole tiles when one workgroup per head and
+// block would leave the chip idle (score_splits): every run is a workgroup of its own and leaves a
+// partial result, and a small kernel adds the partial results up in a fixed order.  (Column pass with
+// more than one query group: the runs end at group boundaries and nothing is left to add.)
+//
+// What bounds it: two weights and a matrix instruction per 32 cycles of the matrix pipe, about as much as one wave
+// can issue, and over long runs the power limit (about 1.2 PFLOP/s).  The row pass used to be a mode of the 256-row
+// attention kernel, 62 KB of straight-line code that every launch fetches anew; this one is 16 KB.  D = 128, 32 heads:
+// 4096 rows 172 -> 128 us, 16384 rows 1877 -> 1842 us, 65536 rows 28.8 -> 28.9 ms.
 #include <utility>
 
 #include "pulsecol_device.h"
@@ -27,8 +40,8 @@ namespace {
 typedef unsigned char byte;
 
 constexpr int NTHREADS = 256;
-constexpr int KEYS_PER_WG = 256;
-constexpr int QT = 64;              // query rows per streamed tile
+constexpr int ROWS_PER_WG = kScoreBlock_bf16;    // stationary rows per workgroup
+constexpr int QT = 64;              // rows per streamed tile
 constexpr int FLUSH = 16;           // tiles between flushes of the short accumulator into the long one
 
 // s_waitcnt vmcnt(v) with the other counters left alone (gfx9 encoding: vmcnt in [3:0] and [15:14])
@@ -43,34 +56,36 @@ __device__ __forceinline__ void memory_order_point() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// One Q tile and its 64 log-sum-exp values, this wave's share: CH loads of 64 x 16 bytes into the
-// 1 KB chunks wave*CH + i of the slot (lane L lands at chunk byte 16*L = tile row chunk*RPC +
-// L/PIECES, LDS piece L%PIECES, and fetches the global piece (L%PIECES) ^ swizzle(row) of its row:
-// qoff[i] is that piece's byte offset from the tile's first row), and one load of 64 x 4 bytes for the
-// tile's log-sum-exp values.  Rows past the end of the head read the last row instead; the caller
+// One streamed tile and (column pass) its 64 log-sum-exp values, this wave's share: CH loads of 64 x 16
+// bytes into the 1 KB chunks wave*CH + i of the slot (lane L lands at chunk byte 16*L = tile row
+// chunk*RPC + L/PIECES, LDS piece L%PIECES, and fetches the global piece (L%PIECES) ^ swizzle(row) of
+// its row: xoff[i] is that piece's byte offset from the row's start), and one load of 64 x 4 bytes for
+// the tile's log-sum-exp values.  Rows past the end of the head read the last row instead; the caller
 // gives them weight zero.
 // (The slot pointer is a restrict parameter so that the loads carry an alias scope: the compiler
 // then does not make LDS reads of the other slots wait for these loads.  A slot is ONE object,
 // the tile followed by its log-sum-exp values: the compiler tells only a handful of such load
 // targets apart, and beyond that number every LDS read waits for every load.)
-template <int CH>
-__device__ __forceinline__ void issue_q_tile(byte* __restrict__ slot, byte* __restrict__ lse_slot,
-                                             const byte* __restrict__ Qg, const float* __restrict__ lse,
-                                             int t, int n, uint32_t row_bytes, const int (&trow)[CH],
-                                             const uint32_t (&qoff)[CH], int wave, int lane) {
+template <int CH, bool ROWS>
+__device__ __forceinline__ void issue_tile(byte* __restrict__ slot, byte* __restrict__ lse_slot,
+                                           const byte* __restrict__ X, const float* __restrict__ lse,
+                                           int t, int n, uint32_t row_bytes, const int (&trow)[CH],
+                                           const uint32_t (&xoff)[CH], int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const int row = t * QT + trow[i];
         // both factors are below 2^24 and the product below 2^32 (checked on the host)
-        const uint32_t off = __umul24((uint32_t)(row < n ? row : n - 1), row_bytes) + qoff[i];
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Qg + off),
+        const uint32_t off = __umul24((uint32_t)(row < n ? row : n - 1), row_bytes) + xoff[i];
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(X + off),
                                          (PULSECOL_LDS void*)(slot + (wave * CH + i) * 1024), 16, 0, 0);
     }
-    // every wave brings all 64 values (the same bytes four times over): no branch in here, which
-    // keeps the compiler's own bookkeeping of these loads exact
-    const int row = t * QT + lane;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(lse + (uint32_t)(row < n ? row : n - 1)),
-                                     (PULSECOL_LDS void*)lse_slot, 4, 0, 0);
+    if constexpr (!ROWS) {
+        // every wave brings all 64 values (the same bytes four times over): no branch in here, which
+        // keeps the compiler's own bookkeeping of these loads exact
+        const int row = t * QT + lane;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(lse + (uint32_t)(row < n ? row : n - 1)),
+                                         (PULSECOL_LDS void*)lse_slot, 4, 0, 0);
+    }
 }
 
 // LDS fragment reads as inline assembly with hand-placed waits.  (The compiler's own wait-count
@@ -95,16 +110,16 @@ __device__ __forceinline__ uint32_t lds_address(const void* generic_lds_ptr) {
     return (uint32_t)(uintptr_t)(PULSECOL_LDS const void*)generic_lds_ptr;
 }
 
-// A tile is two blocks of 32 query rows; a block's scores take 2 * KK matrix instructions (KK
-// fragments of the block's rows, each against the wave's two blocks of 32 keys) and 32 softmax
+// A tile is two blocks of 32 streamed rows; a block's scores take 2 * KK matrix instructions (KK
+// fragments of the block's rows, each against the wave's two blocks of 32 stationary rows) and 32 softmax
 // weights per lane (fma, exp2, add each).  The two kinds of work are interleaved instruction by
 // instruction: while the matrix instructions of a block issue, the weights of the block before it are
 // formed, a few per matrix instruction, so that every wave's instruction stream feeds the matrix pipe
 // and the vector pipe evenly.  (Written as two phases per block -- all matrix instructions, then all
 // weights -- the two waves that share a SIMD fall into step: both in the matrix phase, then both in
 // the vector phase, each pipe idle half of the time.)
-template <int D>
-struct ColWave {
+template <int D, bool ROWS>
+struct ScoreWave {
     static constexpr int PIECES = D / 8;
     static constexpr int KK = D / 16;
     static constexpr int ROW_BYTES = D * 2;
@@ -140,6 +155,7 @@ struct ColWave {
     // it to consume)
     template <bool FIRST>
     static constexpr int lse_reads(int q) {
+        if (ROWS) return 0;
         const int x = q % KK;
         return ((lse_group_consumed(x) >= 0 && !(FIRST && q < KK)) ? 1 : 0) + (lse_group_computed(x) >= 0 ? 1 : 0);
     }
@@ -153,18 +169,29 @@ struct ColWave {
     }
     static_assert(lse_group_consumed(0) < 0 || lse_group_computed(0) < 0, "one log-sum-exp read per pair at most");
 
-    bf16x8 kf[2][KK];         // stationary K fragments: B operand, [key lq of block kb][d = kk*16 + 8*lh .. +7]
-    f32x16 sb[2][2];          // scores [query block qb][key block kb]
-    f32x4 lr[4];              // log-sum-exp (log2 units) of four query rows each, of the block whose weights are being formed
+    bf16x8 yf[2][KK];         // stationary fragments: B operand, [row lq of block kb][d = kk*16 + 8*lh .. +7]
+    f32x16 sb[2][2];          // scores [streamed block qb][stationary block kb]
+    f32x4 lr[4];              // column pass: log-sum-exp (log2 units) of four query rows each, of the block whose weights are being formed
+    float ref[2];             // row pass: the reference (log2 units) of this lane's query rows
     float acc_short[2][4], acc_long[2][4];
-    uint32_t qv[KK];          // LDS address of this lane's fragment kk in slot 0, first block
-    uint32_t lv;              // LDS address of this lane's first log-sum-exp group in ring entry 0
+    uint32_t xv[KK];          // LDS address of this lane's fragment kk in slot 0, first block
+    uint32_t lv;              // column pass: LDS address of this lane's first log-sum-exp group in ring entry 0
     float c2;
 
-    // weight e (0..31) of query block cq: register e / 2, key block e % 2
+    // weight e (0..31) of streamed block cq: register e / 2, stationary block e % 2
     __device__ __forceinline__ void weight(int cq, int e) {
         const int r = e >> 1, kb = e & 1;
-        acc_short[kb][r & 3] += fast_exp2(__builtin_fmaf(sb[cq][kb][r], c2, -lr[r >> 2][r & 3]));
+        acc_short[kb][r & 3] += fast_exp2(__builtin_fmaf(sb[cq][kb][r], c2, ROWS ? -ref[kb] : -lr[r >> 2][r & 3]));
+    }
+    // row pass: the reference from the scores of one streamed block (both half-waves get the same value)
+    __device__ __forceinline__ void set_reference(const f32x16 (&s)[2]) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            float mx = s[kb][0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+            ref[kb] = half_max(mx) * c2;
+        }
     }
     template <int OFF>
     __device__ __forceinline__ void read_lse(int g, uint32_t ring_addr) {
@@ -188,14 +215,14 @@ struct ColWave {
             f32x16 zero;
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-            sb[qb][0] = mfma_bf16(fr[P], kf[0][x], zero);
+            sb[qb][0] = mfma_bf16(fr[P], yf[0][x], zero);
         } else {
-            sb[qb][0] = mfma_bf16(fr[P], kf[0][x], sb[qb][0]);
+            sb[qb][0] = mfma_bf16(fr[P], yf[0][x], sb[qb][0]);
         }
         fence();
         if constexpr (P + AHEAD < NPAIR) {
             constexpr int Q = P + AHEAD;
-            fr[Q] = lds_read_b128_at<SLOT + (Q / KK) * 32 * ROW_BYTES>(qv[Q % KK]);
+            fr[Q] = lds_read_b128_at<SLOT + (Q / KK) * 32 * ROW_BYTES>(xv[Q % KK]);
         }
         if constexpr (CONSUME) {
 #pragma unroll
@@ -206,18 +233,18 @@ struct ColWave {
             f32x16 zero;
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-            sb[qb][1] = mfma_bf16(fr[P], kf[1][x], zero);
+            sb[qb][1] = mfma_bf16(fr[P], yf[1][x], zero);
         } else {
-            sb[qb][1] = mfma_bf16(fr[P], kf[1][x], sb[qb][1]);
+            sb[qb][1] = mfma_bf16(fr[P], yf[1][x], sb[qb][1]);
         }
         fence();
         // the block being consumed: second block of the tile before (qb == 0) or first block of this tile
-        if constexpr (CONSUME && lse_group_consumed(x) >= 0) {
+        if constexpr (!ROWS && CONSUME && lse_group_consumed(x) >= 0) {
             if constexpr (qb == 0) read_lse<32 * 4>(lse_group_consumed(x), ring_prev);
             else read_lse<0>(lse_group_consumed(x), ring_cur);
         }
         // the block being computed, whose weights the next block's pairs will form
-        if constexpr (lse_group_computed(x) >= 0) read_lse<qb * 32 * 4>(lse_group_computed(x), ring_cur);
+        if constexpr (!ROWS && lse_group_computed(x) >= 0) read_lse<qb * 32 * 4>(lse_group_computed(x), ring_cur);
         if constexpr (CONSUME) {
 #pragma unroll
             for (int i = 0; i < PER_SLOT; ++i) weight(cq, x * 2 * PER_SLOT + PER_SLOT + i);
@@ -232,34 +259,58 @@ struct ColWave {
     template <int S>
     __device__ __forceinline__ void request_first(bf16x8 (&fr)[NPAIR]) {
         static_assert(AHEAD == 2 || AHEAD == 4, "written out for two and four");
-        fr[0] = lds_read_b128_at<S * TILE_BYTES>(qv[0]);
-        fr[1] = lds_read_b128_at<S * TILE_BYTES>(qv[1]);
+        fr[0] = lds_read_b128_at<S * TILE_BYTES>(xv[0]);
+        fr[1] = lds_read_b128_at<S * TILE_BYTES>(xv[1]);
         if constexpr (AHEAD == 4) {
-            fr[2] = lds_read_b128_at<S * TILE_BYTES>(qv[2]);
-            fr[3] = lds_read_b128_at<S * TILE_BYTES>(qv[3]);
+            fr[2] = lds_read_b128_at<S * TILE_BYTES>(xv[2]);
+            fr[3] = lds_read_b128_at<S * TILE_BYTES>(xv[3]);
         }
     }
     // The weights of a block outside the interleave (the last full block of a head): the groups that the
     // interleave would have read in the following block are read here.
     __device__ __forceinline__ void weights_alone(int cq, uint32_t ring_addr) {
+        if constexpr (!ROWS) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            if (first_use(g) - LEAD >= 0) {
-                if (g == 1) lr[1] = lds_read_f32x4_at<LSE_BASE + 32 * 4 + 32>(ring_addr);
-                if (g == 2) lr[2] = lds_read_f32x4_at<LSE_BASE + 32 * 4 + 64>(ring_addr);
-                if (g == 3) lr[3] = lds_read_f32x4_at<LSE_BASE + 32 * 4 + 96>(ring_addr);
+            for (int g = 0; g < 4; ++g) {
+                if (first_use(g) - LEAD >= 0) {
+                    if (g == 1) lr[1] = lds_read_f32x4_at<LSE_BASE + 32 * 4 + 32>(ring_addr);
+                    if (g == 2) lr[2] = lds_read_f32x4_at<LSE_BASE + 32 * 4 + 64>(ring_addr);
+                    if (g == 3) lr[3] = lds_read_f32x4_at<LSE_BASE + 32 * 4 + 96>(ring_addr);
+                }
             }
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(lr[0]), "+v"(lr[1]), "+v"(lr[2]), "+v"(lr[3]));
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(lr[0]), "+v"(lr[1]), "+v"(lr[2]), "+v"(lr[3]));
 #pragma unroll
         for (int e = 0; e < 32; ++e) weight(cq, e);
     }
 };
 
-template <int D>
-__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
-colmass_bf16_kernel(ScoreParams p) {
-    using W = ColWave<D>;
+// The tiles [first, last) of run `split` of a streamed range of n rows cut into `splits` runs: whole tiles,
+// as even as they come; with several query groups (unit_rows = rows of a group, column pass) whole groups.
+struct TileRun { int first, last; };
+__device__ __forceinline__ TileRun tile_run(int n, int split, int splits, int unit_rows) {
+    const int tiles = (n + QT - 1) / QT;
+    if (splits == 1) return {0, tiles};
+    // a group of an odd number of 32-row blocks ends inside a tile: two of them make whole tiles
+    const int unit = unit_rows == 0 ? 1 : (unit_rows % QT == 0 ? unit_rows / QT : unit_rows / 32);
+    const int units = (tiles + unit - 1) / unit;
+    const int per = (units + splits - 1) / splits * unit;
+    const int first = split * per < tiles ? split * per : tiles;
+    return {first, first + per < tiles ? first + per : tiles};
+}
+
+// A sum of weights and the reference it was formed against: the sum's exponent goes into the reference as a
+// whole number and leaves a sum in [1, 2), so that partial sums can be added without care for their size and
+// the logarithm that is rounded beside the reference is below one.
+__device__ __forceinline__ void normalise(float& ref, float& sum) {
+    int e;
+    sum = 2.0f * frexpf(sum, &e);
+    ref += (float)(e - 1);
+}
+
+template <int D, bool ROWS>
+__device__ __forceinline__ void score_pass(const ScoreParams& p) {
+    using W = ScoreWave<D, ROWS>;
     constexpr int PIECES = W::PIECES;
     constexpr int KK = W::KK;
     constexpr int ROW_BYTES = W::ROW_BYTES;
@@ -267,80 +318,105 @@ colmass_bf16_kernel(ScoreParams p) {
     constexpr int NPAIR = W::NPAIR;
     constexpr int RPC = 64 / PIECES;                  // tile rows per 1 KB chunk
     constexpr int CH = TILE_BYTES / 1024 / 4;         // chunks per wave and tile
-    constexpr int VM_PER_TILE = CH + 1;               // vector memory operations a wave issues per tile
+    constexpr int VM_PER_TILE = CH + (ROWS ? 0 : 1);  // vector memory operations a wave issues per tile
     static_assert(CH >= 1 && CH * 4 * 1024 == TILE_BYTES, "the waves' chunks cover the tile exactly");
 
     // ONE array: three tile slots, then a ring of four tiles' log-sum-exp values (64 each).  Slot and block
     // are instruction offsets of the fragment reads.  The ring is one entry longer than the slots because the
     // weights of a tile's second block are formed during the first block of the next tile, after the barrier
     // that frees the tile's slot.
-    __shared__ __attribute__((aligned(1024))) byte lds_all[3 * TILE_BYTES + W::LSE_RING * W::LSE_BYTES];
+    __shared__ __attribute__((aligned(1024))) byte lds_all[3 * TILE_BYTES + (ROWS ? 0 : W::LSE_RING * W::LSE_BYTES)];
 
-    const int nkb = (p.n + KEYS_PER_WG - 1) / KEYS_PER_WG;
-    int bh, kblk;
-    if (!xcd_tile(blockIdx.x, nkb, p.batch * p.heads, &bh, &kblk)) return;
+    // item = (head, run, block), blocks innermost: neighbours stream the same tiles
+    const int nblk = (p.n + ROWS_PER_WG - 1) / ROWS_PER_WG;
+    const int splits = ROWS ? p.row_splits : p.col_splits;
+    const int item = xcd_item(blockIdx.x, p.batch * p.heads, splits * nblk);
+    const int run_of_head = item / nblk, blk = item - run_of_head * nblk;
+    const int bh = run_of_head / splits, split = run_of_head - bh * splits;
     const int b = bh / p.heads, h = bh - b * p.heads;
     // variable-length batches: queries and keys of this batch element end at its own length
     const int n = p.varlen != nullptr ? p.varlen[b] : p.n;
-    if (kblk * KEYS_PER_WG >= n) return;    // a block of padding keys: its scores are left untouched
-    const int64_t head_off = (int64_t)b * p.td.sb + (int64_t)h * p.td.sh;
+    if (blk * ROWS_PER_WG >= n) return;     // a block of padding rows: what belongs to it is left untouched
+    const int64_t q_off = (int64_t)b * p.td.sb + (int64_t)h * p.td.sh;
     // grouped-query layout: query head h reads K/V head h / (heads / kv_heads)
-    const int64_t kv_off = (int64_t)b * p.td_kv.sb + (int64_t)(h / (p.heads / p.kv_heads)) * p.td_kv.sh;
-    const byte* __restrict__ Q = (const byte*)((const __bf16*)p.q + head_off);
-    const __bf16* __restrict__ K = (const __bf16*)p.k + kv_off;
+    const int64_t k_off = (int64_t)b * p.td_kv.sb + (int64_t)(h / (p.heads / p.kv_heads)) * p.td_kv.sh;
+    const byte* __restrict__ X = (const byte*)(ROWS ? (const __bf16*)p.k + k_off : (const __bf16*)p.q + q_off);      // streamed
+    const __bf16* __restrict__ Y = ROWS ? (const __bf16*)p.q + q_off : (const __bf16*)p.k + k_off;                   // stationary
+    const int64_t y_stride = ROWS ? p.td.sn : p.td_kv.sn;
+    const uint32_t row_bytes = (uint32_t)(ROWS ? p.td_kv.sn : p.td.sn) * 2u;
     const float* __restrict__ lse = p.lse + (int64_t)bh * p.n;
-    const uint32_t row_bytes = (uint32_t)p.td.sn * 2u;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, lh = lane >> 5;
-    const int key0 = kblk * KEYS_PER_WG + wave * 64;
+    const int y0 = blk * ROWS_PER_WG + wave * 64;
+
+    // the streamed rows of this run: tiles t0 .. t1-1, rows up to x_end
+    const TileRun run = tile_run(n, split, splits, !ROWS && p.groups > 1 ? p.group_size : 0);
+    const int t0 = run.first, t1 = run.last;
+    const int x_end = t1 * QT < n ? t1 * QT : n;
+    const bool partial = splits > 1 && (ROWS || p.groups == 1);
+    const int64_t part_at = ((int64_t)split * p.batch * p.heads + bh) * p.n;      // this run's partial results
+    const int64_t part_words = (int64_t)splits * p.batch * p.heads * p.n;         // row pass: the sums follow the references
+    if (t0 >= t1) {
+        // a run past the end (an element of a padded batch with few tiles): it adds nothing
+        if (partial && y0 + lane < n) {
+            p.part[part_at + y0 + lane] = ROWS ? -INFINITY : 0.f;
+            if (ROWS) p.part[part_words + part_at + y0 + lane] = 0.f;
+        }
+        return;
+    }
 
     W w;
-    // ---- stationary K fragments
+    // ---- stationary fragments
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-        int row = key0 + kb * 32 + lq;
+        int row = y0 + kb * 32 + lq;
         row = row < n ? row : n - 1;
-        const __bf16* src = K + (int64_t)row * p.td_kv.sn + 8 * lh;
+        const __bf16* src = Y + (int64_t)row * y_stride + 8 * lh;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) w.kf[kb][kk] = *(const bf16x8*)(src + kk * 16);
+        for (int kk = 0; kk < KK; ++kk) w.yf[kb][kk] = *(const bf16x8*)(src + kk * 16);
     }
 
     // ---- load geometry of this lane: chunk i of its wave covers tile row trow[i]
     int trow[CH];
-    uint32_t qoff[CH];
+    uint32_t xoff[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         trow[i] = (wave * CH + i) * RPC + lane / PIECES;
-        qoff[i] = (uint32_t)((lane % PIECES) ^ swizzle_k<PIECES>(trow[i])) * 16u;
+        xoff[i] = (uint32_t)((lane % PIECES) ^ swizzle_k<PIECES>(trow[i])) * 16u;
     }
-    // ---- fragment addresses: Q fragment kk of query block qb = tile row qb*32 + lq, piece 2*kk + lh
+    // ---- fragment addresses: fragment kk of streamed block qb = tile row qb*32 + lq, piece 2*kk + lh
     // (rows 32 apart share a swizzle: the block is an instruction offset); log-sum-exp group g of block qb =
     // rows qb*32 + 8*g + 4*lh .. +3
     const uint32_t lds0 = lds_address(lds_all);
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) w.qv[kk] = lds0 + (uint32_t)(lq * ROW_BYTES + (((2 * kk + lh) ^ swizzle_k<PIECES>(lq)) << 4));
+    for (int kk = 0; kk < KK; ++kk) w.xv[kk] = lds0 + (uint32_t)(lq * ROW_BYTES + (((2 * kk + lh) ^ swizzle_k<PIECES>(lq)) << 4));
     w.lv = lds0 + (uint32_t)(16 * lh);
     static_assert(PIECES <= 32, "rows 32 apart share a swizzle");
 
-    const int nfull = n / QT;               // whole tiles: the interleaved steps; a ragged last tile is computed apart
-    const int ntiles = (n + QT - 1) / QT;
+    const int nfull = x_end / QT - t0;      // whole tiles: the interleaved steps; a ragged last tile is computed apart
     w.c2 = p.scale * kLog2e;
-    // per key block kb, this lane's key column; four interleaved partial sums keep the add chains independent
+    w.ref[0] = w.ref[1] = 0.f;
+    // per stationary block kb, this lane's row; four interleaved partial sums keep the add chains independent
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int c = 0; c < 4; ++c) { w.acc_short[kb][c] = 0.f; w.acc_long[kb][c] = 0.f; }
+    // this lane's sum of stationary block kb over both half-waves (they hold the same stationary rows, other streamed rows)
+    auto total = [&](int kb) {
+        return half_sum(((w.acc_long[kb][0] + w.acc_short[kb][0]) + (w.acc_long[kb][1] + w.acc_short[kb][1])) +
+                        ((w.acc_long[kb][2] + w.acc_short[kb][2]) + (w.acc_long[kb][3] + w.acc_short[kb][3])));
+    };
 
-    // rows until the running query group ends (groups are multiples of 32 rows; one group: never)
+    // column pass: rows until the running query group ends (groups are multiples of 32 rows; one group: never;
+    // a run starts at a group's first row)
     int rows_to_group_end = p.groups > 1 ? p.group_size : 0x7fffffff;
 
-    // What follows the weights of block qb of tile t: the periodic flush of the short accumulators and, at
-    // the last rows of a query group (groups are multiples of 32 rows), the group's score row: add the two
-    // half-waves (they hold the same key columns, other query rows), divide by the group's size, store,
-    // start over.
+    // What follows the weights of block qb of the run's tile t: the periodic flush of the short accumulators and,
+    // in the column pass at the last rows of a query group (groups are multiples of 32 rows), the group's score
+    // row: add the two half-waves, divide by the group's size, store, start over.
     auto block_done = [&](int t, int qb) {
         if (qb == 1 && (t % FLUSH) == FLUSH - 1) {
 #pragma unroll
@@ -348,32 +424,34 @@ colmass_bf16_kernel(ScoreParams p) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) { w.acc_long[kb][c] += w.acc_short[kb][c]; w.acc_short[kb][c] = 0.f; }
         }
-        const int rows_done = t * QT + (qb + 1) * 32;
-        rows_to_group_end -= 32;
-        const bool group_end = (rows_done >= n) || (rows_to_group_end == 0 && rows_done < n);
-        if (rows_to_group_end == 0) rows_to_group_end = p.group_size;
-        if (group_end) {
-            const int rows_seen = rows_done < n ? rows_done : n;
-            const int u = p.groups > 1 ? (rows_seen - 1) / p.group_size : 0;
-            const int g_first = p.groups > 1 ? u * p.group_size : 0;
-            const int g_rows = rows_seen - g_first;
-            const float inv = 1.0f / (float)g_rows;
-            float* __restrict__ out = p.scores + ((int64_t)bh * p.groups + u) * p.n;
+        if constexpr (!ROWS) {
+            const int rows_done = (t0 + t) * QT + (qb + 1) * 32;
+            rows_to_group_end -= 32;
+            const bool group_end = (rows_done >= x_end) || (rows_to_group_end == 0 && rows_done < x_end);
+            if (rows_to_group_end == 0) rows_to_group_end = p.group_size;
+            if (group_end) {
+                const int rows_seen = rows_done < x_end ? rows_done : x_end;
+                const int u = p.groups > 1 ? (rows_seen - 1) / p.group_size : 0;
+                const int g_first = p.groups > 1 ? u * p.group_size : 0;
+                const int g_rows = rows_seen - g_first;
+                const float inv = partial ? 1.0f : 1.0f / (float)g_rows;
+                float* __restrict__ out = partial ? p.part + part_at : p.scores + ((int64_t)bh * p.groups + u) * p.n;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const float v = half_sum(((w.acc_long[kb][0] + w.acc_short[kb][0]) + (w.acc_long[kb][1] + w.acc_short[kb][1])) +
-                                         ((w.acc_long[kb][2] + w.acc_short[kb][2]) + (w.acc_long[kb][3] + w.acc_short[kb][3])));
-                const int key = key0 + kb * 32 + lq;
-                if (lh == 0 && key < n) out[key] = v * inv;
+                for (int kb = 0; kb < 2; ++kb) {
+                    const float v = total(kb);
+                    const int key = y0 + kb * 32 + lq;
+                    if (lh == 0 && key < n) out[key] = v * inv;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) { w.acc_long[kb][c] = 0.f; w.acc_short[kb][c] = 0.f; }
+                    for (int c = 0; c < 4; ++c) { w.acc_long[kb][c] = 0.f; w.acc_short[kb][c] = 0.f; }
+                }
             }
         }
     };
     auto ring_of = [&](int t) { return w.lv + (uint32_t)((t & (W::LSE_RING - 1)) * W::LSE_BYTES); };
+    // (t counts the run's tiles: slot and ring entry follow it)
     auto issue = [&](int t) {
-        issue_q_tile<CH>(lds_all + (t % 3) * TILE_BYTES, lds_all + W::LSE_BASE + (t & (W::LSE_RING - 1)) * W::LSE_BYTES,
-                         Q, lse, t, n, row_bytes, trow, qoff, wave, lane);
+        issue_tile<CH, ROWS>(lds_all + (t % 3) * TILE_BYTES, lds_all + W::LSE_BASE + (t & (W::LSE_RING - 1)) * W::LSE_BYTES,
+                             X, lse, t0 + t, n, row_bytes, trow, xoff, wave, lane);
     };
 
     // ---- tiles 0 and 1 go out
@@ -402,6 +480,7 @@ colmass_bf16_kernel(ScoreParams p) {
         // first block of the tile, with the weights of the second block of the tile before
         w.template pairs<S, 0, FIRST>(fr, ring_cur, ring_prev, std::make_integer_sequence<int, KK>{});
         if (!FIRST) block_done(t - 1, 1);
+        if constexpr (ROWS && FIRST) w.set_reference(w.sb[0]);
         // second block, with the weights of the first
         w.template pairs<S, KK, FIRST>(fr, ring_cur, ring_prev, std::make_integer_sequence<int, KK>{});
         block_done(t, 0);
@@ -420,15 +499,15 @@ colmass_bf16_kernel(ScoreParams p) {
         block_done(nfull - 1, 1);
     }
     wait_vmcnt_at_most<0>();
-    if (nfull < ntiles) {
-        // ---- a ragged last tile, in plain code: rows past the end of the head add nothing to any column
+    if (nfull < t1 - t0) {
+        // ---- a ragged last tile, in plain code: rows past the end of the head add nothing to any sum
         memory_order_point();
         __builtin_amdgcn_s_barrier();
         memory_order_point();
         const int t = nfull;
-        const byte* qslot = lds_all + (t % 3) * TILE_BYTES;
+        const byte* xslot = lds_all + (t % 3) * TILE_BYTES;
         const float* lslot = (const float*)(lds_all + W::LSE_BASE + (t & (W::LSE_RING - 1)) * W::LSE_BYTES);
-        const int valid = n - t * QT;
+        const int valid = n - (t0 + t) * QT;
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             if (qb * 32 >= valid) break;
@@ -439,40 +518,177 @@ colmass_bf16_kernel(ScoreParams p) {
                 for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
-                const bf16x8 qfrag = *(const bf16x8*)(qslot + qb * 32 * ROW_BYTES + (w.qv[kk] - lds0));
-                s[0] = mfma_bf16(qfrag, w.kf[0][kk], s[0]);
-                s[1] = mfma_bf16(qfrag, w.kf[1][kk], s[1]);
+                const bf16x8 xfrag = *(const bf16x8*)(xslot + qb * 32 * ROW_BYTES + (w.xv[kk] - lds0));
+                s[0] = mfma_bf16(xfrag, w.yf[0][kk], s[0]);
+                s[1] = mfma_bf16(xfrag, w.yf[1][kk], s[1]);
             }
             f32x4 l2[4];
+            if constexpr (ROWS) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) l2[g] = *(const f32x4*)(lslot + qb * 32 + 8 * g + 4 * lh);
+                for (int r = 0; r < 16; ++r)
+                    if (qb * 32 + acc_row(r, lh) >= valid) { s[0][r] = -INFINITY; s[1][r] = -INFINITY; }
+                if (nfull == 0 && qb == 0) w.set_reference(s);         // finite: the block's first row is valid
+            } else {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) l2[g] = *(const f32x4*)(lslot + qb * 32 + 8 * g + 4 * lh);
+            }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
-                    const float e = fast_exp2(__builtin_fmaf(s[kb][r], w.c2, -l2[r >> 2][r & 3]));
-                    w.acc_short[kb][r & 3] += (qb * 32 + acc_row(r, lh) < valid) ? e : 0.f;
+                    const float e = fast_exp2(__builtin_fmaf(s[kb][r], w.c2, ROWS ? -w.ref[kb] : -l2[r >> 2][r & 3]));
+                    w.acc_short[kb][r & 3] += (ROWS || qb * 32 + acc_row(r, lh) < valid) ? e : 0.f;
                 }
             }
             block_done(t, qb);
         }
     }
+
+    if constexpr (ROWS) {
+        float sum[2] = {total(0), total(1)};
+        if (__builtin_expect(__ballot(!(sum[0] < INFINITY && sum[1] < INFINITY)) != 0ull, 0)) {
+            // Some row of this wave has logits so far above its first 32 that the sum overflowed: the wave's
+            // rows once more, 32 keys at a time straight from memory, with a running maximum.
+            float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
+            for (int x = t0 * QT; x < x_end; x += 32) {
+                const int row = x + lq < x_end ? x + lq : x_end - 1;
+                const byte* src = X + __umul24((uint32_t)row, row_bytes) + 16 * lh;
+                f32x16 s[2];
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    const bf16x8 xfrag = *(const bf16x8*)(src + kk * 32);
+                    s[0] = mfma_bf16(xfrag, w.yf[0][kk], s[0]);
+                    s[1] = mfma_bf16(xfrag, w.yf[1][kk], s[1]);
+                }
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) if (x + acc_row(r, lh) >= x_end) s[kb][r] = -INFINITY;
+                    w.set_reference(s);                                 // of these 32 keys alone
+                    const float up = fmaxf(m[kb], w.ref[kb]);
+                    l[kb] *= fast_exp2(m[kb] - up);
+                    m[kb] = up;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) l[kb] += fast_exp2(__builtin_fmaf(s[kb][r], w.c2, -up));
+                }
+            }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) { w.ref[kb] = m[kb]; sum[kb] = half_sum(l[kb]); }
+        }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const int row = y0 + kb * 32 + lq;
+            normalise(w.ref[kb], sum[kb]);
+            if (lh == 0 && row < n) {
+                if (partial) {
+                    p.part[part_at + row] = w.ref[kb];
+                    p.part[part_words + part_at + row] = sum[kb];
+                } else {
+                    p.lse[(int64_t)bh * p.n + row] = w.ref[kb] + fast_log2(sum[kb]);
+                }
+            }
+        }
+    }
 }
 
 template <int D>
-hipError_t launch(const ScoreParams& p, hipStream_t s) {
-    const int nkb = (p.n + KEYS_PER_WG - 1) / KEYS_PER_WG;
-    const int bh_pad = (p.batch * p.heads + 7) / 8 * 8;
-    hipLaunchKernelGGL((colmass_bf16_kernel<D>), dim3(nkb * bh_pad), dim3(NTHREADS), 0, s, p);
-    return hipGetLastError();
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
+rowlse_bf16_kernel(ScoreParams p) { score_pass<D, true>(p); }
+
+template <int D>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
+colmass_bf16_kernel(ScoreParams p) { score_pass<D, false>(p); }
+
+// ---- partial results of the runs, added up in run order.  One thread per row (row pass) or key (column pass)
+// of a head; latency-bound: the sizes that are split have at most 2^17 of them.
+__global__ void __launch_bounds__(NTHREADS) rowlse_combine_kernel(ScoreParams p, int64_t count) {
+    const int64_t i = (int64_t)blockIdx.x * NTHREADS + threadIdx.x;
+    if (i >= count) return;
+    const float* __restrict__ ref = p.part + i;
+    const float* __restrict__ sum = p.part + (int64_t)p.row_splits * count + i;
+    float m[kMaxScoreSplits], l[kMaxScoreSplits], top = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < kMaxScoreSplits; ++s) {
+        const bool in = s < p.row_splits;
+        m[s] = in ? ref[s * count] : -INFINITY;
+        l[s] = in ? sum[s * count] : 0.f;
+        top = fmaxf(top, m[s]);
+    }
+    float all = 0.f;
+#pragma unroll
+    for (int s = 0; s < kMaxScoreSplits; ++s)
+        if (l[s] != 0.f) all += l[s] * fast_exp2(m[s] - top);
+    normalise(top, all);
+    p.lse[i] = top + fast_log2(all);
+}
+
+__global__ void __launch_bounds__(NTHREADS) colmass_combine_kernel(ScoreParams p, int64_t count) {
+    const int64_t i = (int64_t)blockIdx.x * NTHREADS + threadIdx.x;
+    if (i >= count) return;
+    int n = p.n;
+    if (p.varlen != nullptr) {
+        const int64_t bh = i / p.n;
+        n = p.varlen[bh / p.heads];
+        if (i - bh * p.n >= n) return;       // padding: left untouched
+    }
+    float v[kMaxScoreSplits], all = 0.f;
+#pragma unroll
+    for (int s = 0; s < kMaxScoreSplits; ++s) v[s] = s < p.col_splits ? p.part[s * count + i] : 0.f;
+#pragma unroll
+    for (int s = 0; s < kMaxScoreSplits; ++s) all += v[s];
+    p.scores[i] = all * (1.0f / (float)n);
+}
+
+unsigned grid_of(const ScoreParams& p, int splits) {
+    return (unsigned)((p.n + ROWS_PER_WG - 1) / ROWS_PER_WG * p.batch * p.heads * splits);
+}
+dim3 combine_grid(int64_t count) { return dim3((unsigned)((count + NTHREADS - 1) / NTHREADS)); }
+
+bool splits_fit(const ScoreParams& p, int splits) {
+    return splits == 1 || (splits > 1 && splits <= kMaxScoreSplits && p.part != nullptr);
 }
 
 }  // namespace
 
+// Runs per head and block.  A CU holds two workgroups of either pass; one that is alone on its CU leaves the
+// matrix pipe idle while it forms weights, and a grid smaller than the chip leaves CUs idle altogether.  Below
+// 2 * CUs workgroups the streamed range is cut so that the grid comes as close to that as whole runs allow, in
+// runs of at least four tiles (a run's start, its stationary rows and first tiles from memory, costs about two).
+// Both passes together, D = 128, without and with the cut: 32 heads of 1000 rows 56.4 -> 32.4 us (with the row pass
+// of its own, see above), 4 heads of 8192 rows 264 -> 133 us, 8 heads of 5003 rows in groups of 64 184 -> 114 us.
+int score_splits(int64_t blocks, int32_t longest) {
+    const int64_t room = 2 * (int64_t)compute_units() / blocks;
+    const int64_t tiles = (longest + QT - 1) / QT;
+    const int64_t s = room < tiles / 4 ? room : tiles / 4;
+    return (int)(s < 1 ? 1 : (s > kMaxScoreSplits ? kMaxScoreSplits : s));
+}
+
+hipError_t launch_rowlse_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {
+    if (!splits_fit(p, p.row_splits)) return hipErrorInvalidValue;
+    if (head_dim == 128) hipLaunchKernelGGL((rowlse_bf16_kernel<128>), dim3(grid_of(p, p.row_splits)), dim3(NTHREADS), 0, s, p);
+    else if (head_dim == 64) hipLaunchKernelGGL((rowlse_bf16_kernel<64>), dim3(grid_of(p, p.row_splits)), dim3(NTHREADS), 0, s, p);
+    else return hipErrorInvalidValue;
+    if (p.row_splits > 1) {
+        const int64_t count = (int64_t)p.batch * p.heads * p.n;
+        hipLaunchKernelGGL(rowlse_combine_kernel, combine_grid(count), dim3(NTHREADS), 0, s, p, count);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_colmass_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {
-    if (head_dim == 128) return launch<128>(p, s);
-    if (head_dim == 64) return launch<64>(p, s);
-    return hipErrorInvalidValue;
+    if (!splits_fit(p, p.col_splits)) return hipErrorInvalidValue;
+    if (head_dim == 128) hipLaunchKernelGGL((colmass_bf16_kernel<128>), dim3(grid_of(p, p.col_splits)), dim3(NTHREADS), 0, s, p);
+    else if (head_dim == 64) hipLaunchKernelGGL((colmass_bf16_kernel<64>), dim3(grid_of(p, p.col_splits)), dim3(NTHREADS), 0, s, p);
+    else return hipErrorInvalidValue;
+    if (p.col_splits > 1 && p.groups == 1) {
+        const int64_t count = (int64_t)p.batch * p.heads * p.n;
+        hipLaunchKernelGGL(colmass_combine_kernel, combine_grid(count), dim3(NTHREADS), 0, s, p, count);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace pulsecol

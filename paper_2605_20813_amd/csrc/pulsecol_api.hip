@@ -25,6 +25,9 @@ struct pulsecol_ctx {
     int kv_heads = 1;
     float* lse = nullptr;           // [B*H, n]   row log-sum-exp, log2 units
     float* scores = nullptr;        // [B*H*U, n]
+    float* part = nullptr;          // partial results of split scoring passes; U > 1: in the scores' words
+    int part_splits = 1;            // runs that `part` has room for (1: it has none)
+    int score_splits = 1;           // runs into which the scoring passes cut a head (bf16), at most part_splits
     int32_t* cached_idx = nullptr;  // [B*H*U, cached_k]
     int32_t cached_k = 0;           // 0 = nothing cached
     int32_t k_max = 0;              // columns per group the cache has room for
@@ -137,6 +140,38 @@ void derive_from_shape(pulsecol_ctx* c, const pulsecol_shape* shape, int device)
     }
 }
 
+// Partial results of split scoring passes (bf16).  Per run and row the row pass leaves two words and the column pass,
+// with one query group, one (after the first ones have been used up).  With several groups the column pass leaves
+// none, and the row pass's may lie where the scores will.
+constexpr size_t kPartWords = (size_t)1 << 20;      // what a padded batch gets, whose lengths are not known yet
+
+int splits_of(const pulsecol_ctx* c, const int32_t* lens) {
+    if (c->shape.dtype != PULSECOL_BF16) return 1;
+    int64_t blocks = 0;
+    int32_t longest = 1;
+    for (int32_t b = 0; b < c->shape.batch; ++b) {
+        const int32_t n = lens ? lens[b] : c->shape.seq;
+        blocks += (int64_t)((n + pulsecol::kScoreBlock_bf16 - 1) / pulsecol::kScoreBlock_bf16) * c->shape.heads;
+        longest = n > longest ? n : longest;
+    }
+    return pulsecol::score_splits(blocks, longest);
+}
+size_t row_words(const pulsecol_ctx* c) { return (size_t)c->shape.batch * c->shape.heads * (size_t)c->shape.seq; }
+
+// chooses the number of runs and returns the fp32 words that scores and partial results take
+size_t score_words(pulsecol_ctx* c, bool any_lengths) {
+    c->score_splits = c->part_splits = splits_of(c, nullptr);
+    if (any_lengths && c->shape.batch > 1 && c->shape.dtype == PULSECOL_BF16) {
+        const size_t room = std::min<size_t>(kPartWords / (2 * row_words(c)), pulsecol::kMaxScoreSplits);
+        c->part_splits = std::max(c->part_splits, (int)room);
+    }
+    const size_t part = c->part_splits > 1 ? 2 * (size_t)c->part_splits : 0, groups = (size_t)c->groups;
+    return row_words(c) * (groups == 1 ? 1 + part : std::max(groups, part));
+}
+void place_part(pulsecol_ctx* c) {
+    c->part = c->part_splits > 1 ? c->scores + (c->groups == 1 ? row_words(c) : 0) : nullptr;
+}
+
 struct DeviceGuard {
     int prev = -1;
     bool switched = false;
@@ -202,23 +237,38 @@ pulsecol_status check_ptrs(pulsecol_ctx* ctx, std::initializer_list<const void*>
     return PULSECOL_OK;
 }
 
-// column pass of the scoring stage: ctx->lse (log2 units) must hold the row log-sum-exp of Q, K
-pulsecol_status run_colmass(pulsecol_ctx* ctx, const void* Q, const void* K, float* out, hipStream_t s) {
+pulsecol::ScoreParams score_params(pulsecol_ctx* ctx, const void* Q, const void* K, float* out) {
     pulsecol::ScoreParams sp{};
     sp.q = Q; sp.k = K; sp.lse = ctx->lse; sp.scores = out; sp.td = ctx->td; sp.td_kv = ctx->td_kv; sp.kv_heads = ctx->kv_heads;
     sp.batch = ctx->shape.batch; sp.heads = ctx->shape.heads; sp.n = ctx->shape.seq; sp.scale = ctx->scale;
     sp.groups = ctx->groups; sp.group_size = ctx->shape.group_size;
     sp.varlen = ctx->varlen_on ? ctx->varlen : nullptr;
+    sp.row_splits = ctx->score_splits;
+    // several query groups: a run is made of whole groups (two of them where a group ends inside a 64-row tile)
+    const int units = ctx->groups > 1 && sp.group_size % 64 != 0 ? (ctx->groups + 1) / 2 : ctx->groups;
+    sp.col_splits = ctx->groups > 1 && units < ctx->score_splits ? units : ctx->score_splits;
+    sp.part = ctx->part;
+    return sp;
+}
+
+// column pass of the scoring stage: ctx->lse (log2 units) must hold the row log-sum-exp of Q, K
+pulsecol_status run_colmass(pulsecol_ctx* ctx, const void* Q, const void* K, float* out, hipStream_t s) {
+    const pulsecol::ScoreParams sp = score_params(ctx, Q, K, out);
     const hipError_t e = ctx->shape.dtype == PULSECOL_BF16 ? pulsecol::launch_colmass_bf16(sp, ctx->shape.head_dim, s)
                                                            : pulsecol::launch_colmass_f32(sp, ctx->shape.head_dim, s);
     if (e != hipSuccess) return fail_hip(ctx, e, "column-mass kernel");
     return PULSECOL_OK;
 }
 
-// scores of the current Q, K into `out` (two launches: row pass, column pass)
+// scores of the current Q, K into `out`: row pass, column pass
 pulsecol_status run_scores(pulsecol_ctx* ctx, const void* Q, const void* K, float* out, hipStream_t s) {
-    pulsecol::AttnParams ap = attn_params(ctx, Q, K, nullptr, nullptr, nullptr, ctx->shape.seq, ctx->lse, 1);
-    const hipError_t e = launch_attn(ctx, ap, pulsecol::kLseOnly, s);
+    hipError_t e;
+    if (ctx->shape.dtype == PULSECOL_BF16) {
+        e = pulsecol::launch_rowlse_bf16(score_params(ctx, Q, K, out), ctx->shape.head_dim, s);
+    } else {
+        const pulsecol::AttnParams ap = attn_params(ctx, Q, K, nullptr, nullptr, nullptr, ctx->shape.seq, ctx->lse, 1);
+        e = pulsecol::launch_attn_f32(ap, ctx->shape.head_dim, pulsecol::kLseOnly, s);
+    }
     if (e != hipSuccess) return fail_hip(ctx, e, "row log-sum-exp kernel");
     return run_colmass(ctx, Q, K, out, s);
 }
@@ -255,36 +305,29 @@ pulsecol_status run_topk(pulsecol_ctx* ctx, const float* scores, int32_t k, int3
 }
 
 // ---- scratch of the entry point that allocates nothing (pulsecol_select_noalloc)
-// A file-scope device array, one copy per GPU, held until the process ends: 256 bytes of work
-// counters, then room for kNoallocFloats fp32 words (row log-sum-exp [B*H, n], then scores
-// [B*H*U, n]).  The array's name is only a host-side stand-in for the symbol; the address of a
+// A file-scope device array, one copy per GPU, held until the process ends: kNoallocFloats fp32
+// words (row log-sum-exp [B*H, n], then scores [B*H*U, n] and partial results).  The array's name is only a host-side stand-in for the symbol; the address of a
 // device's copy comes from hipGetSymbolAddress, asked once per device with that device current.
 constexpr size_t kNoallocFloats = (size_t)4 << 20;                 // 16 MiB
-constexpr size_t kNoallocCounterBytes = 256;
-static __device__ __align__(256) unsigned char scratch[kNoallocCounterBytes + kNoallocFloats * sizeof(float)];
+static __device__ __align__(256) float scratch[kNoallocFloats];
 
-struct NoallocDevice {
-    unsigned char* ptr = nullptr;     // this device's copy of `scratch`
-    uint32_t stamp = 0;               // stamp of the last launch that used its work counters
-};
 constexpr int kMaxDevices = 64;
-NoallocDevice g_noalloc[kMaxDevices];
+float* g_noalloc[kMaxDevices];        // each device's copy of `scratch`
 std::mutex g_noalloc_mutex;
 
 // the current device's copy of the scratch array (nullptr + *err on failure)
-NoallocDevice* noalloc_device(int dev, hipError_t* err) {
+float* noalloc_scratch(int dev, hipError_t* err) {
     std::lock_guard<std::mutex> lock(g_noalloc_mutex);
-    NoallocDevice* d = &g_noalloc[dev];
-    if (d->ptr == nullptr) {
-        unsigned char* ptr = nullptr;
+    if (g_noalloc[dev] == nullptr) {
+        float* ptr = nullptr;
         *err = hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch));
         if (*err != hipSuccess || ptr == nullptr) {
             if (*err == hipSuccess) *err = hipErrorInvalidSymbol;
             return nullptr;
         }
-        d->ptr = ptr;
+        g_noalloc[dev] = ptr;
     }
-    return d;
+    return g_noalloc[dev];
 }
 
 // what the block-sparse calls need of a context: the hand-scheduled bf16 kernel (whole 256-row query blocks
@@ -331,7 +374,7 @@ pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape,
     const size_t rows = (size_t)shape->batch * shape->heads;
     const size_t row_bytes = (size_t)shape->seq * sizeof(float);
     hipError_t e1 = hipMalloc((void**)&c->lse, rows * row_bytes);
-    hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, rows * c->groups * row_bytes) : e1;
+    hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, score_words(c, true) * sizeof(float)) : e1;
     c->k_max = shape->max_keep_ratio > 0.0 ? pulsecol_num_keep(shape->seq, shape->max_keep_ratio) : shape->seq;
     hipError_t e3 = e2 == hipSuccess ? hipMalloc((void**)&c->cached_idx, rows * c->groups * (size_t)c->k_max * sizeof(int32_t)) : e2;
     static_assert(64 + pulsecol::kWorkCounters * sizeof(unsigned long long) <= 256, "counter block");
@@ -350,6 +393,7 @@ pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape,
         return e3 == hipErrorOutOfMemory ? fail(nullptr, PULSECOL_ERR_OOM, "pulsecol_create: scratch allocation failed")
                                          : fail_hip(nullptr, e3, "pulsecol_create: hipMalloc");
     }
+    place_part(c);
     const char* env = std::getenv("PULSECOL_VALIDATE");
     c->validate = env != nullptr && env[0] != '\0' && env[0] != '0';
     *out = c;
@@ -372,7 +416,11 @@ pulsecol_status pulsecol_set_attn_block(pulsecol_ctx* ctx, int32_t block_m) {
 
 pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens, void* stream) {
     if (!ctx) return fail(nullptr, PULSECOL_ERR_INVALID_ARG, "pulsecol_set_seq_lens: ctx is NULL");
-    if (!seq_lens) { ctx->varlen_on = false; return PULSECOL_OK; }
+    if (!seq_lens) {
+        ctx->varlen_on = false;
+        ctx->score_splits = splits_of(ctx, nullptr);
+        return PULSECOL_OK;
+    }
     const int32_t B = ctx->shape.batch;
     for (int32_t b = 0; b < B; ++b)
         if (seq_lens[b] < 1 || seq_lens[b] > ctx->shape.seq)
@@ -390,6 +438,7 @@ pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens
         if (e != hipSuccess) { ctx->varlen_on = false; return fail_hip(ctx, e, "pulsecol_set_seq_lens: storing the lengths"); }
     }
     ctx->varlen_on = true;
+    ctx->score_splits = std::min(splits_of(ctx, seq_lens), ctx->part_splits);
     ctx->cached_k = 0;            // a cached pattern belongs to the lengths it was selected with
     return PULSECOL_OK;
 }
@@ -480,18 +529,17 @@ pulsecol_status pulsecol_select_noalloc(const pulsecol_shape* shape, const void*
     derive_from_shape(&c, shape, dev);
     const size_t rows = (size_t)shape->batch * shape->heads;
     const size_t need = rows * (size_t)shape->seq * (1 + (size_t)c.groups);
-    if (need > kNoallocFloats)
+    // (a shape whose passes are split has at most 2^16 rows over all heads, and with kMaxScoreSplits runs of two
+    //  words each it stays far below the limit: what fits unsplit fits split)
+    if (need > kNoallocFloats || rows * (size_t)shape->seq + score_words(&c, false) > kNoallocFloats)
         return fail(nullptr, PULSECOL_ERR_UNSUPPORTED,
                     "pulsecol_select_noalloc: batch*heads*seq*(1 + groups) = " + std::to_string(need) +
                     " exceeds the static scratch of " + std::to_string(kNoallocFloats) + " fp32 words");
-    NoallocDevice* d = noalloc_device(dev, &e);
-    if (!d) return fail_hip(nullptr, e, "pulsecol_select_noalloc: hipGetSymbolAddress");
-    c.work = reinterpret_cast<unsigned long long*>(d->ptr);
-    c.work_stamp = d->stamp;                          // the launch takes the next stamp: stale counters restart themselves
-    c.lse = reinterpret_cast<float*>(d->ptr + kNoallocCounterBytes);
+    c.lse = noalloc_scratch(dev, &e);
+    if (!c.lse) return fail_hip(nullptr, e, "pulsecol_select_noalloc: hipGetSymbolAddress");
     c.scores = c.lse + rows * (size_t)shape->seq;
+    place_part(&c);
     st = run_scores(&c, Q, K, c.scores, (hipStream_t)stream);
-    d->stamp = c.work_stamp;
     if (st == PULSECOL_OK) st = run_topk(&c, c.scores, k, idx_out, (hipStream_t)stream);
     if (st != PULSECOL_OK) g_last_error = "pulsecol_select_noalloc: " + c.last_error;
     return st;

@@ -82,4 +82,15 @@ __device__ __forceinline__ bool xcd_tile(int wg, int nqb, int bh, int* out_bh, i
     return *out_bh < bh;
 }
 
+// Workgroup id -> item, head * per_head + j, the grid being heads * per_head workgroups.  Whole heads go to one XCD
+// each, eight at a time (workgroup ids are dealt round-robin over the XCDs, each with its own L2), so that the rows
+// that a head's workgroups share are fetched into a single L2; the items of up to seven heads that are left over are
+// dealt one by one, so that all XCDs are in use however few heads there are.
+__device__ __forceinline__ int xcd_item(int wg, int heads, int per_head) {
+    const int whole = heads & ~7;
+    if (wg >= whole * per_head) return wg;
+    const int slot = wg >> 3, hh = slot / per_head;
+    return (hh * 8 + (wg & 7)) * per_head + (slot - hh * per_head);
+}
+
 }  // namespace pulsecol

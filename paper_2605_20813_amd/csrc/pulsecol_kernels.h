@@ -42,7 +42,7 @@ constexpr int kWorkCounters = 8;
 struct ScoreParams {
     const void* q;
     const void* k;
-    const float* lse;        // [B*H, n], log2 units: log2 sum_j exp(z_ij)
+    float* lse;              // [B*H, n], log2 units: log2 sum_j exp(z_ij) (row pass: out, column pass: in)
     float* scores;           // [B*H*groups, n]
     TensorDesc td;           // Q: [B, heads, n, D]
     TensorDesc td_kv;        // K: [B, kv_heads, n, D]; query head h reads K head h / (heads / kv_heads)
@@ -52,7 +52,18 @@ struct ScoreParams {
     int32_t group_size;      // rows per group, a multiple of the kernel's query tile (unused when U = 1)
     float scale;
     const int32_t* varlen;   // as in AttnParams (only the lengths are read); scores beyond them are left untouched
+    // bf16: runs into which the streamed range of a head is cut (1 = not at all), row and column pass, and room for
+    // the runs' partial results: [2 * row_splits, B*H, n] and, with one query group, [col_splits, B*H, n] (used one
+    // after the other; may be nullptr if nothing is split; with more than one group it may be `scores` itself)
+    int32_t row_splits, col_splits;
+    float* part;
 };
+
+constexpr int kMaxScoreSplits = 8;
+constexpr int kScoreBlock_bf16 = 256;     // stationary rows per workgroup
+// runs per block that fill the chip in a scoring pass with this many blocks of stationary rows over all heads, the
+// longest head having `longest` rows (bf16)
+int score_splits(int64_t blocks, int32_t longest);
 
 struct TopkParams {
     const float* scores;     // [rows, n], consecutive rows `stride` elements apart (a multiple of 4 where n is)
@@ -84,6 +95,7 @@ hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, AttnMode mode, hi
 // column-sparse attention with query blocks of block_m = 32, 64 or 128 rows (small query groups)
 hipError_t launch_attn_bf16_group(const AttnParams& p, int head_dim, int block_m, hipStream_t s);
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, AttnMode mode, hipStream_t s);
+hipError_t launch_rowlse_bf16(const ScoreParams& p, int head_dim, hipStream_t s);
 hipError_t launch_colmass_bf16(const ScoreParams& p, int head_dim, hipStream_t s);
 hipError_t launch_colmass_f32(const ScoreParams& p, int head_dim, hipStream_t s);
 hipError_t launch_topk(const TopkParams& p, hipStream_t s);
