@@ -327,19 +327,25 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
     // that frees the tile's slot.
     __shared__ __attribute__((aligned(1024))) byte lds_all[3 * TILE_BYTES + (ROWS ? 0 : W::LSE_RING * W::LSE_BYTES)];
 
-    // item = (head, run, block), blocks innermost: neighbours stream the same tiles
-    const int nblk = (p.n + ROWS_PER_WG - 1) / ROWS_PER_WG;
+    // every kernel argument with the first batch of scalar loads: left to itself the compiler loads them where they
+    // are first used, one memory round trip after another
+    asm volatile("" : : "s"(p.q), "s"(p.k), "s"(p.lse), "s"(p.scores), "s"(p.td.sb), "s"(p.td.sh), "s"(p.td.sn),
+                         "s"(p.td_kv.sb), "s"(p.td_kv.sh), "s"(p.td_kv.sn), "s"(p.kv_heads), "s"(p.batch), "s"(p.heads),
+                         "s"(p.n), "s"(p.groups), "s"(p.group_size), "s"(p.scale), "s"(p.varlen), "s"(p.part),
+                         "s"(ROWS ? p.row_splits : p.col_splits));
+    // (run `split` of the head's streamed range: the z planes; only few layers of heads are ever cut into runs)
     const int splits = ROWS ? p.row_splits : p.col_splits;
-    const int item = xcd_item(blockIdx.x, p.batch * p.heads, splits * nblk);
-    const int run_of_head = item / nblk, blk = item - run_of_head * nblk;
-    const int bh = run_of_head / splits, split = run_of_head - bh * splits;
-    const int b = bh / p.heads, h = bh - b * p.heads;
+    const int split = splits > 1 ? blockIdx.z : 0;
+    int bh, blk, b, h;
+    if (!head_and_block(splits > 1 ? blockIdx.y : blockIdx.z * kLayersPerZ + blockIdx.y, p.batch * p.heads,
+                        (p.n + ROWS_PER_WG - 1) / ROWS_PER_WG, &bh, &blk)) return;
+    split_head(bh, p.batch, p.heads, &b, &h);
     // variable-length batches: queries and keys of this batch element end at its own length
     const int n = p.varlen != nullptr ? p.varlen[b] : p.n;
     if (blk * ROWS_PER_WG >= n) return;     // a block of padding rows: what belongs to it is left untouched
     const int64_t q_off = (int64_t)b * p.td.sb + (int64_t)h * p.td.sh;
     // grouped-query layout: query head h reads K/V head h / (heads / kv_heads)
-    const int64_t k_off = (int64_t)b * p.td_kv.sb + (int64_t)(h / (p.heads / p.kv_heads)) * p.td_kv.sh;
+    const int64_t k_off = (int64_t)b * p.td_kv.sb + (int64_t)kv_head_of(h, p.heads, p.kv_heads) * p.td_kv.sh;
     const byte* __restrict__ X = (const byte*)(ROWS ? (const __bf16*)p.k + k_off : (const __bf16*)p.q + q_off);      // streamed
     const __bf16* __restrict__ Y = ROWS ? (const __bf16*)p.q + q_off : (const __bf16*)p.k + k_off;                   // stationary
     const int64_t y_stride = ROWS ? p.td.sn : p.td_kv.sn;
@@ -643,13 +649,16 @@ __global__ void __launch_bounds__(NTHREADS) colmass_combine_kernel(ScoreParams p
     p.scores[i] = all * (1.0f / (float)n);
 }
 
-unsigned grid_of(const ScoreParams& p, int splits) {
-    return (unsigned)((p.n + ROWS_PER_WG - 1) / ROWS_PER_WG * p.batch * p.heads * splits);
+dim3 grid_of(const ScoreParams& p, int splits) {
+    dim3 g = head_grid((int64_t)p.batch * p.heads, (p.n + ROWS_PER_WG - 1) / ROWS_PER_WG);
+    if (splits > 1) g.z = splits;
+    return g;
 }
 dim3 combine_grid(int64_t count) { return dim3((unsigned)((count + NTHREADS - 1) / NTHREADS)); }
 
 bool splits_fit(const ScoreParams& p, int splits) {
-    return splits == 1 || (splits > 1 && splits <= kMaxScoreSplits && p.part != nullptr);
+    return splits == 1 || (splits > 1 && splits <= kMaxScoreSplits && p.part != nullptr &&
+                           (int64_t)p.batch * p.heads <= 8 * (int64_t)kLayersPerZ);
 }
 
 }  // namespace
@@ -669,8 +678,8 @@ int score_splits(int64_t blocks, int32_t longest) {
 
 hipError_t launch_rowlse_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {
     if (!splits_fit(p, p.row_splits)) return hipErrorInvalidValue;
-    if (head_dim == 128) hipLaunchKernelGGL((rowlse_bf16_kernel<128>), dim3(grid_of(p, p.row_splits)), dim3(NTHREADS), 0, s, p);
-    else if (head_dim == 64) hipLaunchKernelGGL((rowlse_bf16_kernel<64>), dim3(grid_of(p, p.row_splits)), dim3(NTHREADS), 0, s, p);
+    if (head_dim == 128) hipLaunchKernelGGL((rowlse_bf16_kernel<128>), grid_of(p, p.row_splits), dim3(NTHREADS), 0, s, p);
+    else if (head_dim == 64) hipLaunchKernelGGL((rowlse_bf16_kernel<64>), grid_of(p, p.row_splits), dim3(NTHREADS), 0, s, p);
     else return hipErrorInvalidValue;
     if (p.row_splits > 1) {
         const int64_t count = (int64_t)p.batch * p.heads * p.n;
@@ -681,8 +690,8 @@ hipError_t launch_rowlse_bf16(const ScoreParams& p, int head_dim, hipStream_t s)
 
 hipError_t launch_colmass_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {
     if (!splits_fit(p, p.col_splits)) return hipErrorInvalidValue;
-    if (head_dim == 128) hipLaunchKernelGGL((colmass_bf16_kernel<128>), dim3(grid_of(p, p.col_splits)), dim3(NTHREADS), 0, s, p);
-    else if (head_dim == 64) hipLaunchKernelGGL((colmass_bf16_kernel<64>), dim3(grid_of(p, p.col_splits)), dim3(NTHREADS), 0, s, p);
+    if (head_dim == 128) hipLaunchKernelGGL((colmass_bf16_kernel<128>), grid_of(p, p.col_splits), dim3(NTHREADS), 0, s, p);
+    else if (head_dim == 64) hipLaunchKernelGGL((colmass_bf16_kernel<64>), grid_of(p, p.col_splits), dim3(NTHREADS), 0, s, p);
     else return hipErrorInvalidValue;
     if (p.col_splits > 1 && p.groups == 1) {
         const int64_t count = (int64_t)p.batch * p.heads * p.n;

@@ -205,9 +205,12 @@ pulsecol::AttnParams attn_params(pulsecol_ctx* c, const void* Q, const void* K, 
 // sets: the largest block that divides the group size.  One set per head: the hand-scheduled kernel
 // with 256-row blocks, except for short jobs, where its fixed costs (one workgroup per CU, a long
 // start-up per launch and per query block) outweigh its faster steady state and the plain kernel
-// with 128-row blocks, three to a CU, finishes first.  The rule is a two-line cost model fitted to
-// launches at 4K to 16K context (microseconds; R = 256-row blocks per CU, t = 64-column tiles):
-//   scheduled: 33 + R (8.7 + 1.64 t)      plain: 12.6 + R (3.1 + 2.23 t)
+// with 128-row blocks, two to a CU, finishes first.  The rule is a two-line cost model per head dimension
+// (microseconds; R = 256-row blocks per CU, t = 64-column tiles), fitted to launches of 2 to 32 heads at 1K to 32K
+// context and keep 5 to 25%; on those it picks the slower kernel only where the two are within 6% of each other.
+//   D = 128  scheduled 40 + R (2.6 + 1.55 t)   plain 5 + R (3.2 + 1.92 t)
+//   D = 64   scheduled 37 + R (2.9 + 0.95 t)   plain 4 + R (1.9 + 1.15 t)
+// D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.9 / 68.1 us, 8K 120 / 133, 16K 437 / 387.
 int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
     if (c->shape.dtype != PULSECOL_BF16) return pulsecol::kBlockM_f32;
     if (c->groups == 1) {
@@ -215,7 +218,9 @@ int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
         const double blocks = (double)((c->shape.seq + 255) / 256) * c->shape.batch * c->shape.heads;
         const double R = blocks / (double)pulsecol::compute_units();
         const double t = (double)((ns + 63) / 64);
-        const double scheduled = 33.0 + R * (8.7 + 1.64 * t), plain = 12.6 + R * (3.1 + 2.23 * t);
+        const bool wide = c->shape.head_dim == 128;
+        const double scheduled = wide ? 40.0 + R * (2.6 + 1.55 * t) : 37.0 + R * (2.9 + 0.95 * t);
+        const double plain = wide ? 5.0 + R * (3.2 + 1.92 * t) : 4.0 + R * (1.9 + 1.15 * t);
         return plain < scheduled ? 128 : pulsecol::kBlockM_bf16;
     }
     for (int bm : {256, 128, 64}) if (c->shape.group_size % bm == 0) return bm;

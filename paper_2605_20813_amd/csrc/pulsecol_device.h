@@ -82,15 +82,35 @@ __device__ __forceinline__ bool xcd_tile(int wg, int nqb, int bh, int* out_bh, i
     return *out_bh < bh;
 }
 
-// Workgroup id -> item, head * per_head + j, the grid being heads * per_head workgroups.  Whole heads go to one XCD
-// each, eight at a time (workgroup ids are dealt round-robin over the XCDs, each with its own L2), so that the rows
-// that a head's workgroups share are fetched into a single L2; the items of up to seven heads that are left over are
-// dealt one by one, so that all XCDs are in use however few heads there are.
-__device__ __forceinline__ int xcd_item(int wg, int heads, int per_head) {
-    const int whole = heads & ~7;
-    if (wg >= whole * per_head) return wg;
-    const int slot = wg >> 3, hh = slot / per_head;
-    return (hh * 8 + (wg & 7)) * per_head + (slot - hh * per_head);
+// Grid of kernels whose workgroups belong to (head, block j of per_head): x = 8 * per_head, y and z the layers of eight
+// heads.  Workgroup ids are dealt round-robin over the XCDs, each with its own L2, so x % 8 is the XCD: it gets whole
+// heads, one per layer, and the rows that a head's workgroups share are fetched into a single L2.  The blocks of a last
+// layer of fewer than eight heads are dealt one by one instead, so that all XCDs are in use however few heads there
+// are; its surplus workgroups have nothing to do.  (No division but there: one costs some forty instructions in front
+// of everything else a workgroup does.)
+constexpr unsigned kLayersPerZ = 32768;      // y and z are limited to 65535
+__device__ __forceinline__ bool head_and_block(int layer, int heads, int per_head, int* head, int* block) {
+    const int x = blockIdx.x;
+    *block = x >> 3;
+    *head = layer * 8 + (x & 7);
+    if (__builtin_expect(layer * 8 + 8 > heads, 0)) {
+        const int left = heads - layer * 8;
+        if (x >= left * per_head) return false;
+        const int i = x / per_head;
+        *head = layer * 8 + i;
+        *block = x - i * per_head;
+    }
+    return true;
 }
+// batch element and head of a head counted over the batch; the K/V head that a query head reads
+__device__ __forceinline__ void split_head(int bh, int batch, int heads, int* b, int* h) {
+    *b = 0;
+    *h = bh;
+    if (batch > 1) {
+        *b = bh / heads;
+        *h = bh - *b * heads;
+    }
+}
+__device__ __forceinline__ int kv_head_of(int h, int heads, int kv_heads) { return heads == kv_heads ? h : h / (heads / kv_heads); }
 
 }  // namespace pulsecol

@@ -88,6 +88,13 @@ constexpr int kBlockN_bf16 = 64;    // gathered columns per tile
 constexpr int kBlockM_f32 = 128;    // 4 waves x 32
 constexpr int kBlockN_f32 = 32;
 
+// grid of a kernel that places its workgroups with head_and_block
+inline dim3 head_grid(int64_t heads, int per_head) {
+    const unsigned layers = (unsigned)((heads + 7) / 8);
+    const unsigned y = layers < 32768u ? layers : 32768u;
+    return dim3(8u * (unsigned)per_head, y, (layers + y - 1) / y);
+}
+
 // compute units of the current device (cached per device; 256 if the runtime does not say)
 int compute_units();
 

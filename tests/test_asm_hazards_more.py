@@ -1,0 +1,22 @@
+"""The static check of test_asm_hazards.py on the other kernels that issue loads from inline assembly: the row pass and
+the plain attention kernel."""
+import os
+import shutil
+
+import pytest
+
+from test_asm_hazards import _assembly_of, check_function, kernels_of
+
+# file, kernel name, instantiations (row pass: two head dimensions; attention: also four workgroup shapes)
+CHECKED = [("colmass_bf16.hip", "rowlse_bf16_kernel", 2), ("attn_bf16_group.hip", "attn_bf16_group_kernel", 8)]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+@pytest.mark.parametrize("source,kernel,count", CHECKED)
+def test_no_instruction_touches_an_assembly_issued_load_in_flight(source, kernel, count):
+    found = 0
+    for name, lines in kernels_of(_assembly_of(source), kernel):
+        found += 1
+        bad = check_function(lines)
+        assert not bad, "%s: %d hazards, first: line %d `%s` touches %s" % (name, len(bad), bad[0][0], bad[0][1], bad[0][2])
+    assert found == count
