@@ -278,35 +278,28 @@ pulsecol_status run_scores(pulsecol_ctx* ctx, const void* Q, const void* K, floa
     return run_colmass(ctx, Q, K, out, s);
 }
 
-// top-k of ctx->scores into idx_out, and into the context's cache
-pulsecol_status run_topk(pulsecol_ctx* ctx, const float* scores, int32_t k, int32_t* out, hipStream_t s);
-
-pulsecol_status select_from_scores(pulsecol_ctx* ctx, double keep_ratio, int32_t k, int32_t* idx_out, hipStream_t s, const char* who) {
-    if (ctx->varlen_on) {
-        // every batch element keeps max(1, floor(keep_ratio * its own length)) columns
-        const hipError_t ev = pulsecol::launch_varlen_kept_from_ratio(ctx->varlen, ctx->shape.batch, keep_ratio, s);
-        if (ev != hipSuccess) return fail_hip(ctx, ev, (std::string(who) + ": per-element keep counts").c_str());
-    }
-    pulsecol_status st = run_topk(ctx, ctx->scores, k, idx_out, s);
-    if (st != PULSECOL_OK) return st;
-    ctx->cached_k = 0;
-    const size_t idx_bytes = (size_t)ctx->shape.batch * ctx->shape.heads * ctx->groups * (size_t)k * sizeof(int32_t);
-    const hipError_t e = hipMemcpyAsync(ctx->cached_idx, idx_out, idx_bytes, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return fail_hip(ctx, e, (std::string(who) + ": caching the pattern").c_str());
-    ctx->cached_k = k;
-    return PULSECOL_OK;
-}
-
-pulsecol_status run_topk(pulsecol_ctx* ctx, const float* scores, int32_t k, int32_t* out, hipStream_t s) {
+// top-k of a score array into `out` and, if given, `copy`
+// (variable-length batches: keep_ratio > 0: every element keeps max(1, floor(keep_ratio * its own length)) columns, else
+//  min(k, its length))
+pulsecol_status run_topk(pulsecol_ctx* ctx, const float* scores, int32_t k, double keep_ratio, int32_t* out, int32_t* copy, hipStream_t s) {
     pulsecol::TopkParams tp{};
-    tp.scores = scores; tp.idx = out;
+    tp.scores = scores; tp.idx = out; tp.idx_copy = copy;
     tp.rows = ctx->shape.batch * ctx->shape.heads * ctx->groups; tp.n = ctx->shape.seq; tp.k = k; tp.stride = ctx->shape.seq;
     tp.varlen = ctx->varlen_on ? ctx->varlen : nullptr;
+    tp.keep_ratio = keep_ratio;
     tp.batch = ctx->shape.batch; tp.rows_per_batch = ctx->shape.heads * ctx->groups;
     tp.groups = ctx->groups; tp.group_size = ctx->shape.group_size;
     const hipError_t e = pulsecol::launch_topk(tp, s);
     if (e != hipSuccess) return fail_hip(ctx, e, "top-k kernel");
     return PULSECOL_OK;
+}
+
+// top-k of ctx->scores into idx_out, and into the context's cache
+pulsecol_status select_from_scores(pulsecol_ctx* ctx, double keep_ratio, int32_t k, int32_t* idx_out, hipStream_t s) {
+    ctx->cached_k = 0;
+    const pulsecol_status st = run_topk(ctx, ctx->scores, k, keep_ratio, idx_out, ctx->cached_idx, s);
+    if (st == PULSECOL_OK) ctx->cached_k = k;
+    return st;
 }
 
 // ---- scratch of the entry point that allocates nothing (pulsecol_select_noalloc)
@@ -481,11 +474,7 @@ pulsecol_status pulsecol_topk(pulsecol_ctx* ctx, const float* scores, int32_t k,
     if (k < 1 || k > ctx->shape.seq) return fail(ctx, PULSECOL_ERR_INVALID_ARG, "pulsecol_topk: need 1 <= k <= seq");
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return fail_hip(ctx, guard.err, "pulsecol_topk: hipSetDevice");
-    if (ctx->varlen_on) {
-        const hipError_t ev = pulsecol::launch_varlen_kept_from_k(ctx->varlen, ctx->shape.batch, k, (hipStream_t)stream);
-        if (ev != hipSuccess) return fail_hip(ctx, ev, "pulsecol_topk: per-element keep counts");
-    }
-    return run_topk(ctx, scores, k, idx_out, (hipStream_t)stream);
+    return run_topk(ctx, scores, k, 0.0, idx_out, nullptr, (hipStream_t)stream);
 }
 
 pulsecol_status pulsecol_select(pulsecol_ctx* ctx, const void* Q, const void* K, double keep_ratio, int refresh,
@@ -512,7 +501,7 @@ pulsecol_status pulsecol_select(pulsecol_ctx* ctx, const void* Q, const void* K,
     if (guard.err != hipSuccess) return fail_hip(ctx, guard.err, "pulsecol_select: hipSetDevice");
     st = run_scores(ctx, Q, K, ctx->scores, s);
     if (st != PULSECOL_OK) return st;
-    return select_from_scores(ctx, keep_ratio, k, idx_out, s, "pulsecol_select");
+    return select_from_scores(ctx, keep_ratio, k, idx_out, s);
 }
 
 pulsecol_status pulsecol_select_noalloc(const pulsecol_shape* shape, const void* Q, const void* K, double keep_ratio,
@@ -545,7 +534,7 @@ pulsecol_status pulsecol_select_noalloc(const pulsecol_shape* shape, const void*
     c.scores = c.lse + rows * (size_t)shape->seq;
     place_part(&c);
     st = run_scores(&c, Q, K, c.scores, (hipStream_t)stream);
-    if (st == PULSECOL_OK) st = run_topk(&c, c.scores, k, idx_out, (hipStream_t)stream);
+    if (st == PULSECOL_OK) st = run_topk(&c, c.scores, k, keep_ratio, idx_out, nullptr, (hipStream_t)stream);
     if (st != PULSECOL_OK) g_last_error = "pulsecol_select_noalloc: " + c.last_error;
     return st;
 }
@@ -568,7 +557,7 @@ pulsecol_status pulsecol_refresh_dense(pulsecol_ctx* ctx, const void* Q, const v
     if (e != hipSuccess) return fail_hip(ctx, e, "dense attention kernel");
     st = run_colmass(ctx, Q, K, ctx->scores, s);
     if (st != PULSECOL_OK) return st;
-    return select_from_scores(ctx, keep_ratio, k, idx_out, s, "pulsecol_refresh_dense");
+    return select_from_scores(ctx, keep_ratio, k, idx_out, s);
 }
 
 pulsecol_status pulsecol_attn(pulsecol_ctx* ctx, const void* Q, const void* K, const void* V, const int32_t* idx,

@@ -66,15 +66,18 @@ constexpr int kScoreBlock_bf16 = 256;     // stationary rows per workgroup
 int score_splits(int64_t blocks, int32_t longest);
 
 struct TopkParams {
-    const float* scores;     // [rows, n], consecutive rows `stride` elements apart (a multiple of 4 where n is)
+    const float* scores;     // [rows, n], consecutive rows `stride` elements apart
     int32_t* idx;            // [rows, k]
+    int32_t* idx_copy;       // [rows, k], a second copy of the result, or nullptr
     int32_t rows, n, k;
     int64_t stride;
     // variable-length batches (else nullptr): rows = batch * rows_per_batch; row r belongs to batch
-    // element b = r / rows_per_batch and is group u = r % groups of its head; it selects varlen[batch + b]
-    // of its first varlen[b] scores and pads the rest of its k entries with -1; rows of groups that lie
-    // wholly beyond the element's length are padded altogether
+    // element b = r / rows_per_batch and is group u = r % groups of its head; it selects
+    // max(1, floor(keep_ratio * varlen[b])) of its first varlen[b] scores (keep_ratio = 0: min(k, varlen[b]))
+    // and pads the rest of its k entries with -1; rows of groups that lie wholly beyond the element's length
+    // are padded altogether
     const int32_t* varlen;
+    double keep_ratio;
     int32_t batch, rows_per_batch, groups, group_size;
 };
 
@@ -121,10 +124,6 @@ hipError_t launch_index_range_check(const int32_t* idx, int64_t count, int32_t n
 // lens[0..count) -> varlen[first .. first+count) for count <= 64 values carried in the launch itself
 struct VarlenChunk { int32_t v[64]; };
 hipError_t launch_varlen_store(int32_t* varlen, int32_t first, int32_t count, const VarlenChunk& values, hipStream_t s);
-// kept[b] = max(1, floor(keep_ratio * len_b)) (the keep-count rule on the element's own length)
-hipError_t launch_varlen_kept_from_ratio(int32_t* varlen, int32_t batch, double keep_ratio, hipStream_t s);
-// kept[b] = min(k, len_b)
-hipError_t launch_varlen_kept_from_k(int32_t* varlen, int32_t batch, int32_t k, hipStream_t s);
 // kept[b] = number of leading non-negative entries of the first column set of batch element b (at most
 // min(k, len_b)); per_batch = entries of idx per batch element
 hipError_t launch_varlen_kept_from_idx(int32_t* varlen, int32_t batch, const int32_t* idx, int64_t per_batch, int32_t k, hipStream_t s);

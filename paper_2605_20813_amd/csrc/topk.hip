@@ -7,10 +7,9 @@
 // therefore ascending in column index and, among equal scores, the lower index wins.  Integer
 // work only: results are exact and identical from run to run.
 //
-// Two kernels: topk_rows_kernel reads the row once and keeps it in registers (rows of up to
-// 65536 elements, a multiple of 4, 16-byte aligned: every shape of the paper's workloads; a
-// resident grid whose workgroups walk over the rows and fetch the next row while writing out);
-// topk_kernel streams the row from memory five times and takes everything else.
+// Two kernels: topk_rows_kernel reads the row once and keeps it in registers (rows of 4 to
+// 65536 elements; a resident grid whose workgroups walk over the rows and fetch the next row while
+// writing out); topk_kernel streams the row from memory five times and takes everything else.
 #include <type_traits>
 #include "pulsecol_device.h"
 #include "pulsecol_kernels.h"
@@ -37,15 +36,22 @@ __device__ __forceinline__ void row_geometry(const TopkParams& p, int row, int& 
         const int b = row / p.rows_per_batch;
         const int u = row % p.groups;                   // rows are ordered [batch, head, group]
         const int len = p.varlen[b];
-        const int kept = p.varlen[p.batch + b];
+        // the element's own kept count: the same rule, the same guard against the binary image of a decimal ratio, as
+        // the host's pulsecol_num_keep; or the caller's k
+        long long kept = p.k;
+        if (p.keep_ratio > 0.0) kept = (long long)__builtin_floor(p.keep_ratio * (double)len + 1e-9);
+        kept = kept < 1 ? 1 : (kept > len ? len : kept);
         const bool padding = p.groups > 1 && u * p.group_size >= len;
         n_row = padding ? 0 : len;
-        k_row = padding ? 0 : (kept < p.k ? kept : p.k);
+        k_row = padding ? 0 : ((int)kept < p.k ? (int)kept : p.k);
     }
 }
-// entries [from, k) of an output row are padding: -1
-__device__ __forceinline__ void pad_row(int32_t* __restrict__ out, int from, int k, int tid) {
-    for (int j = from + tid; j < k; j += TK_THREADS) out[j] = -1;
+// entries [from, k) of an output row (and of its copy, if there is one) are padding: -1
+__device__ __forceinline__ void pad_row(int32_t* __restrict__ out, int32_t* __restrict__ copy, int from, int k, int tid) {
+    for (int j = from + tid; j < k; j += TK_THREADS) {
+        out[j] = -1;
+        if (copy != nullptr) copy[j] = -1;
+    }
 }
 
 __global__ void __launch_bounds__(TK_THREADS) topk_kernel(TopkParams p) {
@@ -56,11 +62,12 @@ __global__ void __launch_bounds__(TK_THREADS) topk_kernel(TopkParams p) {
     const int row = blockIdx.x;
     const float* __restrict__ s = p.scores + (int64_t)row * p.stride;
     int32_t* __restrict__ out = p.idx + (int64_t)row * p.k;
+    int32_t* __restrict__ copy = p.idx_copy != nullptr ? p.idx_copy + (int64_t)row * p.k : nullptr;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     int n, k_row;
     row_geometry(p, row, n, k_row);
-    pad_row(out, k_row, p.k, tid);
+    pad_row(out, copy, k_row, p.k, tid);
     if (k_row == 0) return;                             // uniform: the whole workgroup
 
     // ---- radix select: after the loop `prefix` is the key of the k-th largest element and
@@ -127,7 +134,10 @@ __global__ void __launch_bounds__(TK_THREADS) topk_kernel(TopkParams p) {
         }
         if (sel) {
             const uint32_t pos = sel_before + sel_lane;
-            if (pos < (uint32_t)k_row) out[pos] = j;     // guard: holds by construction
+            if (pos < (uint32_t)k_row) {                 // guard: holds by construction
+                out[pos] = j;
+                if (copy != nullptr) copy[pos] = j;
+            }
         }
         eq_seen += eq_total;
         out_pos += sel_total;
@@ -138,7 +148,7 @@ __global__ void __launch_bounds__(TK_THREADS) topk_kernel(TopkParams p) {
 }
 
 
-// ---- rows that fit the registers of one workgroup (n <= 65536, n % 4 == 0, 16-byte aligned):
+// ---- rows that fit the registers of one workgroup (4 <= n <= 65536):
 // the row is read from memory ONCE, as order keys, 4 * V4 per thread; everything after that works
 // on registers.  Wave w owns the contiguous segment [w*SEG, (w+1)*SEG), SEG = 256 * V4; its load
 // instruction i covers 256 consecutive elements, lane l the four elements seg0 + i*256 + 4*l .. +3
@@ -201,8 +211,17 @@ constexpr int TKR_FEW = 32;                          // keys that one wave ranks
 constexpr uint32_t TKR_PROBE = 1u << 20;             // distance of the probe levels from the last row's threshold, in key units
 constexpr uint32_t TKR_HALF_WIDTH_MIN = 1u << 12, TKR_HALF_WIDTH_MAX = 1u << 22;
 
-template <int V4, bool VARLEN>
+// ODD: rows whose length or alignment is not a multiple of 16 bytes.  Their loads are 16 bytes at 4-byte alignment, the
+// one that would reach behind the row is pulled back to end with it and its elements moved up when the row's turn comes;
+// the registers that are left over hold the key 0, below every score's.  632 rows of 5003 elements: 87 us in the streaming
+// kernel, 28 here.
+// COPY: the result goes to a second place as well (select keeps the pattern; a copy of 32 sets of 409 columns took 2 us
+// in a launch of its own, of 632 sets of 500 5 us).
+enum TopkRows { kPlainRows, kOddRows, kVarlenRows };
+
+template <int V4, TopkRows MODE, bool COPY>
 __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int rows_per_wg) {
+    constexpr bool VARLEN = MODE == kVarlenRows, ODD = MODE != kPlainRows;
     constexpr int SEG = 256 * V4;
     static_assert(TKR_BPT * TK_THREADS == TKR_BINS && TKR_BPT % 4 == 0, "whole 16-byte groups of bins per thread");
     __shared__ __attribute__((aligned(16))) uint32_t hist[TKR_BINS];
@@ -219,9 +238,8 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int first = wave * SEG + lane * 4;          // this lane's first element
-    // load instructions of this lane that reach into a row of n_row elements (the row stride p.n is a
-    // multiple of 4, so a 16-byte load never leaves the row's storage; with a fixed length a lane's four
-    // elements are inside or outside together, with variable lengths the last group may straddle the end)
+    // load instructions of this lane that reach into a row of n_row elements (plain rows: a lane's four elements are
+    // inside or outside together; else the last group may straddle the end)
     auto groups_inside = [&](int n_row) {
         return first >= n_row ? 0 : ((n_row - first + 255) / 256 < V4 ? (n_row - first + 255) / 256 : V4);
     };
@@ -242,16 +260,23 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
     // order keys from then on
     uint32_t key[V4][4];
     const uint32_t* __restrict__ bits = (const uint32_t*)p.scores;
+    // register group i of the row that starts at `row_bits`, its first element being `e`
+    typedef u32x4 unaligned_u32x4 __attribute__((aligned(4)));
+    auto load_group = [&](const uint32_t* row_bits, int e) -> u32x4 {
+        if constexpr (ODD) return *(const unaligned_u32x4*)(row_bits + (e < p.n - 4 ? e : p.n - 4));
+        else return *(const u32x4*)(row_bits + e);
+    };
 #pragma unroll
     for (int i = 0; i < V4; ++i) {
         u32x4 v = {0u, 0u, 0u, 0u};                          // outside the row: never looked at, every use is guarded by nv
-        if (i < nv) v = *(const u32x4*)(bits + (int64_t)row_begin * p.stride + first + i * 256);
+        if (i < nv) v = load_group(bits + (int64_t)row_begin * p.stride, first + i * 256);
 #pragma unroll
         for (int c = 0; c < 4; ++c) key[i][c] = v[c];
     }
 
   for (int row = row_begin; row < row_end; ++row) {
     int32_t* __restrict__ out = p.idx + (int64_t)row * p.k;
+    int32_t* __restrict__ copy = COPY ? p.idx_copy + (int64_t)row * p.k : nullptr;
     // The thread's number, hidden from the compiler's loop-invariant hoisting once per row: it would compute
     // everything that follows from it (the 64 column numbers of the lane, LDS addresses, lane masks) in front of
     // the loop and, with no registers for them, keep them in scratch.
@@ -261,18 +286,18 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
     const int lane = tid & 63, wave = tid >> 6;
     const int first_r = wave * SEG + lane * 4;
     const bool more = row + 1 < row_end;
-    const uint32_t* __restrict__ next_bits = bits + (int64_t)(more ? row + 1 : row) * p.stride + first_r;
+    const uint32_t* __restrict__ next_bits = bits + (int64_t)(more ? row + 1 : row) * p.stride;
     // this row's geometry was settled when its load was issued; the next row's decides what is fetched for it
     int n_next = p.n, k_next = p.k;
     if constexpr (VARLEN) { if (more) row_geometry(p, row + 1, n_next, k_next); }
     const int nv_next = more ? (VARLEN ? groups_inside(n_next) : nv) : 0;
-    if constexpr (VARLEN) pad_row(out, k_row, p.k, tid);
+    if constexpr (VARLEN) pad_row(out, copy, k_row, p.k, tid);
     if (VARLEN && k_row == 0) {
         // a row of padding (uniform over the workgroup): nothing to select, only the next row's load
 #pragma unroll
         for (int i = 0; i < V4; ++i) {
             if (i < nv_next) {
-                const u32x4 v = *(const u32x4*)(next_bits + i * 256);
+                const u32x4 v = load_group(next_bits, first_r + i * 256);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) key[i][c] = v[c];
             }
@@ -280,12 +305,26 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
         n = n_next; k_row = k_next; nv = nv_next;
         continue;
     }
-    const bool straddles = VARLEN && (n & 3) != 0;    // uniform: variable-length rows only
+    const bool straddles = ODD && (n & 3) != 0;       // uniform
 
 #pragma unroll
     for (int i = 0; i < V4; ++i) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) key[i][c] = order_key_of_bits(key[i][c]);
+    }
+    if (ODD && (p.n & 3) != 0) {
+        // the load that was pulled back by 1, 2 or 3 elements (one lane of the workgroup): move its elements up
+#pragma unroll
+        for (int i = 0; i < V4; ++i) {
+            const int back = first_r + i * 256 - (p.n - 4);
+            if (back > 0 && back < 4) {
+                const uint32_t a = key[i][1], b = key[i][2], c = key[i][3];
+                key[i][0] = back == 1 ? a : back == 2 ? b : c;
+                key[i][1] = back == 1 ? b : back == 2 ? c : 0u;
+                key[i][2] = back == 1 ? c : 0u;
+                key[i][3] = 0u;
+            }
+        }
     }
     // bits of a ballot that belong to the lanes in front of this one, counted on top of `acc`
     auto count_before = [](uint64_t ballot, uint32_t acc) {
@@ -391,9 +430,11 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
         for (int i = 0; i < V4; ++i) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (i < nv && (!straddles || first_r + i * 256 + c < n)) {
+                if (i < nv && (!VARLEN || !straddles || first_r + i * 256 + c < n)) {
                     kmax = key[i][c] > kmax ? key[i][c] : kmax;
-                    kmin = key[i][c] < kmin ? key[i][c] : kmin;
+                    // (odd rows: the key 0 of a register without an element becomes the largest number)
+                    const uint32_t low = ODD && !VARLEN ? key[i][c] - 1u : key[i][c];
+                    kmin = low < kmin ? low : kmin;
                 }
             }
         }
@@ -407,14 +448,15 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
             kmin = wave_b[w] < kmin ? wave_b[w] : kmin;
         }
         __syncthreads();                                   // wave_a / wave_b are reused below
+        if (ODD && !VARLEN) kmin += 1u;
         if (straddles) {
-            // the elements a 16-byte load brought in from behind the row's end take the row's smallest key: they
-            // follow every real element in index order, so the selection (k_row <= n real elements) never reaches them
+            // what the row's last 16 bytes hold beside its elements takes the row's smallest key: it
+            // follows every real element in index order, so the selection (k_row <= n real elements) never reaches it
 #pragma unroll
             for (int i = 0; i < V4; ++i) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if (i < nv && first_r + i * 256 + c >= n) key[i][c] = kmin;
+                    if (VARLEN ? (i < nv && first_r + i * 256 + c >= n) : key[i][c] == 0u) key[i][c] = kmin;
             }
         }
         // Bits above `hi` are the same in every key of the row.
@@ -669,7 +711,10 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
         const bool fits = out_pos + sel_all <= (uint32_t)k_row;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            if (sel[c] & fits) out[pos] = first_r + i * 256 + c;
+            if (sel[c] & fits) {
+                out[pos] = first_r + i * 256 + c;
+                if constexpr (COPY) copy[pos] = first_r + i * 256 + c;
+            }
             pos += sel[c] ? 1u : 0u;
         }
         out_pos += sel_all;
@@ -682,7 +727,7 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
         }
         // the compaction is done with this register group: refill it with the next row's scores
         if (i < nv_next) {
-            const u32x4 v = *(const u32x4*)(next_bits + i * 256);
+            const u32x4 v = load_group(next_bits, first_r + i * 256);
 #pragma unroll
             for (int c = 0; c < 4; ++c) key[i][c] = v[c];
         }
@@ -692,21 +737,23 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
   }
 }
 
-template <int V4, bool VARLEN>
+template <int V4, TopkRows MODE>
 hipError_t launch_rows_as(const TopkParams& p, hipStream_t s) {
     // as many workgroups as the chip holds at a time (1024 threads at more than 64 registers: one
     // per CU); each walks over its run of consecutive rows
     const int resident = compute_units();
     const int rows_per_wg = (p.rows + resident - 1) / resident;
     const int grid = (p.rows + rows_per_wg - 1) / rows_per_wg;
-    hipLaunchKernelGGL((topk_rows_kernel<V4, VARLEN>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
+    if (p.idx_copy != nullptr) hipLaunchKernelGGL((topk_rows_kernel<V4, MODE, true>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
+    else hipLaunchKernelGGL((topk_rows_kernel<V4, MODE, false>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
     return hipGetLastError();
 }
 
 template <int V4>
 hipError_t launch_rows(const TopkParams& p, hipStream_t s) {
-    if (p.varlen != nullptr) return launch_rows_as<V4, true>(p, s);
-    return launch_rows_as<V4, false>(p, s);
+    if (p.varlen != nullptr) return launch_rows_as<V4, kVarlenRows>(p, s);
+    if (p.n % 4 == 0 && p.stride % 4 == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15u) == 0) return launch_rows_as<V4, kPlainRows>(p, s);
+    return launch_rows_as<V4, kOddRows>(p, s);
 }
 
 // Block masses, in place.  One workgroup per score row; a sweep of the workgroup covers 1024 consecutive scores with one
@@ -769,9 +816,9 @@ hipError_t launch_block_sums(const float* scores, float* out, int32_t rows, int3
 
 hipError_t launch_topk(const TopkParams& p, hipStream_t s) {
     if (p.rows < 1 || p.n < 1 || p.k < 1 || p.k > p.n) return hipErrorInvalidValue;
-    // rows that one workgroup can hold in registers, and that 16-byte loads can read
     if (p.stride < p.n) return hipErrorInvalidValue;
-    if (p.n <= 65536 && p.n % 4 == 0 && p.stride % 4 == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15u) == 0) {
+    // rows that one workgroup can hold in registers, and that hold a 16-byte load
+    if (p.n <= 65536 && p.n >= 4) {
         const int per_wave = (p.n + TK_WAVES - 1) / TK_WAVES;      // elements a wave has to hold
         if (per_wave <= 256) return launch_rows<1>(p, s);
         if (per_wave <= 512) return launch_rows<2>(p, s);
