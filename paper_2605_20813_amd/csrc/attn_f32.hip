@@ -5,7 +5,8 @@
 // Same transposed formulation as the bf16 kernels but on the fp32 matrix instruction
 // v_mfma_f32_32x32x2_f32 (two contraction indices per step, one per half-wave), so no
 // operand is rounded: Q, K, V, P and all accumulators are fp32.  One workgroup = 128 query
-// rows (4 waves x 32), one tile = 32 K/V rows staged in padded LDS.
+// rows (4 waves x 32), one tile = 32 K/V rows staged in padded LDS; for grids that would leave the
+// chip idle, a workgroup = 32 query rows whose tiles are shared out among its waves.
 #include "pulsecol_device.h"
 #include "pulsecol_kernels.h"
 
@@ -173,8 +174,193 @@ __global__ void __launch_bounds__(NTHREADS) attn_f32_kernel(AttnParams p) {
     }
 }
 
+// ---- Few query rows: a workgroup owns 32 of them, wave w of KS takes the tiles w, w + KS, ... and the waves' results are
+// merged through LDS at the end.  Nothing else is shared, so there is no LDS staging and no barrier on the way: K rows
+// come from memory as A fragments (half of the wave h holds the columns h*D/2 .. of a row, sixteen bytes at a time; the
+// contraction index is the same permutation on the Q side), V values as the coalesced dwords the second product takes.
+// K of the next tile is requested behind the last product that reads the running one and arrives during the softmax and
+// the second product, V during the first.
+// What bounds it: with three tiles per wave its start and end, memory latency both; the matrix pipe beyond.
+template <int D>
+__device__ __forceinline__ void load_half_row(const float* __restrict__ base, uint32_t row, uint32_t row_bytes, int lh, float (&f)[D / 2]) {
+    const char* src = (const char*)base + (row * row_bytes + (uint32_t)lh * (D / 2 * 4));        // 32-bit offset from the uniform base
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) {
+        const f32x4 v = *(const f32x4*)(src + i * 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[4 * i + e] = v[e];
+    }
+}
+
+template <int D, int MODE, int KS>
+__global__ void __launch_bounds__(64 * KS) attn_f32_split_kernel(AttnParams p) {
+    constexpr int HALF = D / 2;
+    constexpr int DB = D / 32;
+    constexpr bool HAS_V = (MODE != kLseOnly);
+    constexpr bool GATHER = (MODE == kSparse);
+    constexpr int CHUNKS = HAS_V ? DB * 4 : 0;                    // f32x4 per lane of a wave's output tile
+
+    __shared__ __attribute__((aligned(16))) f32x4 lds_o[HAS_V ? KS * CHUNKS * 64 : 1];
+    __shared__ float lds_m[KS][32], lds_l[KS][32];
+
+    int bh, qblk, b, h;
+    if (!head_and_block(blockIdx.z * kLayersPerZ + blockIdx.y, p.batch * p.heads, (p.n + 31) / 32, &bh, &qblk)) return;
+    split_head(bh, p.batch, p.heads, &b, &h);
+    int n = p.n, ns = p.ns;
+    if (p.varlen != nullptr) {
+        n = p.varlen[b];
+        const int kept = p.varlen[p.batch + b];
+        ns = GATHER ? (kept < ns ? kept : ns) : n;
+        if (qblk * 32 >= n) return;         // a block of padding rows
+    }
+    const int64_t head_off = (int64_t)b * p.td.sb + (int64_t)h * p.td.sh;
+    // grouped-query layout: query head h reads K/V head h / (heads / kv_heads)
+    const int64_t kv_off = (int64_t)b * p.td_kv.sb + (int64_t)kv_head_of(h, p.heads, p.kv_heads) * p.td_kv.sh;
+    const float* __restrict__ Q = (const float*)p.q + head_off;
+    const float* __restrict__ K = (const float*)p.k + kv_off;
+    const float* __restrict__ V = HAS_V ? (const float*)p.v + kv_off : nullptr;
+    const int group = p.groups > 1 ? (qblk * 32) / p.group_size : 0;
+    const int32_t* __restrict__ idx = GATHER ? p.idx + ((int64_t)bh * p.groups + group) * p.ns : nullptr;
+    const uint32_t kv_bytes = (uint32_t)p.td_kv.sn * 4u;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lq = lane & 31, lh = lane >> 5;
+    const int ntiles = (ns + BN - 1) / BN;
+    const int row_q = qblk * 32 + lq;
+    const float c2 = p.scale * kLog2e;
+
+    // row number of this lane's position lq of tile t (positions past the end: the last entry's)
+    auto tile_row = [&](int t) {
+        const int pos = t * BN + lq < ns ? t * BN + lq : ns - 1;
+        return GATHER ? idx[pos] : pos;
+    };
+    int row = 0;
+    float kf[HALF], qf[HALF];
+    if (wave < ntiles) {
+        row = tile_row(wave);
+        load_half_row<D>(K, (uint32_t)row, kv_bytes, lh, kf);
+    }
+    load_half_row<D>(Q, (uint32_t)(row_q < n ? row_q : n - 1), (uint32_t)p.td.sn * 4u, lh, qf);
+
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x16 o_acc[HAS_V ? DB : 1];
+#pragma unroll
+    for (int db = 0; db < (HAS_V ? DB : 1); ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
+
+    for (int t = wave; t < ntiles; t += KS) {
+        float vf[HAS_V ? 16 : 1][DB];
+        if constexpr (HAS_V) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t off = (uint32_t)__shfl(row, acc_row(r, lh)) * kv_bytes + (uint32_t)lq * 4u;
+#pragma unroll
+                for (int db = 0; db < DB; ++db) vf[r][db] = *(const float*)((const char*)V + off + db * 128);
+            }
+        }
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < HALF; ++kk) s = mfma_f32(kf[kk], qf[kk], s);
+        if (t + KS < ntiles) {
+            row = tile_row(t + KS);
+            load_half_row<D>(K, (uint32_t)row, kv_bytes, lh, kf);
+        }
+        if (t == ntiles - 1 && (ns & (BN - 1))) {
+            const int valid = ns - t * BN;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (acc_row(r, lh) >= valid) s[r] = -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+        mx = half_max(mx);
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = exp2f((m_run - m_new) * c2);
+        const float mc = m_new * c2;
+        m_run = m_new;
+        float rs = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            s[r] = exp2f(__builtin_fmaf(s[r], c2, -mc));
+            rs += s[r];
+        }
+        l_run = l_run * alpha + rs;
+        if constexpr (HAS_V) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o_acc[db][r] *= alpha;
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) o_acc[db] = mfma_f32(vf[r][db], s[r], o_acc[db]);
+        }
+    }
+
+    // ---- merge: reference and sum of every wave, then (attention) the output tiles, each scaled to the common reference.
+    // A wave without a tile has reference -inf, sum and output zero.
+    const float l_tot = half_sum(l_run);
+    if (lh == 0) { lds_m[wave][lq] = m_run; lds_l[wave][lq] = l_tot; }
+    __syncthreads();
+    float top = -INFINITY, l_all = 0.f;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) top = fmaxf(top, lds_m[w][lq]);
+#pragma unroll
+    for (int w = 0; w < KS; ++w) l_all += lds_l[w][lq] * exp2f((lds_m[w][lq] - top) * c2);
+    if (p.lse != nullptr && wave == 0 && lh == 0 && row_q < n)
+        p.lse[(int64_t)bh * p.n + row_q] = (top * c2 + log2f(l_all)) * (p.lse_base2 ? 1.0f : kLn2);
+    if constexpr (HAS_V) {
+        const float mine = exp2f((m_run - top) * c2);
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) {
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = o_acc[i / 4][(i % 4) * 4 + e] * mine;
+            lds_o[(wave * CHUNKS + i) * 64 + lane] = v;
+        }
+        __syncthreads();
+        static_assert(CHUNKS % KS == 0 || KS % CHUNKS == 0, "chunks are shared out evenly");
+        const float inv = 1.0f / l_all;
+        float* dst = (float*)p.o + head_off + (int64_t)row_q * p.td.sn;
+#pragma unroll
+        for (int j = 0; j < (CHUNKS + KS - 1) / KS; ++j) {
+            const int i = j * KS + wave;
+            if (i < CHUNKS && row_q < n) {
+                f32x4 v = lds_o[i * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < KS; ++w) v += lds_o[(w * CHUNKS + i) * 64 + lane];
+                *(f32x4*)(dst + (i / 4) * 32 + (i % 4) * 8 + 4 * lh) = v * inv;
+            }
+        }
+    }
+}
+
 template <int D, int MODE>
 hipError_t launch(const AttnParams& p, hipStream_t s) {
+    const int64_t heads = (int64_t)p.batch * p.heads;
+    // Where workgroups of 128 rows leave CUs idle: 32-row workgroups, with eight waves to share the tiles where every CU
+    // has room for all of them at once.  The line: with 128 columns of V one split workgroup fills a CU, and a round of
+    // them costs 0.36 (gathered) or 0.27 (dense) of a 128-row workgroup's time -- two or three rounds; the lighter ones
+    // win up to a 128-row workgroup per CU, the gathered one with 64 columns up to seven eighths of that.
+    // Before / after, keep 20%: 2 heads of 256, D = 64, dense 26.0 / 10.6 us; 8 of 1500, D = 128, sparse 57.5 / 41.6,
+    // dense 221 / 123; 3 of 8000, D = 64, sparse 246 / 97; beyond the line, 10 of 2048, D = 128, sparse: 73 / 77.
+    const int64_t blocks = (int64_t)((p.n + 31) / 32) * heads, wide_blocks = (int64_t)((p.n + BM - 1) / BM) * heads;
+    const int64_t cus = compute_units();
+    const bool split = MODE == kLseOnly ? wide_blocks < cus
+                     : D == 128         ? blocks <= (MODE == kSparse ? 2 : 3) * cus
+                                        : (MODE == kSparse ? 8 * wide_blocks <= 7 * cus : wide_blocks < cus);
+    if (split) {
+        constexpr int MANY = D == 128 && MODE != kLseOnly ? 4 : 8;          // (eight waves have no registers for 128 columns of V)
+        const dim3 grid = head_grid(heads, (p.n + 31) / 32);
+        if (blocks <= compute_units()) hipLaunchKernelGGL((attn_f32_split_kernel<D, MODE, MANY>), grid, dim3(64 * MANY), 0, s, p);
+        else hipLaunchKernelGGL((attn_f32_split_kernel<D, MODE, 4>), grid, dim3(256), 0, s, p);
+        return hipGetLastError();
+    }
     const int nqb = (p.n + BM - 1) / BM;
     const int bh_pad = (p.batch * p.heads + 7) / 8 * 8;
     hipLaunchKernelGGL((attn_f32_kernel<D, MODE>), dim3(nqb * bh_pad), dim3(NTHREADS), 0, s, p);
