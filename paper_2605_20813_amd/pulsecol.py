@@ -154,11 +154,12 @@ def last_error(handle=None) -> str:
 
 
 def _ptr(t):
-    return None if t is None else c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle alone: torch.cuda.current_stream() builds a Stream object for it, three times as long
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def select_noalloc(shape: Shape, Q, K, keep_ratio: float, idx_out):
@@ -178,6 +179,7 @@ class Context:
                                 max_keep_ratio)
         self.torch_dtype = torch.bfloat16 if self.shape.dtype == BF16 else torch.float32
         self.device = torch.device("cuda", device)
+        self._q_geometry, self._kv_geometry = self._geometries()
         self._h = c_void_p()
         st = lib().pulsecol_create(ctypes.byref(self._h), ctypes.byref(self.shape), device)
         if st != OK:
@@ -209,22 +211,29 @@ class Context:
         if st != OK:
             raise PulseColError(st, last_error(self._h))
 
-    def _check_tensor(self, t, name):
-        """Shape and strides of a tensor argument; K and V follow the K/V head count and strides."""
+    def _geometries(self):
+        """(shape, strides) that Q and O must have, and K and V: theirs follow the K/V head count and strides."""
         s = self.shape
-        if t.device != self.device or t.dtype != self.torch_dtype:
+
+        def geometry(heads, sb, sh, sn):
+            sn = sn or s.head_dim
+            sh = sh or s.seq * sn
+            return (s.batch, heads, s.seq, s.head_dim), (sb or heads * sh, sh, sn, 1)
+
+        q = geometry(s.heads, s.stride_b, s.stride_h, s.stride_n)
+        if s.kv_heads in (0, s.heads) and not (s.kv_stride_b or s.kv_stride_h or s.kv_stride_n):
+            return q, q
+        return q, geometry(s.kv_heads or s.heads, s.kv_stride_b, s.kv_stride_h, s.kv_stride_n)
+
+    def _check_tensor(self, t, name):
+        """Type, place, shape and strides of a tensor argument."""
+        if t.dtype != self.torch_dtype or t.device != self.device:
             raise ValueError(f"{name}: expected {self.torch_dtype} on {self.device}")
-        kv = name in ("K", "V")
-        kv_follows_q = s.kv_heads in (0, s.heads) and not (s.kv_stride_b or s.kv_stride_h or s.kv_stride_n)
-        if kv and not kv_follows_q:
-            heads, sb, sh, sn = s.kv_heads or s.heads, s.kv_stride_b, s.kv_stride_h, s.kv_stride_n
-        else:
-            heads, sb, sh, sn = s.heads, s.stride_b, s.stride_h, s.stride_n
-        if tuple(t.shape) != (s.batch, heads, s.seq, s.head_dim):
-            raise ValueError(f"{name}: expected shape {(s.batch, heads, s.seq, s.head_dim)}, got {tuple(t.shape)}")
-        want = (sb or heads * (sh or s.seq * (sn or s.head_dim)), sh or s.seq * (sn or s.head_dim), sn or s.head_dim, 1)
-        if tuple(t.stride()) != want:
-            raise ValueError(f"{name}: strides {tuple(t.stride())} do not match the context's {want}")
+        shape, strides = self._kv_geometry if name in ("K", "V") else self._q_geometry
+        if t.shape != shape:
+            raise ValueError(f"{name}: expected shape {shape}, got {tuple(t.shape)}")
+        if t.stride() != strides:
+            raise ValueError(f"{name}: strides {tuple(t.stride())} do not match the context's {strides}")
 
     def _new_output(self):
         """An O with the context's own strides (a padded row stride makes it larger than a packed tensor)."""
