@@ -664,16 +664,26 @@ bool splits_fit(const ScoreParams& p, int splits) {
 }  // namespace
 
 // Runs per head and block.  A CU holds two workgroups of either pass; one that is alone on its CU leaves the
-// matrix pipe idle while it forms weights, and a grid smaller than the chip leaves CUs idle altogether.  Below
-// 2 * CUs workgroups the streamed range is cut so that the grid comes as close to that as whole runs allow, in
-// runs of at least four tiles (a run's start, its stationary rows and first tiles from memory, costs about two).
-// Both passes together, D = 128, without and with the cut: 32 heads of 1000 rows 56.4 -> 32.4 us (with the row pass
-// of its own, see above), 4 heads of 8192 rows 264 -> 133 us, 8 heads of 5003 rows in groups of 64 184 -> 114 us.
-int score_splits(int64_t blocks, int32_t longest) {
-    const int64_t room = 2 * (int64_t)compute_units() / blocks;
-    const int64_t tiles = (longest + QT - 1) / QT;
-    const int64_t s = room < tiles / 4 ? room : tiles / 4;
-    return (int)(s < 1 ? 1 : (s > kMaxScoreSplits ? kMaxScoreSplits : s));
+// matrix pipe idle while it forms weights, a grid smaller than the chip leaves CUs idle altogether, and so does the
+// last round of one a little larger.  The rule counts rounds of 2 * CUs workgroups in units of a tile: a run costs its
+// tiles and 2.5 for its start (stationary rows and first tiles from memory), a last round that leaves one workgroup to a
+// CU two thirds of a full one, the launches that add the partial results up 1.5; runs have at least four tiles.
+// Both passes together, D = 128, uncut and cut: 32 heads of 1000 rows 56.4 -> 32.4 us (with the row pass
+// of its own, see above), 4 heads of 8192 rows 264 -> 133 us, 8 heads of 5003 rows in groups of 64 184 -> 114 us;
+// grids of more than half the chip and up to two rounds: 20 heads of 4096 rows 204 -> 167 us, 24 heads 211 -> 192, 18
+// heads of 8192 661 -> 554, 28 heads 889 -> 835, 10 heads of 15360 1235 -> 1069, 20 heads of 8192 at D = 64 462 -> 402 us.
+// Four elements of 3000, 1711, 902 and 130 rows, 8 heads, two runs -> three: selection and attention 105 -> 101 us.
+int score_splits(int64_t blocks, int32_t longest, int most) {
+    const double slots = 2.0 * compute_units(), tiles = (longest + QT - 1) / QT;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1; s <= most && s <= kMaxScoreSplits && (s == 1 || tiles >= 4.0 * s); ++s) {
+        const double rounds = (double)blocks * s / slots, whole = __builtin_floor(rounds), rest = rounds - whole;
+        const double last = rest == 0.0 ? 0.0 : (rest <= 0.5 ? 0.65 : 1.0);
+        const double cost = (whole + last) * (tiles / s + 2.5) + (s > 1 ? 1.5 : 0.0);
+        if (s == 1 || cost < 0.95 * best_cost) { best = s; best_cost = cost; }
+    }
+    return best;
 }
 
 hipError_t launch_rowlse_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {

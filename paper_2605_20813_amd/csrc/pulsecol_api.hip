@@ -145,18 +145,27 @@ void derive_from_shape(pulsecol_ctx* c, const pulsecol_shape* shape, int device)
 // none, and the row pass's may lie where the scores will.
 constexpr size_t kPartWords = (size_t)1 << 20;      // what a padded batch gets, whose lengths are not known yet
 
+// ... and the most that scores, partial results and row statistics may take together where a shape is cut: what the
+// static scratch of pulsecol_select_noalloc holds, so that it cuts every shape as a context does
+constexpr size_t kNoallocFloats = (size_t)4 << 20;                 // 16 MiB
+
+size_t row_words(const pulsecol_ctx* c) { return (size_t)c->shape.batch * c->shape.heads * (size_t)c->shape.seq; }
+
 int splits_of(const pulsecol_ctx* c, const int32_t* lens) {
     if (c->shape.dtype != PULSECOL_BF16) return 1;
-    int64_t blocks = 0;
     int32_t longest = 1;
+    int64_t work = 0;                                  // of blocks of stationary rows that stream n rows each
     for (int32_t b = 0; b < c->shape.batch; ++b) {
         const int32_t n = lens ? lens[b] : c->shape.seq;
-        blocks += (int64_t)((n + pulsecol::kScoreBlock_bf16 - 1) / pulsecol::kScoreBlock_bf16) * c->shape.heads;
+        work += (int64_t)((n + pulsecol::kScoreBlock_bf16 - 1) / pulsecol::kScoreBlock_bf16) * c->shape.heads * n;
         longest = n > longest ? n : longest;
     }
-    return pulsecol::score_splits(blocks, longest);
+    const int64_t blocks = (work + longest - 1) / longest;
+    // (one group: row statistics, scores and 2 words per run and row; else the partial results lie in the scores)
+    const size_t per_row = kNoallocFloats / row_words(c), taken = c->groups == 1 ? 2 : 1;
+    const size_t most = per_row > taken ? (per_row - taken) / 2 : 0;
+    return pulsecol::score_splits(blocks, longest, (int)std::min<size_t>(most, pulsecol::kMaxScoreSplits));
 }
-size_t row_words(const pulsecol_ctx* c) { return (size_t)c->shape.batch * c->shape.heads * (size_t)c->shape.seq; }
 
 // chooses the number of runs and returns the fp32 words that scores and partial results take
 size_t score_words(pulsecol_ctx* c, bool any_lengths) {
@@ -306,7 +315,6 @@ pulsecol_status select_from_scores(pulsecol_ctx* ctx, double keep_ratio, int32_t
 // A file-scope device array, one copy per GPU, held until the process ends: kNoallocFloats fp32
 // words (row log-sum-exp [B*H, n], then scores [B*H*U, n] and partial results).  The array's name is only a host-side stand-in for the symbol; the address of a
 // device's copy comes from hipGetSymbolAddress, asked once per device with that device current.
-constexpr size_t kNoallocFloats = (size_t)4 << 20;                 // 16 MiB
 static __device__ __align__(256) float scratch[kNoallocFloats];
 
 constexpr int kMaxDevices = 64;
@@ -523,8 +531,7 @@ pulsecol_status pulsecol_select_noalloc(const pulsecol_shape* shape, const void*
     derive_from_shape(&c, shape, dev);
     const size_t rows = (size_t)shape->batch * shape->heads;
     const size_t need = rows * (size_t)shape->seq * (1 + (size_t)c.groups);
-    // (a shape whose passes are split has at most 2^16 rows over all heads, and with kMaxScoreSplits runs of two
-    //  words each it stays far below the limit: what fits unsplit fits split)
+    // (what fits uncut fits cut: splits_of)
     if (need > kNoallocFloats || rows * (size_t)shape->seq + score_words(&c, false) > kNoallocFloats)
         return fail(nullptr, PULSECOL_ERR_UNSUPPORTED,
                     "pulsecol_select_noalloc: batch*heads*seq*(1 + groups) = " + std::to_string(need) +

@@ -61,9 +61,9 @@ struct ScoreParams {
 
 constexpr int kMaxScoreSplits = 8;
 constexpr int kScoreBlock_bf16 = 256;     // stationary rows per workgroup
-// runs per block that fill the chip in a scoring pass with this many blocks of stationary rows over all heads, the
-// longest head having `longest` rows (bf16)
-int score_splits(int64_t blocks, int32_t longest);
+// runs per block that fill the chip in a scoring pass with this many blocks of stationary rows over all heads that
+// stream `longest` rows each (blocks of shorter elements count by their share); at most `most` (bf16)
+int score_splits(int64_t blocks, int32_t longest, int most);
 
 struct TopkParams {
     const float* scores;     // [rows, n], consecutive rows `stride` elements apart

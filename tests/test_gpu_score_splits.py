@@ -46,6 +46,26 @@ def test_split_scores_match_oracle(H, n, d, G):
         assert (np.abs(got[h] - want) / want).max() < 2e-5
 
 
+@pytest.mark.parametrize("H,n,d", [(40, 2000, 64), (36, 4100, 128)])
+def test_runs_of_grids_larger_than_half_the_chip(H, n, d):
+    """Three runs per block where 320 blocks would fill part of the chip only, two where 612 blocks would leave most
+    of it idle in the last round.  First and last head against the oracle, every head's sum, and the entry point without
+    allocations, which cuts the shape alike, against the context."""
+    print(f"split scores H={H} n={n} d={d}", flush=True)
+    Q, K = rand_qk(1, H, n, d, torch.bfloat16, seed=H)
+    Qd, Kd = Q.to(DEV), K.to(DEV)
+    with pc.Context(1, H, n, d, torch.bfloat16) as ctx:
+        got = f64(ctx.scores(Qd, Kd))[0, :, 0]
+        kept = ctx.select(Qd, Kd, 0.1)
+    same = torch.empty_like(kept)
+    pc.select_noalloc(pc.make_shape(1, H, n, d, torch.bfloat16), Qd, Kd, 0.1, same)
+    assert torch.equal(same, kept)
+    assert np.abs(got.sum(axis=-1) - 1.0).max() < 1e-5
+    for h in (0, H - 1):
+        want = oracle.column_scores(f64(Q[0, h]), f64(K[0, h]))[0]
+        assert (np.abs(got[h] - want) / want).max() < 2e-5
+
+
 def test_runs_past_the_end_of_a_short_batch_element():
     n, lens, d = 2049, (2049, 70, 1), 128
     print(f"split scores n={n} lens={lens}", flush=True)
