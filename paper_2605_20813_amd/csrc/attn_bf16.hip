@@ -1,7 +1,7 @@
 // bf16 attention kernels for gfx950: column-sparse attention (Sec. 3.4 and the appendix
-// listing "Column-Sparse Attention Forward"), the dense baseline (Sec. 3.1) and the row
-// log-sum-exp pass of the identification step (Sec. 3.3: the softmax matrix P needs the
-// row normalisers before column masses can be summed).
+// listing "Column-Sparse Attention Forward"), the dense baseline (Sec. 3.1; on request with
+// the row log-sum-exp that the column pass of a fused refresh step reads) and the block-sparse
+// mode.
 //
 // One workgroup = 256 query rows (4 waves x 64 rows), one tile = 64 K/V rows, processed as
 // two half-tiles of 32.  Q stays in registers (AGPRs) as the MFMA B operand for the whole
