@@ -19,7 +19,10 @@
 // 128: 0.47 us per tile and CU = 1.18 PFLOP/s, against 1.29 of the main kernel; with all-zero operands 1.49), and the
 // start and end of a block, some 3 us each at keep 10%.  Against the three-step form, inputs from memory: that shape
 // 139 -> 136 us, its groups of 64 170 -> 165, of 32 271 -> 232; one set per head, 32 heads of 4096: 42.1 -> 39.7,
-// 4 heads of 8192 37.5 -> 21.4.  A fourth slot per operand is slower where every group gathers its own rows (145 us:
+// 4 heads of 8192 37.5 -> 21.4; 64K rows: groups of 128 6.69 -> 6.56 ms, 2 heads in groups of 64 1.94 -> 0.54, 32 heads in
+// groups of 32 at 32K 3.55 -> 3.08.  Groups of 64 with D = 128 over long contexts lose a little: three slots per operand leave
+// a CU three workgroups of two waves where two slots left five, 32 heads of 32K 2.15 -> 2.17 ms, of 64K 8.50 -> 8.62 (16K and
+// D = 64: 0.573 -> 0.573, 0.295 -> 0.287).  A fourth slot per operand is slower where every group gathers its own rows (145 us:
 // more requests in flight, fewer of them served by the L2), and no faster elsewhere.
 //
 // Start and end of a query block: a workgroup works through a list of blocks, and requests what the next block needs
