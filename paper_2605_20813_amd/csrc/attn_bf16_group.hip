@@ -269,7 +269,8 @@ attn_bf16_group_kernel(AttnParams p) {
     // workgroups to a CU.  (Smaller ones come three to a CU and cover each other, and have no registers for it.)
     constexpr bool LIST = KS == 1 && NW == 4;
 
-    __shared__ __attribute__((aligned(1024))) byte lds_all[KS * TEAM_BYTES];
+    // (two teams: the reference of every query of the block behind the tile slots)
+    __shared__ __attribute__((aligned(1024))) byte lds_all[KS * TEAM_BYTES + (KS > 1 ? BM * 4 : 0)];
 
     // every kernel argument with the first batch of scalar loads: left to itself the compiler loads them where they
     // are first used, one memory round trip after another
@@ -556,9 +557,17 @@ attn_bf16_group_kernel(AttnParams p) {
         float mx = sa[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sa[r]);
-        // (the bound keeps the reference of a team without a single entry finite: its weights are then zero)
         w.ref = fmaxf(half_max(mx) * w.c2, -1e30f);
     }
+    // Two teams: both weigh against the reference that team 0 takes from the block's first tile, handed over behind the
+    // next barrier.  A weight then has the same bits whichever team forms it, in this form of the kernel or in the one
+    // with a single team, as a raise moves the reference by whole log2 units: the forms differ in the order of fp32 sums alone.
+    // (Each team with a reference of its own rounded half of the weights to other 16-bit values.)
+    const uint32_t ref_at = lds_address(lds_all) + (uint32_t)(KS * TEAM_BYTES + (wave * 32 + lq) * 4);
+    if (KS > 1 && team == 0) asm volatile("ds_write_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : : "v"(ref_at), "v"(w.ref) : "memory");
+    auto common_reference = [&] {
+        if constexpr (KS > 1) asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(w.ref) : "v"(ref_at) : "memory");
+    };
 
     // Iteration t, U = t % NBUF: S(t) in s -> P(t) in P, S(t+1) in s_next, P(t-1) in P_prev.  K(t+1) and V(t-1) have
     // landed in every wave once this wave's loads of the iteration before are the only ones it still may have in
@@ -574,6 +583,7 @@ attn_bf16_group_kernel(AttnParams p) {
         memory_order_point();
         __builtin_amdgcn_s_barrier();
         memory_order_point();
+        if constexpr (!PV) common_reference();              // the first tile's weights come next
         typename W::Fragment fr[KK + W::NPV];
         w.template request_first<QK, PV, KOFF, VOFF>(fr);
         memory_order_point();
@@ -628,6 +638,7 @@ attn_bf16_group_kernel(AttnParams p) {
     } else {
         __builtin_amdgcn_s_barrier();                       // every wave has read K(0)
         memory_order_point();
+        common_reference();
         begin_next(1);
 #pragma unroll
         for (int r = 0; r < 16; ++r) w.weight(r, sa, pa, sm);

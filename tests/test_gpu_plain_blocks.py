@@ -55,3 +55,25 @@ def test_several_blocks_per_workgroup_in_a_ragged_batch():
 def test_two_teams_per_block(H, n, d, k):
     print(f"two teams H={H} n={n} d={d} k={k}", flush=True)
     run(1, H, n, d, k)
+
+
+@pytest.mark.parametrize("H,n,d,k,copies", [(2, 1000, 128, 200, 20), (3, 500, 128, 161, 30), (2, 333, 64, 129, 50)])
+def test_two_teams_form_the_weights_that_one_team_forms(H, n, d, k, copies):
+    """The same heads alone (two teams per block) and many times over in one launch (one team).  The weights and their
+    16-bit roundings are the same in both, the fp32 sums run in another order: relative differences of some 1e-6 move a
+    rounding boundary of the output under about 1e-6 / 2^-8 of the values, by 2^-8 of the value, 6e-5 of the norm.  (Weights
+    rounded against two references differ by some 2e-3.)"""
+    print(f"two teams against one H={H} n={n} d={d} k={k}", flush=True)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(n + k)
+    Q, K, V = (torch.randn(1, H, n, d, generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+    idx = random_idx(n, k, H, seed=n).view(1, H, 1, k).to(DEV)
+    outs = []
+    for r in (1, copies):
+        with pc.Context(1, H * r, n, d, torch.bfloat16) as ctx:
+            ctx.set_attn_block(128)
+            assert (H * r * -(-n // 128) <= 256) == (r == 1)
+            O = ctx.attn(*(t.repeat(1, r, 1, 1).contiguous() for t in (Q, K, V)), idx.repeat(1, r, 1, 1).contiguous())
+            torch.cuda.synchronize()
+        outs.append(f64(O[0, :H]))
+    assert np.linalg.norm(outs[0] - outs[1]) <= 5e-4 * np.linalg.norm(outs[1])
