@@ -27,7 +27,8 @@ struct pulsecol_ctx {
     float* scores = nullptr;        // [B*H*U, n]
     float* part = nullptr;          // partial results of split scoring passes; U > 1: in the scores' words
     int part_splits = 1;            // runs that `part` has room for (1: it has none)
-    int score_splits = 1;           // runs into which the scoring passes cut a head (bf16), at most part_splits
+    int fixed_splits = 1;           // runs into which the scoring passes cut a head (bf16) of `seq` rows in every element
+    int score_splits = 1;           // ... and with the present lengths, at most part_splits
     int32_t* cached_idx = nullptr;  // [B*H*U, cached_k]
     int32_t cached_k = 0;           // 0 = nothing cached
     int32_t k_max = 0;              // columns per group the cache has room for
@@ -169,7 +170,7 @@ int splits_of(const pulsecol_ctx* c, const int32_t* lens) {
 
 // chooses the number of runs and returns the fp32 words that scores and partial results take
 size_t score_words(pulsecol_ctx* c, bool any_lengths) {
-    c->score_splits = c->part_splits = splits_of(c, nullptr);
+    c->fixed_splits = c->score_splits = c->part_splits = splits_of(c, nullptr);
     if (any_lengths && c->shape.batch > 1 && c->shape.dtype == PULSECOL_BF16) {
         const size_t room = std::min<size_t>(kPartWords / (2 * row_words(c)), pulsecol::kMaxScoreSplits);
         c->part_splits = std::max(c->part_splits, (int)room);
@@ -424,7 +425,7 @@ pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens
     if (!ctx) return fail(nullptr, PULSECOL_ERR_INVALID_ARG, "pulsecol_set_seq_lens: ctx is NULL");
     if (!seq_lens) {
         ctx->varlen_on = false;
-        ctx->score_splits = splits_of(ctx, nullptr);
+        ctx->score_splits = ctx->fixed_splits;       // what the scratch was sized for
         return PULSECOL_OK;
     }
     const int32_t B = ctx->shape.batch;

@@ -1,0 +1,70 @@
+// Stand-ins of the HIP runtime and of the kernel launchers behind csrc/pulsecol_api.hip: two devices with different
+// numbers of compute units.  The launchers compare what a pass would touch with the allocations it was given.
+#include <cstdlib>
+#include <cstring>
+#include <map>
+
+#include "pulsecol_kernels.h"
+
+namespace {
+int current = 0;
+const int kUnits[2] = {64, 256};
+std::map<char*, size_t> blocks;
+int row_splits = 0, outside = 0, allocations = 0;
+
+// counts accesses [p, p + bytes) that no allocation holds
+void touch(const void* p, size_t bytes) {
+    char* c = (char*)p;
+    auto it = blocks.upper_bound(c);
+    if (it == blocks.begin()) { ++outside; return; }
+    --it;
+    if (c + bytes > it->first + it->second) ++outside;
+}
+}  // namespace
+
+hipError_t hipMalloc(void** p, size_t bytes) { *p = std::malloc(bytes); blocks[(char*)*p] = bytes; ++allocations; return hipSuccess; }
+hipError_t hipFree(void* p) { blocks.erase((char*)p); std::free(p); return hipSuccess; }
+hipError_t hipMemset(void* p, int value, size_t bytes) { std::memset(p, value, bytes); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind, hipStream_t) { std::memcpy(to, from, bytes); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = current; return hipSuccess; }
+hipError_t hipSetDevice(int d) { current = d; return hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) { *n = 2; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = (void*)symbol; return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+
+extern "C" {
+int fake_row_splits() { return row_splits; }
+int fake_outside() { return outside; }
+int fake_device() { return current; }
+void fake_set_device(int d) { current = d; }
+}
+
+namespace pulsecol {
+int compute_units() { return kUnits[current]; }
+// more runs where there are more compute units
+int score_splits(int64_t, int32_t, int most) { const int s = compute_units() / 32; return s < most ? s : most; }
+
+hipError_t launch_rowlse_bf16(const ScoreParams& p, int, hipStream_t) {
+    const size_t rows = (size_t)p.batch * p.heads * p.n;
+    row_splits = p.row_splits;
+    touch(p.lse, rows * 4);
+    if (p.row_splits > 1) touch(p.part, 2 * (size_t)p.row_splits * rows * 4);
+    return hipSuccess;
+}
+hipError_t launch_colmass_bf16(const ScoreParams& p, int, hipStream_t) {
+    const size_t rows = (size_t)p.batch * p.heads * p.n;
+    if (p.col_splits > 1 && p.groups == 1) touch(p.part, (size_t)p.col_splits * rows * 4);
+    return hipSuccess;
+}
+hipError_t launch_colmass_f32(const ScoreParams&, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_bf16(const AttnParams&, int, AttnMode, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_bf16_group(const AttnParams&, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_attn_f32(const AttnParams&, int, AttnMode, hipStream_t) { return hipSuccess; }
+hipError_t launch_topk(const TopkParams&, hipStream_t) { return hipSuccess; }
+hipError_t launch_block_sums(const float*, float*, int32_t, int32_t, int64_t, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_index_range_check(const int32_t*, int64_t, int32_t, int32_t*, const int32_t*, int32_t, int64_t, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_varlen_store(int32_t*, int32_t, int32_t, const VarlenChunk&, hipStream_t) { return hipSuccess; }
+hipError_t launch_varlen_kept_from_idx(int32_t*, int32_t, const int32_t*, int64_t, int32_t, hipStream_t) { return hipSuccess; }
+}  // namespace pulsecol

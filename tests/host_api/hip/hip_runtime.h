@@ -1,0 +1,30 @@
+// Host stand-in for the HIP runtime, as far as the C-ABI layer (csrc/pulsecol_api.hip) uses it: "devices" are ordinary
+// memory, the stand-ins of the kernel launchers (fake_kernels.cpp) only look at what they are given.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#define __device__
+#define __align__(n) __attribute__((aligned(n)))
+#define HIP_SYMBOL(x) ((const void*)&(x))
+
+struct dim3 {
+    unsigned x, y, z;
+    dim3(unsigned x_ = 1, unsigned y_ = 1, unsigned z_ = 1) : x(x_), y(y_), z(z_) {}
+};
+typedef void* hipStream_t;
+enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorInvalidSymbol = 13 };
+enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3 };
+
+hipError_t hipMalloc(void** p, size_t bytes);
+hipError_t hipFree(void* p);
+hipError_t hipMemset(void* p, int value, size_t bytes);
+hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind kind, hipStream_t s);
+hipError_t hipStreamSynchronize(hipStream_t s);
+hipError_t hipGetDevice(int* d);
+hipError_t hipSetDevice(int d);
+hipError_t hipGetDeviceCount(int* n);
+hipError_t hipGetLastError();
+hipError_t hipGetSymbolAddress(void** p, const void* symbol);
+const char* hipGetErrorString(hipError_t e);

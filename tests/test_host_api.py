@@ -1,0 +1,64 @@
+"""The C-ABI layer on stand-ins of the HIP runtime and of the kernels (host_api/): what it hands to the passes, on two
+devices with different numbers of compute units.  No GPU."""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+import torch
+
+from paper_2605_20813_amd import pulsecol as pc
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(HERE, "..", "paper_2605_20813_amd", "csrc")
+FEW, MANY = 0, 1                   # devices of 64 and 256 compute units
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def api(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("host_api") / "libhost_api.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(HERE, "host_api"), "-I", CSRC, "-x", "c++",
+                    os.path.join(CSRC, "pulsecol_api.hip"), os.path.join(HERE, "host_api", "fake_kernels.cpp"), "-o", out],
+                   check=True)
+    return ctypes.CDLL(out)
+
+
+class Ctx:
+    def __init__(self, api, device, *shape, **kw):
+        self.api, self.h, self.shape = api, ctypes.c_void_p(), pc.make_shape(*shape, **kw)
+        assert api.pulsecol_create(ctypes.byref(self.h), ctypes.byref(self.shape), device) == pc.OK
+
+    def set_seq_lens(self, lens):
+        return self.api.pulsecol_set_seq_lens(self.h, (ctypes.c_int32 * len(lens))(*lens) if lens else None, None)
+
+    def scores(self):
+        """Runs the scoring passes; the accesses outside of the context's allocations."""
+        before = self.api.fake_outside()
+        fake = ctypes.c_void_p(1 << 20)
+        assert self.api.pulsecol_scores(self.h, fake, fake, fake, None) == pc.OK
+        return self.api.fake_outside() - before
+
+    def close(self):
+        self.api.pulsecol_destroy(self.h)
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+def test_fixed_lengths_restored_while_another_device_is_current(api, batch):
+    """The runs of the scoring passes that come back with set_seq_lens(NULL) are those that the scratch was sized for."""
+    api.fake_set_device(FEW)
+    ctx = Ctx(api, FEW, batch, 4, 4096, 128, torch.bfloat16)
+    assert ctx.scores() == 0
+    splits = api.fake_row_splits()
+    assert ctx.set_seq_lens([4096] * batch) == pc.OK
+    api.fake_set_device(MANY)
+    assert ctx.set_seq_lens(None) == pc.OK
+    assert ctx.scores() == 0
+    assert api.fake_row_splits() == splits
+    assert ctx.set_seq_lens([2000] * batch) == pc.OK
+    assert ctx.scores() == 0
+    assert api.fake_device() == MANY
+    ctx.close()
