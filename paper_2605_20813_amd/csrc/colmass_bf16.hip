@@ -13,10 +13,12 @@
 // in-lane sum (four interleaved partial sums, each a short and a long accumulator) and the two
 // half-waves meet once at the end (column pass: once per group).
 //   column pass: exp2(z*c - lse_i) takes lse_i per register row, read from LDS four at a time.
-//   row pass: exp2(z*c - ref) against one reference per lane, the maximum of the first 32 keys.  The
-//     sum is fp32 and keeps its relative precision however far later logits rise above the reference;
-//     only an overflow (some 2^127) has to be caught: a wave that ends with a sum that is not finite
-//     does its rows over with a running maximum.
+//   row pass: exp2(z*c - ref) against one reference per lane, a whole number, at first 3 log2 units above
+//     the maximum of the first 32 keys (ordinary rows rise 5 to 10 units above it, and a raise costs the
+//     wave a block's weights anew).  z*c - ref is rounded at its own size, so a reference far below the
+//     weights that dominate a row costs their precision: where the weights of a block of 32 keys outgrow
+//     2^8 in some lane, the reference goes up with the block's maximum, the sums so far are scaled by that
+//     exact power of two and the block's weights formed anew from its scores, which are still there.
 // P never leaves fp32 and there are no floating-point atomics: the result is bit-identical
 // from run to run.
 //
@@ -27,7 +29,8 @@
 //
 // What bounds it: two weights and a matrix instruction per 32 cycles of the matrix pipe, about as much as one wave
 // can issue, and over long runs the power limit (about 1.2 PFLOP/s).  The row pass used to be a mode of the 256-row
-// attention kernel, 62 KB of straight-line code that every launch fetches anew; this one is 16 KB.  D = 128, 32 heads:
+// attention kernel, 62 KB of straight-line code that every launch fetches anew; this one is 22 KB,
+// 7 of them the raises, out of the way.  (Checking every block for one costs 0.3% at 64K, 0.8% at 4K.)  D = 128, 32 heads:
 // 4096 rows 172 -> 128 us, 16384 rows 1877 -> 1842 us, 65536 rows 28.8 -> 28.9 ms.
 #include <utility>
 
@@ -43,6 +46,9 @@ constexpr int NTHREADS = 256;
 constexpr int ROWS_PER_WG = kScoreBlock_bf16;    // stationary rows per workgroup
 constexpr int QT = 64;              // rows per streamed tile
 constexpr int FLUSH = 16;           // tiles between flushes of the short accumulator into the long one
+constexpr float kGrowthLimit = 256.0f;      // row pass: sum of a lane's 16 weights of a block that raises the reference
+constexpr float kHeadroom = 3.0f;           // row pass: log2 units between a maximum and the reference taken from it
+constexpr float kNoReference = -1e30f;      // row pass: the reference of a row without a finite logit so far
 
 // s_waitcnt vmcnt(v) with the other counters left alone (gfx9 encoding: vmcnt in [3:0] and [15:14])
 template <int v>
@@ -172,8 +178,10 @@ struct ScoreWave {
     bf16x8 yf[2][KK];         // stationary fragments: B operand, [row lq of block kb][d = kk*16 + 8*lh .. +7]
     f32x16 sb[2][2];          // scores [streamed block qb][stationary block kb]
     f32x4 lr[4];              // column pass: log-sum-exp (log2 units) of four query rows each, of the block whose weights are being formed
-    float ref[2];             // row pass: the reference (log2 units) of this lane's query rows
-    float acc_short[2][4], acc_long[2][4];
+    float ref[2];             // row pass: the reference (log2 units, whole) of this lane's query rows
+    float blk[2][4];          // row pass: the sums of the block whose weights are being formed
+    static constexpr int NACC = ROWS ? 1 : 4;       // (row pass: whole blocks are added up)
+    float acc_short[2][NACC], acc_long[2][NACC];
     uint32_t xv[KK];          // LDS address of this lane's fragment kk in slot 0, first block
     uint32_t lv;              // column pass: LDS address of this lane's first log-sum-exp group in ring entry 0
     float c2;
@@ -181,17 +189,55 @@ struct ScoreWave {
     // weight e (0..31) of streamed block cq: register e / 2, stationary block e % 2
     __device__ __forceinline__ void weight(int cq, int e) {
         const int r = e >> 1, kb = e & 1;
-        acc_short[kb][r & 3] += fast_exp2(__builtin_fmaf(sb[cq][kb][r], c2, ROWS ? -ref[kb] : -lr[r >> 2][r & 3]));
+        add_weight(kb, r, fast_exp2(__builtin_fmaf(sb[cq][kb][r], c2, ROWS ? -ref[kb] : -lr[r >> 2][r & 3])));
     }
-    // row pass: the reference from the scores of one streamed block (both half-waves get the same value)
+    __device__ __forceinline__ void add_weight(int kb, int r, float e) {
+        if constexpr (ROWS) {
+            blk[kb][r & 3] = r < 4 ? e : blk[kb][r & 3] + e;
+            // (chains are added up as they end, so that one addition is left for the end of the block)
+            if (r == 13) blk[kb][0] += blk[kb][1];
+            if (r == 15) blk[kb][2] += blk[kb][3];
+        } else {
+            acc_short[kb][r & 3] += e;
+        }
+    }
+    __device__ __forceinline__ float block_sum(int kb) const { return blk[kb][0] + blk[kb][2]; }
+    // row pass: a reference from 32 keys, the next whole number above their maximum and kHeadroom more (both half-waves get
+    // the same one)
+    __device__ __forceinline__ float reference_of(const f32x16& s) const {
+        float mx = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+        // (the bound: a block of keys without a finite logit leaves the reference finite and adds nothing)
+        return fmaxf(ceilf(half_max(mx) * c2) + kHeadroom, kNoReference);
+    }
     __device__ __forceinline__ void set_reference(const f32x16 (&s)[2]) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            float mx = s[kb][0];
+        for (int kb = 0; kb < 2; ++kb) ref[kb] = reference_of(s[kb]);
+    }
+    // row pass: accept the sums of a block, or raise the reference first.  The scores `s` are the block's.
+    __device__ __forceinline__ void close_block(const f32x16 (&s)[2]) {
+        float sum[2];
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-            ref[kb] = half_max(mx) * c2;
+        for (int kb = 0; kb < 2; ++kb) sum[kb] = block_sum(kb);
+        if (__builtin_expect(__ballot(!(sum[0] <= kGrowthLimit) | !(sum[1] <= kGrowthLimit)) != 0ull, 0)) {
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const float top = reference_of(s[kb]);
+                if (top > ref[kb]) {
+                    // (a row without a finite logit so far has nothing to scale)
+                    const float down = ref[kb] == kNoReference ? 0.f : fast_exp2(ref[kb] - top);
+                    acc_short[kb][0] *= down;
+                    acc_long[kb][0] *= down;
+                    ref[kb] = top;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) add_weight(kb, r, fast_exp2(__builtin_fmaf(s[kb][r], c2, -top)));
+                    sum[kb] = block_sum(kb);
+                }
+            }
         }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) acc_short[kb][0] += sum[kb];
     }
     template <int OFF>
     __device__ __forceinline__ void read_lse(int g, uint32_t ring_addr) {
@@ -409,9 +455,11 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) { w.acc_short[kb][c] = 0.f; w.acc_long[kb][c] = 0.f; }
+        for (int c = 0; c < W::NACC; ++c) { w.acc_short[kb][c] = 0.f; w.acc_long[kb][c] = 0.f; }
     // this lane's sum of stationary block kb over both half-waves (they hold the same stationary rows, other streamed rows)
     auto total = [&](int kb) {
+        if constexpr (ROWS) return half_sum(w.acc_long[kb][0] + w.acc_short[kb][0]);
+        else
         return half_sum(((w.acc_long[kb][0] + w.acc_short[kb][0]) + (w.acc_long[kb][1] + w.acc_short[kb][1])) +
                         ((w.acc_long[kb][2] + w.acc_short[kb][2]) + (w.acc_long[kb][3] + w.acc_short[kb][3])));
     };
@@ -424,11 +472,12 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
     // in the column pass at the last rows of a query group (groups are multiples of 32 rows), the group's score
     // row: add the two half-waves, divide by the group's size, store, start over.
     auto block_done = [&](int t, int qb) {
+        if constexpr (ROWS) w.close_block(w.sb[qb]);
         if (qb == 1 && (t % FLUSH) == FLUSH - 1) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) { w.acc_long[kb][c] += w.acc_short[kb][c]; w.acc_short[kb][c] = 0.f; }
+                for (int c = 0; c < W::NACC; ++c) { w.acc_long[kb][c] += w.acc_short[kb][c]; w.acc_short[kb][c] = 0.f; }
         }
         if constexpr (!ROWS) {
             const int rows_done = (t0 + t) * QT + (qb + 1) * 32;
@@ -533,7 +582,7 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     if (qb * 32 + acc_row(r, lh) >= valid) { s[0][r] = -INFINITY; s[1][r] = -INFINITY; }
-                if (nfull == 0 && qb == 0) w.set_reference(s);         // finite: the block's first row is valid
+                if (nfull == 0 && qb == 0) w.set_reference(s);
             } else {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) l2[g] = *(const f32x4*)(lslot + qb * 32 + 8 * g + 4 * lh);
@@ -543,48 +592,16 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
                     const float e = fast_exp2(__builtin_fmaf(s[kb][r], w.c2, ROWS ? -w.ref[kb] : -l2[r >> 2][r & 3]));
-                    w.acc_short[kb][r & 3] += (ROWS || qb * 32 + acc_row(r, lh) < valid) ? e : 0.f;
+                    w.add_weight(kb, r, (ROWS || qb * 32 + acc_row(r, lh) < valid) ? e : 0.f);
                 }
             }
+            if constexpr (ROWS) { w.sb[qb][0] = s[0]; w.sb[qb][1] = s[1]; }
             block_done(t, qb);
         }
     }
 
     if constexpr (ROWS) {
         float sum[2] = {total(0), total(1)};
-        if (__builtin_expect(__ballot(!(sum[0] < INFINITY && sum[1] < INFINITY)) != 0ull, 0)) {
-            // Some row of this wave has logits so far above its first 32 that the sum overflowed: the wave's
-            // rows once more, 32 keys at a time straight from memory, with a running maximum.
-            float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
-            for (int x = t0 * QT; x < x_end; x += 32) {
-                const int row = x + lq < x_end ? x + lq : x_end - 1;
-                const byte* src = X + __umul24((uint32_t)row, row_bytes) + 16 * lh;
-                f32x16 s[2];
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-#pragma unroll
-                for (int kk = 0; kk < KK; ++kk) {
-                    const bf16x8 xfrag = *(const bf16x8*)(src + kk * 32);
-                    s[0] = mfma_bf16(xfrag, w.yf[0][kk], s[0]);
-                    s[1] = mfma_bf16(xfrag, w.yf[1][kk], s[1]);
-                }
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) if (x + acc_row(r, lh) >= x_end) s[kb][r] = -INFINITY;
-                    w.set_reference(s);                                 // of these 32 keys alone
-                    const float up = fmaxf(m[kb], w.ref[kb]);
-                    l[kb] *= fast_exp2(m[kb] - up);
-                    m[kb] = up;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) l[kb] += fast_exp2(__builtin_fmaf(s[kb][r], w.c2, -up));
-                }
-            }
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) { w.ref[kb] = m[kb]; sum[kb] = half_sum(l[kb]); }
-        }
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
             const int row = y0 + kb * 32 + lq;

@@ -1,0 +1,63 @@
+"""The reference of the row pass (bf16): rows whose dominating logits come late and far above the first keys, and blocks of
+keys whose logits are all -inf, at the start of a head and where a pass is cut into runs.  One component of Q and K carries
+the logits, so that every dot product is exact and what is measured is the softmax alone."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_20813_amd import pulsecol as pc
+from parity_util import f64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def scores_of(k0, n, d, heads=1):
+    """Column scores [heads, n] on the GPU and in fp64 for identical rows whose logit against key j is k0[h, j] / sqrt(d)."""
+    Q, K = torch.zeros(1, heads, n, d), torch.zeros(1, heads, n, d)
+    Q[..., 0] = 1.0
+    K[0, :, :, 0] = torch.as_tensor(np.asarray(k0), dtype=torch.float32)
+    K = K.to(torch.bfloat16)
+    with pc.Context(1, heads, n, d, torch.bfloat16) as ctx:
+        got = f64(ctx.scores(Q.to(torch.bfloat16).to(DEV), K.to(DEV)))[0, :, 0]
+    # (log2 units per unit of K: the product of two fp32 numbers, rounded to fp32, as in the kernels)
+    c2 = float(np.float32(np.float32(1.0 / np.float32(np.sqrt(np.float32(d)))) * np.float32(1.4426950408889634)))
+    z = f64(K[0, :, :, 0]) * c2
+    w = np.exp2(z - z.max(axis=1, keepdims=True))
+    return got, w / w.sum(axis=1, keepdims=True)
+
+
+@pytest.mark.parametrize("n,d,heads", [(200, 128, 40), (260, 64, 40), (511, 128, 16)])
+def test_late_logits_keep_the_precision_of_early_ones(n, d, heads):
+    """One key per head carries the row; it lies 20 to 120 log2 units above the first keys.  Its score is off by the
+    rounding of log2(sum) + reference below one, 2^-24, of the exponentials and the logarithm of the hardware, about one
+    unit of 2^-23 each, and of the division: 4e-7.  (Weighed against the first keys, z - reference alone is rounded by up to
+    2^-18, 2.6e-6 of the score.  Few rows: the rows are equal, so the rounding of a sum over them does not average out.)"""
+    print(f"late logits n={n} d={d}", flush=True)
+    rng = np.random.default_rng(n)
+    unit = np.sqrt(d) / 1.4426950408889634                          # of K per log2 unit
+    k0 = np.full((heads, n), -140.0 * unit)
+    late = rng.integers(n // 3, n, heads)
+    k0[:, :32] = -np.linspace(20.0, 120.0, heads)[:, None] * unit
+    k0[np.arange(heads), late] = rng.uniform(-0.9, 0.9, heads) * unit
+    got, want = scores_of(k0, n, d, heads)
+    err = np.abs(got - want)[np.arange(heads), late]
+    print("worst", err.max())
+    assert err.max() < 4e-7
+
+
+@pytest.mark.parametrize("first,last", [(320, 352), (0, 32), (0, 400), (1000, 2049), (640, 1280)])
+def test_keys_without_a_finite_logit(first, last):
+    """Keys first .. last-1 have logits of -inf; 33 tiles of 64 keys in runs of a few tiles each.  Their score is zero, that of the
+    others the softmax over them."""
+    n, d = 2049, 128
+    print(f"-inf logits {first}..{last}", flush=True)
+    rng = np.random.default_rng(first)
+    k0 = rng.normal(size=(1, n)) * np.sqrt(d)
+    k0[:, first:last] = -np.inf
+    got, want = scores_of(k0, n, d)
+    assert (got[:, first:last] == 0.0).all()
+    assert np.isfinite(got).all()
+    ok = want > 0
+    assert (np.abs(got - want)[ok] / want[ok]).max() < 2e-5
