@@ -105,8 +105,8 @@ PULSECOL_API pulsecol_status pulsecol_validate_shape(const pulsecol_shape* shape
 /* Create a context on HIP device `device`: copies `shape`, allocates the scratch
  * (4*B*H*seq bytes of row statistics, 4*B*H*U*seq bytes of scores, 4*B*H*U*k_max bytes for the
  * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 256 bytes of counters; bf16 shapes
- * whose grids leave part of the chip idle: partial results of the scoring passes, at most 16 MiB together with the
- * row statistics and the scores, and up to 4 MiB for the ragged lengths of a padded batch).
+ * whose grids leave part of the chip idle: partial results of the scoring passes, at most 64 MiB together with the
+ * row statistics and the scores, and at most 16 MiB for the ragged lengths of a padded batch).
  * *out is set only on PULSECOL_OK. */
 PULSECOL_API pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape, int device);
 
@@ -164,7 +164,8 @@ PULSECOL_API pulsecol_status pulsecol_select(pulsecol_ctx* ctx, const void* Q, c
 /* The scoring stage alone (Sec. 3.3, score equation):
  * scores_out[b, h, u, j] = (1/|G_u|) sum_{i in G_u} softmax_j(q_i . k_j * scale), fp32 [B, H, U, seq].
  * Row sums of the softmax are accumulated in fp32 in a fixed order: results are
- * bit-identical from run to run. */
+ * bit-identical from run to run.  bf16: the scores of a head follow from its own Q, K, length and group size alone; they are the
+ * same bits whatever other heads and batch elements a context holds. */
 PULSECOL_API pulsecol_status pulsecol_scores(pulsecol_ctx* ctx, const void* Q, const void* K, float* scores_out,
                                 void* stream);
 

@@ -10,8 +10,8 @@
 // 64-row tiles of the other tensor through LDS as the A operand: direct-to-LDS loads into one of three
 // tile slots, issued two tiles ahead of their use.  In S[streamed][stationary] a lane owns one
 // stationary row and its 16 registers are 16 streamed rows, so the sum over the streamed rows is an
-// in-lane sum (four interleaved partial sums, each a short and a long accumulator) and the two
-// half-waves meet once at the end (column pass: once per group).
+// in-lane sum (a short accumulator, in the column pass four interleaved ones, that is added to a long one now and
+// then) and the two half-waves meet at the end of a segment (column pass with several query groups: of a group).
 //   column pass: exp2(z*c - lse_i) takes lse_i per register row, read from LDS four at a time.
 //   row pass: exp2(z*c - ref) against one reference per lane, a whole number, at first 3 log2 units above
 //     the maximum of the first 32 keys (ordinary rows rise 5 to 10 units above it, and a raise costs the
@@ -22,15 +22,18 @@
 // P never leaves fp32 and there are no floating-point atomics: the result is bit-identical
 // from run to run.
 //
-// The streamed range of a head is cut into `splits` runs of whole tiles when one workgroup per head and
-// block would leave the chip idle (score_splits): every run is a workgroup of its own and leaves a
-// partial result, and a small kernel adds the partial results up in a fixed order.  (Column pass with
-// more than one query group: the runs end at group boundaries and nothing is left to add.)
+// The streamed range of a head is made of segments (score_runs.h), each with a sum and (row pass) a reference of its
+// own, which are added up in order.  Where one workgroup per head and block would leave the chip idle the segments are
+// shared out among several (`splits` runs, score_splits): each leaves the results of its segments, and a small
+// kernel adds them up, in the same order: a head's scores do not depend on the grid, the other heads or the other
+// elements of a batch.  (Column pass with more than one query group: the sums are those of the groups, runs end at
+// group boundaries, and nothing is left to add.)
 //
 // What bounds it: two weights and a matrix instruction per 32 cycles of the matrix pipe, about as much as one wave
 // can issue, and over long runs the power limit (about 1.2 PFLOP/s).  The row pass used to be a mode of the 256-row
 // attention kernel, 62 KB of straight-line code that every launch fetches anew; this one is 22 KB,
-// 7 of them the raises, out of the way.  (Checking every block for one costs 0.3% at 64K, 0.8% at 4K.)  D = 128, 32 heads:
+// 6 of them the raises, out of the way.  (Checking every block for one costs 0.3% at 64K, 0.8% at 4K; the ends of segments,
+// in both passes, nothing at 64K, 1.6% at 4K.)  D = 128, 32 heads:
 // 4096 rows 172 -> 128 us, 16384 rows 1877 -> 1842 us, 65536 rows 28.8 -> 28.9 ms.
 #include <utility>
 
@@ -44,8 +47,8 @@ typedef unsigned char byte;
 
 constexpr int NTHREADS = 256;
 constexpr int ROWS_PER_WG = kScoreBlock_bf16;    // stationary rows per workgroup
-constexpr int QT = 64;              // rows per streamed tile
-constexpr int FLUSH = 16;           // tiles between flushes of the short accumulator into the long one
+constexpr int QT = kScoreTile_bf16;         // rows per streamed tile
+constexpr int FLUSH = 16;           // most tiles between flushes of the short accumulator into the long one
 constexpr float kGrowthLimit = 256.0f;      // row pass: sum of a lane's 16 weights of a block that raises the reference
 constexpr float kHeadroom = 3.0f;           // row pass: log2 units between a maximum and the reference taken from it
 constexpr float kNoReference = -1e30f;      // row pass: the reference of a row without a finite logit so far
@@ -133,6 +136,8 @@ struct ScoreWave {
     static constexpr int NPAIR = 2 * KK;                      // fragment reads (= pairs of matrix instructions) per tile
     static constexpr int AHEAD = KK / 2;                      // fragment reads in flight ahead of their use
     static constexpr int PER_SLOT = 16 / KK;                  // weights formed behind each matrix instruction
+    // row pass: behind all but the last one, which covers the closing of the block's sums: the first weight of slot s
+    static constexpr int row_weight(int s) { return s >= 2 * KK - 1 ? 32 : 32 * s / (2 * KK - 1); }
     static constexpr int LSE_RING = 4;                        // tiles whose log-sum-exp values LDS holds at a time
     static constexpr int LSE_BYTES = QT * 4;
     static constexpr int LSE_BASE = 3 * TILE_BYTES;           // the ring follows the three tile slots
@@ -179,9 +184,10 @@ struct ScoreWave {
     f32x16 sb[2][2];          // scores [streamed block qb][stationary block kb]
     f32x4 lr[4];              // column pass: log-sum-exp (log2 units) of four query rows each, of the block whose weights are being formed
     float ref[2];             // row pass: the reference (log2 units, whole) of this lane's query rows
-    float blk[2][4];          // row pass: the sums of the block whose weights are being formed
+    float blk[2][4], sum[2];  // row pass: the sums of the block whose weights are being formed
+    uint64_t grown;           // row pass: lanes whose sums have outgrown the reference
     static constexpr int NACC = ROWS ? 1 : 4;       // (row pass: whole blocks are added up)
-    float acc_short[2][NACC], acc_long[2][NACC];
+    float acc_short[2][NACC], acc_long[2];
     uint32_t xv[KK];          // LDS address of this lane's fragment kk in slot 0, first block
     uint32_t lv;              // column pass: LDS address of this lane's first log-sum-exp group in ring entry 0
     float c2;
@@ -194,14 +200,16 @@ struct ScoreWave {
     __device__ __forceinline__ void add_weight(int kb, int r, float e) {
         if constexpr (ROWS) {
             blk[kb][r & 3] = r < 4 ? e : blk[kb][r & 3] + e;
-            // (chains are added up as they end, so that one addition is left for the end of the block)
-            if (r == 13) blk[kb][0] += blk[kb][1];
-            if (r == 15) blk[kb][2] += blk[kb][3];
         } else {
             acc_short[kb][r & 3] += e;
         }
     }
-    __device__ __forceinline__ float block_sum(int kb) const { return blk[kb][0] + blk[kb][2]; }
+    // row pass: a block's sums, and the lanes where they outgrow the reference (or are NaN)
+    __device__ __forceinline__ void sum_block() {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) sum[kb] = (blk[kb][0] + blk[kb][1]) + (blk[kb][2] + blk[kb][3]);
+        grown = __ballot(!(sum[0] <= kGrowthLimit) | !(sum[1] <= kGrowthLimit));
+    }
     // row pass: a reference from 32 keys, the next whole number above their maximum and kHeadroom more (both half-waves get
     // the same one)
     __device__ __forceinline__ float reference_of(const f32x16& s) const {
@@ -215,12 +223,9 @@ struct ScoreWave {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) ref[kb] = reference_of(s[kb]);
     }
-    // row pass: accept the sums of a block, or raise the reference first.  The scores `s` are the block's.
+    // row pass: accept the sums of a block (sum_block), or raise the reference first.  The scores `s` are the block's.
     __device__ __forceinline__ void close_block(const f32x16 (&s)[2]) {
-        float sum[2];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) sum[kb] = block_sum(kb);
-        if (__builtin_expect(__ballot(!(sum[0] <= kGrowthLimit) | !(sum[1] <= kGrowthLimit)) != 0ull, 0)) {
+        if (__builtin_expect(grown != 0ull, 0)) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
                 const float top = reference_of(s[kb]);
@@ -228,11 +233,11 @@ struct ScoreWave {
                     // (a row without a finite logit so far has nothing to scale)
                     const float down = ref[kb] == kNoReference ? 0.f : fast_exp2(ref[kb] - top);
                     acc_short[kb][0] *= down;
-                    acc_long[kb][0] *= down;
+                    acc_long[kb] *= down;
                     ref[kb] = top;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) add_weight(kb, r, fast_exp2(__builtin_fmaf(s[kb][r], c2, -top)));
-                    sum[kb] = block_sum(kb);
+                    sum[kb] = (blk[kb][0] + blk[kb][1]) + (blk[kb][2] + blk[kb][3]);
                 }
             }
         }
@@ -246,6 +251,19 @@ struct ScoreWave {
         if (g == 1) lr[1] = lds_read_f32x4_at<LSE_BASE + OFF + 32>(ring_addr);
         if (g == 2) lr[2] = lds_read_f32x4_at<LSE_BASE + OFF + 64>(ring_addr);
         if (g == 3) lr[3] = lds_read_f32x4_at<LSE_BASE + OFF + 96>(ring_addr);
+    }
+
+    // the weights behind matrix instruction SLOT of a block
+    template <int SLOT>
+    __device__ __forceinline__ void slot_weights(int cq) {
+        if constexpr (ROWS) {
+#pragma unroll
+            for (int e = row_weight(SLOT); e < row_weight(SLOT + 1); ++e) weight(cq, e);
+            if constexpr (SLOT == 2 * KK - 1) sum_block();
+        } else {
+#pragma unroll
+            for (int i = 0; i < PER_SLOT; ++i) weight(cq, SLOT * PER_SLOT + i);
+        }
     }
 
     // Pair P of the tile in slot S: two matrix instructions on fragment P, the request for fragment P + AHEAD,
@@ -270,10 +288,7 @@ struct ScoreWave {
             constexpr int Q = P + AHEAD;
             fr[Q] = lds_read_b128_at<SLOT + (Q / KK) * 32 * ROW_BYTES>(xv[Q % KK]);
         }
-        if constexpr (CONSUME) {
-#pragma unroll
-            for (int i = 0; i < PER_SLOT; ++i) weight(cq, x * 2 * PER_SLOT + i);
-        }
+        if constexpr (CONSUME) slot_weights<2 * x>(cq);
         fence();
         if constexpr (x == 0) {
             f32x16 zero;
@@ -291,10 +306,7 @@ struct ScoreWave {
         }
         // the block being computed, whose weights the next block's pairs will form
         if constexpr (!ROWS && lse_group_computed(x) >= 0) read_lse<qb * 32 * 4>(lse_group_computed(x), ring_cur);
-        if constexpr (CONSUME) {
-#pragma unroll
-            for (int i = 0; i < PER_SLOT; ++i) weight(cq, x * 2 * PER_SLOT + PER_SLOT + i);
-        }
+        if constexpr (CONSUME) slot_weights<2 * x + 1>(cq);
         fence();
     }
     template <int S, int P0, bool FIRST, int... Ps>
@@ -328,33 +340,42 @@ struct ScoreWave {
         }
 #pragma unroll
         for (int e = 0; e < 32; ++e) weight(cq, e);
+        if constexpr (ROWS) sum_block();
     }
 };
 
-// The tiles [first, last) of run `split` of a streamed range of n rows cut into `splits` runs: whole tiles,
-// as even as they come; with several query groups (unit_rows = rows of a group, column pass) whole groups.
+// Column pass with several query groups: the tiles [first, last) of run `split` of `splits`, whole groups each
 struct TileRun { int first, last; };
-__device__ __forceinline__ TileRun tile_run(int n, int split, int splits, int unit_rows) {
-    const int tiles = (n + QT - 1) / QT;
-    if (splits == 1) return {0, tiles};
+__device__ __forceinline__ TileRun group_run(int tiles, int split, int splits, int group_rows) {
     // a group of an odd number of 32-row blocks ends inside a tile: two of them make whole tiles
-    const int unit = unit_rows == 0 ? 1 : (unit_rows % QT == 0 ? unit_rows / QT : unit_rows / 32);
+    const int unit = group_rows % QT == 0 ? group_rows / QT : group_rows / 32;
     const int units = (tiles + unit - 1) / unit;
     const int per = (units + splits - 1) / splits * unit;
     const int first = split * per < tiles ? split * per : tiles;
     return {first, first + per < tiles ? first + per : tiles};
 }
 
-// A sum of weights and the reference it was formed against: the sum's exponent goes into the reference as a
-// whole number and leaves a sum in [1, 2), so that partial sums can be added without care for their size and
-// the logarithm that is rounded beside the reference is below one.
-__device__ __forceinline__ void normalise(float& ref, float& sum) {
+// Distance of two references, whole numbers (beyond 300 what is scaled down by it is gone; 0 for NaN, whose sums are NaN)
+__device__ __forceinline__ int log2_units(float d) {
+    return d == d ? (int)__builtin_amdgcn_fmed3f(d, -300.0f, 300.0f) : 0;
+}
+// Row pass: a segment's reference and sum on top of those of the segments before it.  References are whole numbers:
+// what is scaled is scaled by an exact power of two.
+__device__ __forceinline__ void add_segment(float& ref, float& sum, float seg_ref, float seg_sum) {
+    const int up = log2_units(seg_ref - ref);
+    sum = ldexpf(sum, up > 0 ? -up : 0) + ldexpf(seg_sum, up < 0 ? up : 0);
+    ref = up > 0 ? seg_ref : ref;
+}
+// log2 of a row's sum: its exponent goes into the reference as a whole number and leaves a sum in [1, 2), so that the
+// logarithm that is rounded beside the reference is below one
+__device__ __forceinline__ float log2_of(float ref, float sum) {
     int e;
     sum = 2.0f * frexpf(sum, &e);
-    ref += (float)(e - 1);
+    return (ref + (float)(e - 1)) + fast_log2(sum);
 }
 
-template <int D, bool ROWS>
+// GROUPED: column pass with several query groups.  CUT: the head's segments (groups) are shared out among several runs
+template <int D, bool ROWS, bool GROUPED, bool CUT>
 __device__ __forceinline__ void score_pass(const ScoreParams& p) {
     using W = ScoreWave<D, ROWS>;
     constexpr int PIECES = W::PIECES;
@@ -381,9 +402,9 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
                          "s"(ROWS ? p.row_splits : p.col_splits));
     // (run `split` of the head's streamed range: the z planes; only few layers of heads are ever cut into runs)
     const int splits = ROWS ? p.row_splits : p.col_splits;
-    const int split = splits > 1 ? blockIdx.z : 0;
+    const int split = CUT ? blockIdx.z : 0;
     int bh, blk, b, h;
-    if (!head_and_block(splits > 1 ? blockIdx.y : blockIdx.z * kLayersPerZ + blockIdx.y, p.batch * p.heads,
+    if (!head_and_block(CUT ? blockIdx.y : blockIdx.z * kLayersPerZ + blockIdx.y, p.batch * p.heads,
                         (p.n + ROWS_PER_WG - 1) / ROWS_PER_WG, &bh, &blk)) return;
     split_head(bh, p.batch, p.heads, &b, &h);
     // variable-length batches: queries and keys of this batch element end at its own length
@@ -404,21 +425,30 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
     const int lq = lane & 31, lh = lane >> 5;
     const int y0 = blk * ROWS_PER_WG + wave * 64;
 
-    // the streamed rows of this run: tiles t0 .. t1-1, rows up to x_end
-    const TileRun run = tile_run(n, split, splits, !ROWS && p.groups > 1 ? p.group_size : 0);
-    const int t0 = run.first, t1 = run.last;
-    const int x_end = t1 * QT < n ? t1 * QT : n;
-    const bool partial = splits > 1 && (ROWS || p.groups == 1);
-    const int64_t part_at = ((int64_t)split * p.batch * p.heads + bh) * p.n;      // this run's partial results
-    const int64_t part_words = (int64_t)splits * p.batch * p.heads * p.n;         // row pass: the sums follow the references
-    if (t0 >= t1) {
-        // a run past the end (an element of a padded batch with few tiles): it adds nothing
-        if (partial && y0 + lane < n) {
-            p.part[part_at + y0 + lane] = ROWS ? -INFINITY : 0.f;
-            if (ROWS) p.part[part_words + part_at + y0 + lane] = 0.f;
+    // the streamed rows of this run: segments seg .. , tiles t0 .. t1-1, rows up to x_end
+    const ScoreSegments segments(n);
+    int seg = 0, t0 = 0, t1 = segments.tiles;
+    if constexpr (CUT) {
+        if constexpr (GROUPED) {
+            const TileRun run = group_run(segments.tiles, split, splits, p.group_size);
+            t0 = run.first;
+            t1 = run.last;
+        } else {
+            const uint32_t reciprocal = ROWS ? p.row_reciprocal : p.col_reciprocal;
+            seg = segments.first_of_run(split, reciprocal);
+            t0 = segments.first_tile(seg);
+            t1 = segments.first_tile(segments.first_of_run(split + 1, reciprocal));
         }
-        return;
     }
+    if (t0 >= t1) return;       // more runs than an element of a padded batch has segments
+    const int x_end = t1 * QT < n ? t1 * QT : n;
+    const int64_t all_rows = (int64_t)p.batch * p.heads * p.n;
+    const int64_t sums_at = p.segment_room * all_rows;          // row pass: the sums follow the references
+    int seg_first = t0, seg_end = GROUPED ? t1 : segments.first_tile(seg + 1);      // the running segment's tiles
+    // the next tile in front of which something is to be done but forming weights: the end of the running segment, or a
+    // flush of the short accumulators every FLUSH tiles of it (groups: of the head)
+    int stop = t0 + FLUSH - (GROUPED ? t0 % FLUSH : 0);
+    stop = stop < seg_end ? stop : seg_end;
 
     W w;
     // ---- stationary fragments
@@ -451,53 +481,90 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
     const int nfull = x_end / QT - t0;      // whole tiles: the interleaved steps; a ragged last tile is computed apart
     w.c2 = p.scale * kLog2e;
     w.ref[0] = w.ref[1] = 0.f;
-    // per stationary block kb, this lane's row; four interleaved partial sums keep the add chains independent
+    // per stationary block kb, this lane's row; (column pass) four interleaved partial sums keep the add chains independent
+    auto start_sums = [&] {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < 2; ++kb) {
+            w.acc_long[kb] = 0.f;
 #pragma unroll
-        for (int c = 0; c < W::NACC; ++c) { w.acc_short[kb][c] = 0.f; w.acc_long[kb][c] = 0.f; }
-    // this lane's sum of stationary block kb over both half-waves (they hold the same stationary rows, other streamed rows)
-    auto total = [&](int kb) {
-        if constexpr (ROWS) return half_sum(w.acc_long[kb][0] + w.acc_short[kb][0]);
-        else
-        return half_sum(((w.acc_long[kb][0] + w.acc_short[kb][0]) + (w.acc_long[kb][1] + w.acc_short[kb][1])) +
-                        ((w.acc_long[kb][2] + w.acc_short[kb][2]) + (w.acc_long[kb][3] + w.acc_short[kb][3])));
+            for (int c = 0; c < W::NACC; ++c) w.acc_short[kb][c] = 0.f;
+        }
+    };
+    start_sums();
+    auto flush = [&] {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            if constexpr (ROWS) w.acc_long[kb] += w.acc_short[kb][0];
+            else w.acc_long[kb] += (w.acc_short[kb][0] + w.acc_short[kb][1]) + (w.acc_short[kb][2] + w.acc_short[kb][3]);
+#pragma unroll
+            for (int c = 0; c < W::NACC; ++c) w.acc_short[kb][c] = 0.f;
+        }
+    };
+    // this lane's sum of stationary block kb over both half-waves (they hold the same stationary rows, other streamed
+    // rows), behind a flush
+    auto total = [&](int kb) { return half_sum(w.acc_long[kb]); };
+
+    // column pass with several query groups: rows until the running one ends (a run starts at a group's first row)
+    int rows_to_group_end = p.group_size;
+
+    float all_ref[2] = {kNoReference, kNoReference}, all_sum[2] = {0.f, 0.f};      // of the segments that have ended
+    // The end of segment `seg`: its sum (row pass: and reference) into registers, or to memory, to be added up when all runs
+    // have ended; accumulators start over.
+    auto end_segment = [&] {
+        flush();
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const float v = total(kb);
+            const int row = y0 + kb * 32 + lq;
+            if constexpr (CUT) {
+                if (lh == 0 && row < n) {
+                    float* const at = p.part + (seg * all_rows + (int64_t)bh * p.n + row);
+                    if (ROWS) { at[0] = w.ref[kb]; at[sums_at] = v; }
+                    else at[0] = v;
+                }
+            } else if constexpr (ROWS) {
+                add_segment(all_ref[kb], all_sum[kb], w.ref[kb], v);
+            } else {
+                all_sum[kb] += v;
+            }
+            w.acc_long[kb] = 0.f;
+        }
+        ++seg;
     };
 
-    // column pass: rows until the running query group ends (groups are multiples of 32 rows; one group: never;
-    // a run starts at a group's first row)
-    int rows_to_group_end = p.groups > 1 ? p.group_size : 0x7fffffff;
-
-    // What follows the weights of block qb of the run's tile t: the periodic flush of the short accumulators and,
-    // in the column pass at the last rows of a query group (groups are multiples of 32 rows), the group's score
-    // row: add the two half-waves, divide by the group's size, store, start over.
+    // What follows the weights of block qb of the run's tile t: the periodic flush of the short accumulators,
+    // the end of a segment inside the run, and in the column pass with several query groups at
+    // the last rows of one (groups are multiples of 32 rows), the group's score row: add the two half-waves,
+    // divide by the group's size, store, start over.
     auto block_done = [&](int t, int qb) {
-        if constexpr (ROWS) w.close_block(w.sb[qb]);
-        if (qb == 1 && (t % FLUSH) == FLUSH - 1) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int c = 0; c < W::NACC; ++c) { w.acc_long[kb][c] += w.acc_short[kb][c]; w.acc_short[kb][c] = 0.f; }
+        if (qb == 1 && __builtin_expect(t0 + t + 1 == stop, 0)) {
+            if (stop < seg_end) {
+                flush();
+            } else if (seg_end < t1) {
+                end_segment();
+                seg_first = seg_end;
+                seg_end = segments.first_tile(seg + 1);
+            }
+            stop = stop + FLUSH < seg_end ? stop + FLUSH : seg_end;
         }
-        if constexpr (!ROWS) {
+        if constexpr (GROUPED) {
             const int rows_done = (t0 + t) * QT + (qb + 1) * 32;
             rows_to_group_end -= 32;
             const bool group_end = (rows_done >= x_end) || (rows_to_group_end == 0 && rows_done < x_end);
             if (rows_to_group_end == 0) rows_to_group_end = p.group_size;
             if (group_end) {
                 const int rows_seen = rows_done < x_end ? rows_done : x_end;
-                const int u = p.groups > 1 ? (rows_seen - 1) / p.group_size : 0;
-                const int g_first = p.groups > 1 ? u * p.group_size : 0;
-                const int g_rows = rows_seen - g_first;
-                const float inv = partial ? 1.0f : 1.0f / (float)g_rows;
-                float* __restrict__ out = partial ? p.part + part_at : p.scores + ((int64_t)bh * p.groups + u) * p.n;
+                const int u = (rows_seen - 1) / p.group_size;
+                const int g_rows = rows_seen - u * p.group_size;
+                const float inv = 1.0f / (float)g_rows;
+                float* __restrict__ out = p.scores + ((int64_t)bh * p.groups + u) * p.n;
+                flush();
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
                     const float v = total(kb);
                     const int key = y0 + kb * 32 + lq;
                     if (lh == 0 && key < n) out[key] = v * inv;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) { w.acc_long[kb][c] = 0.f; w.acc_short[kb][c] = 0.f; }
+                    w.acc_long[kb] = 0.f;
                 }
             }
         }
@@ -534,10 +601,13 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
         const uint32_t ring_cur = ring_of(t), ring_prev = ring_of(t - 1);
         // first block of the tile, with the weights of the second block of the tile before
         w.template pairs<S, 0, FIRST>(fr, ring_cur, ring_prev, std::make_integer_sequence<int, KK>{});
+        if constexpr (ROWS && !FIRST) w.close_block(w.sb[1]);
         if (!FIRST) block_done(t - 1, 1);
-        if constexpr (ROWS && FIRST) w.set_reference(w.sb[0]);
+        // (a segment that starts with this tile: its reference)
+        if (ROWS && (FIRST || __builtin_expect(seg_first == t0 + t, 0))) w.set_reference(w.sb[0]);
         // second block, with the weights of the first
         w.template pairs<S, KK, FIRST>(fr, ring_cur, ring_prev, std::make_integer_sequence<int, KK>{});
+        if constexpr (ROWS) w.close_block(w.sb[0]);
         block_done(t, 0);
     };
     if (nfull > 0) {
@@ -551,6 +621,7 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
         }
         // the weights of the last whole tile's second block, on their own
         w.weights_alone(1, ring_of(nfull - 1));
+        if constexpr (ROWS) w.close_block(w.sb[1]);
         block_done(nfull - 1, 1);
     }
     wait_vmcnt_at_most<0>();
@@ -563,7 +634,7 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
         const byte* xslot = lds_all + (t % 3) * TILE_BYTES;
         const float* lslot = (const float*)(lds_all + W::LSE_BASE + (t & (W::LSE_RING - 1)) * W::LSE_BYTES);
         const int valid = n - (t0 + t) * QT;
-#pragma unroll
+#pragma nounroll
         for (int qb = 0; qb < 2; ++qb) {
             if (qb * 32 >= valid) break;
             f32x16 s[2];
@@ -595,23 +666,20 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
                     w.add_weight(kb, r, (ROWS || qb * 32 + acc_row(r, lh) < valid) ? e : 0.f);
                 }
             }
-            if constexpr (ROWS) { w.sb[qb][0] = s[0]; w.sb[qb][1] = s[1]; }
+            if constexpr (ROWS) { w.sum_block(); w.close_block(s); }
             block_done(t, qb);
         }
     }
 
-    if constexpr (ROWS) {
-        float sum[2] = {total(0), total(1)};
+    if constexpr (!GROUPED) {
+        end_segment();              // the run's last one
+        if constexpr (!CUT) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const int row = y0 + kb * 32 + lq;
-            normalise(w.ref[kb], sum[kb]);
-            if (lh == 0 && row < n) {
-                if (partial) {
-                    p.part[part_at + row] = w.ref[kb];
-                    p.part[part_words + part_at + row] = sum[kb];
-                } else {
-                    p.lse[(int64_t)bh * p.n + row] = w.ref[kb] + fast_log2(sum[kb]);
+            for (int kb = 0; kb < 2; ++kb) {
+                const int row = y0 + kb * 32 + lq;
+                if (lh == 0 && row < n) {
+                    if (ROWS) p.lse[(int64_t)bh * p.n + row] = log2_of(all_ref[kb], all_sum[kb]);
+                    else p.scores[(int64_t)bh * p.n + row] = all_sum[kb] * (1.0f / (float)n);
                 }
             }
         }
@@ -620,50 +688,61 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
 
 template <int D>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
-rowlse_bf16_kernel(ScoreParams p) { score_pass<D, true>(p); }
+rowlse_bf16_kernel(ScoreParams p) { score_pass<D, true, false, false>(p); }
 
 template <int D>
 __global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
-colmass_bf16_kernel(ScoreParams p) { score_pass<D, false>(p); }
+rowlse_runs_bf16_kernel(ScoreParams p) { score_pass<D, true, false, true>(p); }
 
-// ---- partial results of the runs, added up in run order.  One thread per row (row pass) or key (column pass)
-// of a head; latency-bound: the sizes that are split have at most 2^17 of them.
-__global__ void __launch_bounds__(NTHREADS) rowlse_combine_kernel(ScoreParams p, int64_t count) {
-    const int64_t i = (int64_t)blockIdx.x * NTHREADS + threadIdx.x;
-    if (i >= count) return;
-    const float* __restrict__ ref = p.part + i;
-    const float* __restrict__ sum = p.part + (int64_t)p.row_splits * count + i;
-    float m[kMaxScoreSplits], l[kMaxScoreSplits], top = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < kMaxScoreSplits; ++s) {
-        const bool in = s < p.row_splits;
-        m[s] = in ? ref[s * count] : -INFINITY;
-        l[s] = in ? sum[s * count] : 0.f;
-        top = fmaxf(top, m[s]);
-    }
-    float all = 0.f;
-#pragma unroll
-    for (int s = 0; s < kMaxScoreSplits; ++s)
-        if (l[s] != 0.f) all += l[s] * fast_exp2(m[s] - top);
-    normalise(top, all);
-    p.lse[i] = top + fast_log2(all);
-}
+template <int D>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
+colmass_bf16_kernel(ScoreParams p) { score_pass<D, false, false, false>(p); }
 
-__global__ void __launch_bounds__(NTHREADS) colmass_combine_kernel(ScoreParams p, int64_t count) {
-    const int64_t i = (int64_t)blockIdx.x * NTHREADS + threadIdx.x;
-    if (i >= count) return;
+template <int D>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
+colmass_runs_bf16_kernel(ScoreParams p) { score_pass<D, false, false, true>(p); }
+
+template <int D>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
+colmass_groups_bf16_kernel(ScoreParams p) { score_pass<D, false, true, false>(p); }
+
+template <int D>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2)))
+colmass_groups_runs_bf16_kernel(ScoreParams p) { score_pass<D, false, true, true>(p); }
+
+// ---- the segments of heads that were cut into runs, added up in order.  One thread per row (row pass) or key (column
+// pass), y = the head; latency-bound: all loads go out at once, and the sums are scaled to the last reference in one
+// step (add_segment scales by exact powers of two: the same bits).
+// MOST: segments that a head may have
+template <bool ROWS, int MOST>
+__global__ void __launch_bounds__(NTHREADS) score_combine_kernel(ScoreParams p) {
+    const int bh = blockIdx.y, row = blockIdx.x * NTHREADS + threadIdx.x;
     int n = p.n;
-    if (p.varlen != nullptr) {
-        const int64_t bh = i / p.n;
-        n = p.varlen[bh / p.heads];
-        if (i - bh * p.n >= n) return;       // padding: left untouched
+    if (p.varlen != nullptr) n = p.varlen[bh / p.heads];
+    if (row >= n) return;                    // (padding: left untouched)
+    const int segments = ScoreSegments(n).count;
+    const int64_t count = (int64_t)p.batch * p.heads * p.n, at = (int64_t)bh * p.n + row;
+    const float* __restrict__ first = p.part + at;
+    const float* __restrict__ second = first + p.segment_room * count;
+    float a[MOST], b[MOST];
+#pragma unroll
+    for (int s = 0; s < MOST; ++s) {
+        const int64_t from = (s < segments ? s : 0) * count;
+        a[s] = first[from];
+        if (ROWS) b[s] = second[from];
     }
-    float v[kMaxScoreSplits], all = 0.f;
+    float ref = kNoReference, sum = 0.f;
+    if (ROWS) {
 #pragma unroll
-    for (int s = 0; s < kMaxScoreSplits; ++s) v[s] = s < p.col_splits ? p.part[s * count + i] : 0.f;
+        for (int s = 0; s < MOST; ++s) ref = fmaxf(ref, a[s]);
+    }
 #pragma unroll
-    for (int s = 0; s < kMaxScoreSplits; ++s) all += v[s];
-    p.scores[i] = all * (1.0f / (float)n);
+    for (int s = 0; s < MOST; ++s) {
+        const float v = ROWS ? ldexpf(b[s], log2_units(a[s] - ref)) : a[s];
+        sum += s < segments ? v : 0.f;
+    }
+    if (ROWS) p.lse[at] = log2_of(ref, sum);
+    else p.scores[at] = sum * (1.0f / (float)n);
 }
 
 dim3 grid_of(const ScoreParams& p, int splits) {
@@ -671,59 +750,44 @@ dim3 grid_of(const ScoreParams& p, int splits) {
     if (splits > 1) g.z = splits;
     return g;
 }
-dim3 combine_grid(int64_t count) { return dim3((unsigned)((count + NTHREADS - 1) / NTHREADS)); }
+template <bool ROWS>
+void launch_combine(const ScoreParams& p, hipStream_t s) {
+    const dim3 grid((unsigned)((p.n + NTHREADS - 1) / NTHREADS), (unsigned)(p.batch * p.heads));
+    if (p.segment_room <= 4) hipLaunchKernelGGL((score_combine_kernel<ROWS, 4>), grid, dim3(NTHREADS), 0, s, p);
+    else if (p.segment_room <= 12) hipLaunchKernelGGL((score_combine_kernel<ROWS, 12>), grid, dim3(NTHREADS), 0, s, p);
+    else hipLaunchKernelGGL((score_combine_kernel<ROWS, kMaxScoreSegments>), grid, dim3(NTHREADS), 0, s, p);
+}
 
 bool splits_fit(const ScoreParams& p, int splits) {
-    return splits == 1 || (splits > 1 && splits <= kMaxScoreSplits && p.part != nullptr &&
-                           (int64_t)p.batch * p.heads <= 8 * (int64_t)kLayersPerZ);
+    return splits == 1 || (splits > 1 && splits <= kMaxScoreSegments && p.part != nullptr &&
+                           (int64_t)p.batch * p.heads <= kLayersPerZ);      // (y of the combining launch)
 }
 
 }  // namespace
 
-// Runs per head and block.  A CU holds two workgroups of either pass; one that is alone on its CU leaves the
-// matrix pipe idle while it forms weights, a grid smaller than the chip leaves CUs idle altogether, and so does the
-// last round of one a little larger.  The rule counts rounds of 2 * CUs workgroups in units of a tile: a run costs its
-// tiles and 2.5 for its start (stationary rows and first tiles from memory), a last round that leaves one workgroup to a
-// CU two thirds of a full one, the launches that add the partial results up 1.5; runs have at least four tiles.
-// Both passes together, D = 128, uncut and cut: 32 heads of 1000 rows 56.4 -> 32.4 us (with the row pass
-// of its own, see above), 4 heads of 8192 rows 264 -> 133 us, 8 heads of 5003 rows in groups of 64 184 -> 114 us;
-// grids of more than half the chip and up to two rounds: 20 heads of 4096 rows 204 -> 167 us, 24 heads 211 -> 192, 18
-// heads of 8192 661 -> 554, 28 heads 889 -> 835, 10 heads of 15360 1235 -> 1069, 20 heads of 8192 at D = 64 462 -> 402 us.
-// Four elements of 3000, 1711, 902 and 130 rows, 8 heads, two runs -> three: selection and attention 105 -> 101 us.
-int score_splits(int64_t blocks, int32_t longest, int most) {
-    const double slots = 2.0 * compute_units(), tiles = (longest + QT - 1) / QT;
-    int best = 1;
-    double best_cost = 0.0;
-    for (int s = 1; s <= most && s <= kMaxScoreSplits && (s == 1 || tiles >= 4.0 * s); ++s) {
-        const double rounds = (double)blocks * s / slots, whole = __builtin_floor(rounds), rest = rounds - whole;
-        const double last = rest == 0.0 ? 0.0 : (rest <= 0.5 ? 0.65 : 1.0);
-        const double cost = (whole + last) * (tiles / s + 2.5) + (s > 1 ? 1.5 : 0.0);
-        if (s == 1 || cost < 0.95 * best_cost) { best = s; best_cost = cost; }
-    }
-    return best;
-}
-
 hipError_t launch_rowlse_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {
-    if (!splits_fit(p, p.row_splits)) return hipErrorInvalidValue;
-    if (head_dim == 128) hipLaunchKernelGGL((rowlse_bf16_kernel<128>), grid_of(p, p.row_splits), dim3(NTHREADS), 0, s, p);
-    else if (head_dim == 64) hipLaunchKernelGGL((rowlse_bf16_kernel<64>), grid_of(p, p.row_splits), dim3(NTHREADS), 0, s, p);
-    else return hipErrorInvalidValue;
-    if (p.row_splits > 1) {
-        const int64_t count = (int64_t)p.batch * p.heads * p.n;
-        hipLaunchKernelGGL(rowlse_combine_kernel, combine_grid(count), dim3(NTHREADS), 0, s, p, count);
-    }
+    if (!splits_fit(p, p.row_splits) || (head_dim != 128 && head_dim != 64)) return hipErrorInvalidValue;
+    const bool cut = p.row_splits > 1;
+    const dim3 grid = grid_of(p, p.row_splits);
+    auto* const kernel = head_dim == 128 ? (cut ? rowlse_runs_bf16_kernel<128> : rowlse_bf16_kernel<128>)
+                                         : (cut ? rowlse_runs_bf16_kernel<64> : rowlse_bf16_kernel<64>);
+    hipLaunchKernelGGL(kernel, grid, dim3(NTHREADS), 0, s, p);
+    if (cut) launch_combine<true>(p, s);
     return hipGetLastError();
 }
 
+template <int D>
+static auto* colmass_kernel(bool groups, bool cut) {
+    if (groups) return cut ? colmass_groups_runs_bf16_kernel<D> : colmass_groups_bf16_kernel<D>;
+    return cut ? colmass_runs_bf16_kernel<D> : colmass_bf16_kernel<D>;
+}
+
 hipError_t launch_colmass_bf16(const ScoreParams& p, int head_dim, hipStream_t s) {
-    if (!splits_fit(p, p.col_splits)) return hipErrorInvalidValue;
-    if (head_dim == 128) hipLaunchKernelGGL((colmass_bf16_kernel<128>), grid_of(p, p.col_splits), dim3(NTHREADS), 0, s, p);
-    else if (head_dim == 64) hipLaunchKernelGGL((colmass_bf16_kernel<64>), grid_of(p, p.col_splits), dim3(NTHREADS), 0, s, p);
-    else return hipErrorInvalidValue;
-    if (p.col_splits > 1 && p.groups == 1) {
-        const int64_t count = (int64_t)p.batch * p.heads * p.n;
-        hipLaunchKernelGGL(colmass_combine_kernel, combine_grid(count), dim3(NTHREADS), 0, s, p, count);
-    }
+    if (!splits_fit(p, p.col_splits) || (head_dim != 128 && head_dim != 64)) return hipErrorInvalidValue;
+    const bool cut = p.col_splits > 1, groups = p.groups > 1;
+    const dim3 grid = grid_of(p, p.col_splits);
+    hipLaunchKernelGGL((head_dim == 128 ? colmass_kernel<128>(groups, cut) : colmass_kernel<64>(groups, cut)), grid, dim3(NTHREADS), 0, s, p);
+    if (cut && !groups) launch_combine<false>(p, s);
     return hipGetLastError();
 }
 

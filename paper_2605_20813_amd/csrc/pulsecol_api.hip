@@ -25,10 +25,10 @@ struct pulsecol_ctx {
     int kv_heads = 1;
     float* lse = nullptr;           // [B*H, n]   row log-sum-exp, log2 units
     float* scores = nullptr;        // [B*H*U, n]
-    float* part = nullptr;          // partial results of split scoring passes; U > 1: in the scores' words
-    int part_splits = 1;            // runs that `part` has room for (1: it has none)
+    float* part = nullptr;          // results of the segments of scoring passes cut into runs; U > 1: in the scores' words
+    bool room = false;              // `part` has been allocated
     int fixed_splits = 1;           // runs into which the scoring passes cut a head (bf16) of `seq` rows in every element
-    int score_splits = 1;           // ... and with the present lengths, at most part_splits
+    int score_splits = 1;           // ... and with the present lengths; more than one only where there is room
     int32_t* cached_idx = nullptr;  // [B*H*U, cached_k]
     int32_t cached_k = 0;           // 0 = nothing cached
     int32_t k_max = 0;              // columns per group the cache has room for
@@ -141,13 +141,13 @@ void derive_from_shape(pulsecol_ctx* c, const pulsecol_shape* shape, int device)
     }
 }
 
-// Partial results of split scoring passes (bf16).  Per run and row the row pass leaves two words and the column pass,
-// with one query group, one (after the first ones have been used up).  With several groups the column pass leaves
-// none, and the row pass's may lie where the scores will.
-constexpr size_t kPartWords = (size_t)1 << 20;      // what a padded batch gets, whose lengths are not known yet
-
-// ... and the most that scores, partial results and row statistics may take together where a shape is cut: what the
-// static scratch of pulsecol_select_noalloc holds, so that it cuts every shape as a context does
+// Scoring passes cut into runs (bf16) keep the results of a head's segments until all have ended: two words per segment and
+// row from the row pass, then, with one query group, one from the column pass.  With several groups the column pass
+// leaves none, and the row pass's may lie where the scores will.  Whether a pass is cut does not change its result.
+// The most that row statistics, scores and segments may take together, in fp32 words: what the grids that gain from
+// a cut need (2500 blocks of 256 rows in twelve segments, five rounds of the chip); for the lengths, not known yet, of a padded batch; and
+// in the static scratch of pulsecol_select_noalloc.
+constexpr size_t kMostFloats = (size_t)16 << 20, kPaddedFloats = (size_t)4 << 20;
 constexpr size_t kNoallocFloats = (size_t)4 << 20;                 // 16 MiB
 
 size_t row_words(const pulsecol_ctx* c) { return (size_t)c->shape.batch * c->shape.heads * (size_t)c->shape.seq; }
@@ -161,25 +161,22 @@ int splits_of(const pulsecol_ctx* c, const int32_t* lens) {
         work += (int64_t)((n + pulsecol::kScoreBlock_bf16 - 1) / pulsecol::kScoreBlock_bf16) * c->shape.heads * n;
         longest = n > longest ? n : longest;
     }
-    const int64_t blocks = (work + longest - 1) / longest;
-    // (one group: row statistics, scores and 2 words per run and row; else the partial results lie in the scores)
-    const size_t per_row = kNoallocFloats / row_words(c), taken = c->groups == 1 ? 2 : 1;
-    const size_t most = per_row > taken ? (per_row - taken) / 2 : 0;
-    return pulsecol::score_splits(blocks, longest, (int)std::min<size_t>(most, pulsecol::kMaxScoreSplits));
+    return pulsecol::score_splits((work + longest - 1) / longest, longest, pulsecol::compute_units());
 }
 
-// chooses the number of runs and returns the fp32 words that scores and partial results take
-size_t score_words(pulsecol_ctx* c, bool any_lengths) {
-    c->fixed_splits = c->score_splits = c->part_splits = splits_of(c, nullptr);
-    if (any_lengths && c->shape.batch > 1 && c->shape.dtype == PULSECOL_BF16) {
-        const size_t room = std::min<size_t>(kPartWords / (2 * row_words(c)), pulsecol::kMaxScoreSplits);
-        c->part_splits = std::max(c->part_splits, (int)room);
-    }
-    const size_t part = c->part_splits > 1 ? 2 * (size_t)c->part_splits : 0, groups = (size_t)c->groups;
-    return row_words(c) * (groups == 1 ? 1 + part : std::max(groups, part));
+// chooses the number of runs, and whether there is room for the results of segments (at most `most` words altogether);
+// returns the fp32 words that scores and segments take
+size_t score_words(pulsecol_ctx* c, size_t most, size_t most_padded) {
+    const size_t groups = (size_t)c->groups, segment_words = 2 * (size_t)pulsecol::ScoreSegments(c->shape.seq).count;
+    const size_t with = row_words(c) * (groups == 1 ? 1 + segment_words : std::max(groups, segment_words));
+    const bool padded = c->shape.batch > 1 && c->shape.dtype == PULSECOL_BF16 && segment_words > 2;
+    c->fixed_splits = row_words(c) + with <= most ? splits_of(c, nullptr) : 1;
+    c->room = c->fixed_splits > 1 || (padded && row_words(c) + with <= most_padded);
+    c->score_splits = c->fixed_splits;
+    return c->room ? with : row_words(c) * groups;
 }
 void place_part(pulsecol_ctx* c) {
-    c->part = c->part_splits > 1 ? c->scores + (c->groups == 1 ? row_words(c) : 0) : nullptr;
+    c->part = c->room ? c->scores + (c->groups == 1 ? row_words(c) : 0) : nullptr;
 }
 
 struct DeviceGuard {
@@ -262,6 +259,9 @@ pulsecol::ScoreParams score_params(pulsecol_ctx* ctx, const void* Q, const void*
     // several query groups: a run is made of whole groups (two of them where a group ends inside a 64-row tile)
     const int units = ctx->groups > 1 && sp.group_size % 64 != 0 ? (ctx->groups + 1) / 2 : ctx->groups;
     sp.col_splits = ctx->groups > 1 && units < ctx->score_splits ? units : ctx->score_splits;
+    sp.row_reciprocal = pulsecol::run_reciprocal(sp.row_splits);
+    sp.col_reciprocal = pulsecol::run_reciprocal(sp.col_splits);
+    sp.segment_room = pulsecol::ScoreSegments(sp.n).count;
     sp.part = ctx->part;
     return sp;
 }
@@ -381,7 +381,7 @@ pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape,
     const size_t rows = (size_t)shape->batch * shape->heads;
     const size_t row_bytes = (size_t)shape->seq * sizeof(float);
     hipError_t e1 = hipMalloc((void**)&c->lse, rows * row_bytes);
-    hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, score_words(c, true) * sizeof(float)) : e1;
+    hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, score_words(c, kMostFloats, kPaddedFloats) * sizeof(float)) : e1;
     c->k_max = shape->max_keep_ratio > 0.0 ? pulsecol_num_keep(shape->seq, shape->max_keep_ratio) : shape->seq;
     hipError_t e3 = e2 == hipSuccess ? hipMalloc((void**)&c->cached_idx, rows * c->groups * (size_t)c->k_max * sizeof(int32_t)) : e2;
     static_assert(64 + pulsecol::kWorkCounters * sizeof(unsigned long long) <= 256, "counter block");
@@ -445,7 +445,7 @@ pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens
         if (e != hipSuccess) { ctx->varlen_on = false; return fail_hip(ctx, e, "pulsecol_set_seq_lens: storing the lengths"); }
     }
     ctx->varlen_on = true;
-    ctx->score_splits = std::min(splits_of(ctx, seq_lens), ctx->part_splits);
+    ctx->score_splits = ctx->room ? splits_of(ctx, seq_lens) : 1;
     ctx->cached_k = 0;            // a cached pattern belongs to the lengths it was selected with
     return PULSECOL_OK;
 }
@@ -532,11 +532,11 @@ pulsecol_status pulsecol_select_noalloc(const pulsecol_shape* shape, const void*
     derive_from_shape(&c, shape, dev);
     const size_t rows = (size_t)shape->batch * shape->heads;
     const size_t need = rows * (size_t)shape->seq * (1 + (size_t)c.groups);
-    // (what fits uncut fits cut: splits_of)
-    if (need > kNoallocFloats || rows * (size_t)shape->seq + score_words(&c, false) > kNoallocFloats)
+    if (need > kNoallocFloats)
         return fail(nullptr, PULSECOL_ERR_UNSUPPORTED,
                     "pulsecol_select_noalloc: batch*heads*seq*(1 + groups) = " + std::to_string(need) +
                     " exceeds the static scratch of " + std::to_string(kNoallocFloats) + " fp32 words");
+    (void)score_words(&c, kNoallocFloats, 0);
     c.lse = noalloc_scratch(dev, &e);
     if (!c.lse) return fail_hip(nullptr, e, "pulsecol_select_noalloc: hipGetSymbolAddress");
     c.scores = c.lse + rows * (size_t)shape->seq;

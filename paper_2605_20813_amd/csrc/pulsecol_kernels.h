@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "score_runs.h"
+
 namespace pulsecol {
 
 struct TensorDesc {          // [B, H, n, D] tensor, last dimension contiguous, strides in elements
@@ -52,18 +54,14 @@ struct ScoreParams {
     int32_t group_size;      // rows per group, a multiple of the kernel's query tile (unused when U = 1)
     float scale;
     const int32_t* varlen;   // as in AttnParams (only the lengths are read); scores beyond them are left untouched
-    // bf16: runs into which the streamed range of a head is cut (1 = not at all), row and column pass, and room for
-    // the runs' partial results: [2 * row_splits, B*H, n] and, with one query group, [col_splits, B*H, n] (used one
-    // after the other; may be nullptr if nothing is split; with more than one group it may be `scores` itself)
+    // bf16: runs into which the segments of a head are shared out (1: one workgroup takes them all), row and column
+    // pass, and room for the segments' results: [2 * segments of n rows, B*H, n] and, with one query group, half of that
+    // (used one after the other; may be nullptr if nothing is split; with more than one group it may be `scores` itself)
     int32_t row_splits, col_splits;
+    uint32_t row_reciprocal, col_reciprocal;      // run_reciprocal of them
+    int32_t segment_room;                         // segments of n rows
     float* part;
 };
-
-constexpr int kMaxScoreSplits = 8;
-constexpr int kScoreBlock_bf16 = 256;     // stationary rows per workgroup
-// runs per block that fill the chip in a scoring pass with this many blocks of stationary rows over all heads that
-// stream `longest` rows each (blocks of shorter elements count by their share); at most `most` (bf16)
-int score_splits(int64_t blocks, int32_t longest, int most);
 
 struct TopkParams {
     const float* scores;     // [rows, n], consecutive rows `stride` elements apart

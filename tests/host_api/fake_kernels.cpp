@@ -39,23 +39,23 @@ int fake_row_splits() { return row_splits; }
 int fake_outside() { return outside; }
 int fake_device() { return current; }
 void fake_set_device(int d) { current = d; }
+int fake_segments(int n) { return pulsecol::ScoreSegments(n).count; }
+int fake_first_tile(int n, int i) { return pulsecol::ScoreSegments(n).first_tile(i); }
+int fake_first_of_run(int n, int r, int runs) { return pulsecol::ScoreSegments(n).first_of_run(r, pulsecol::run_reciprocal(runs)); }
 }
 
 namespace pulsecol {
 int compute_units() { return kUnits[current]; }
-// more runs where there are more compute units
-int score_splits(int64_t, int32_t, int most) { const int s = compute_units() / 32; return s < most ? s : most; }
-
 hipError_t launch_rowlse_bf16(const ScoreParams& p, int, hipStream_t) {
     const size_t rows = (size_t)p.batch * p.heads * p.n;
     row_splits = p.row_splits;
     touch(p.lse, rows * 4);
-    if (p.row_splits > 1) touch(p.part, 2 * (size_t)p.row_splits * rows * 4);
+    if (p.row_splits > 1) touch(p.part, 2 * (size_t)ScoreSegments(p.n).count * rows * 4);
     return hipSuccess;
 }
 hipError_t launch_colmass_bf16(const ScoreParams& p, int, hipStream_t) {
     const size_t rows = (size_t)p.batch * p.heads * p.n;
-    if (p.col_splits > 1 && p.groups == 1) touch(p.part, (size_t)p.col_splits * rows * 4);
+    if (p.col_splits > 1 && p.groups == 1) touch(p.part, (size_t)ScoreSegments(p.n).count * rows * 4);
     return hipSuccess;
 }
 hipError_t launch_colmass_f32(const ScoreParams&, int, hipStream_t) { return hipSuccess; }

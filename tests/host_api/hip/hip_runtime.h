@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #define __device__
+#define __host__
 #define __align__(n) __attribute__((aligned(n)))
 #define HIP_SYMBOL(x) ((const void*)&(x))
 

@@ -1,5 +1,5 @@
-"""The static check of test_asm_hazards.py on the other kernels that issue loads from inline assembly: the row pass and
-the plain attention kernel."""
+"""The static check of test_asm_hazards.py on the other kernels that issue loads from inline assembly: the row pass, the
+forms of the scoring passes for runs and query groups, and the plain attention kernel."""
 import os
 import shutil
 
@@ -8,7 +8,9 @@ import pytest
 from test_asm_hazards import _assembly_of, check_function, kernels_of
 
 # file, kernel name, instantiations (row pass: two head dimensions; attention: also four workgroup shapes)
-CHECKED = [("colmass_bf16.hip", "rowlse_bf16_kernel", 2), ("attn_bf16_group.hip", "attn_bf16_group_kernel", 8)]
+CHECKED = [("colmass_bf16.hip", "rowlse_bf16_kernel", 2), ("colmass_bf16.hip", "rowlse_runs_bf16_kernel", 2),
+           ("colmass_bf16.hip", "colmass_runs_bf16_kernel", 2), ("colmass_bf16.hip", "colmass_groups_bf16_kernel", 2),
+           ("colmass_bf16.hip", "colmass_groups_runs_bf16_kernel", 2), ("attn_bf16_group.hip", "attn_bf16_group_kernel", 8)]
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")

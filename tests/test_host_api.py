@@ -62,3 +62,33 @@ def test_fixed_lengths_restored_while_another_device_is_current(api, batch):
     assert ctx.scores() == 0
     assert api.fake_device() == MANY
     ctx.close()
+
+
+def test_segments_and_runs(api):
+    """Segments cover the tiles of a head, three at least; runs are made of whole segments, none empty
+    up to the number of segments, for every length and number of runs."""
+    for n in [*range(1, 4000), 4096, 5003, 8192, 15360, 65536, 65537, 131072, (1 << 24) - 1]:
+        tiles, count = -(-n // 64), api.fake_segments(n)
+        first = [api.fake_first_tile(n, i) for i in range(count + 1)]
+        assert 1 <= count <= 24 and first[0] == 0 and first[-1] == tiles
+        assert all(b - a >= min(3, tiles) for a, b in zip(first, first[1:]))
+        if n % 97 == 0 or n >= 4000:
+            for runs in range(1, 25):
+                at = [api.fake_first_of_run(n, r, runs) for r in range(runs + 1)]
+                assert at[0] == 0 and at[-1] == count and sorted(at) == at
+                assert at == [r * count // runs for r in range(runs + 1)]
+
+
+@pytest.mark.parametrize("lens", [None, [4096, 4096, 4096], [4096, 70, 1], [300, 300, 300]])
+@pytest.mark.parametrize("heads", [1, 4, 11, 40])
+@pytest.mark.parametrize("group", [0, 32, 96, 512])
+def test_room_for_the_segments_of_every_call(api, lens, heads, group):
+    """Whatever lengths are set, what the passes leave for being added up lies in the context's allocations."""
+    for batch, device in ((1, FEW), (3, FEW), (3, MANY)):
+        ctx = Ctx(api, device, batch, heads, 4096, 128, torch.bfloat16, group_size=group)
+        assert ctx.scores() == 0
+        assert ctx.set_seq_lens(lens[:batch] if lens else None) == pc.OK
+        assert ctx.scores() == 0
+        assert ctx.set_seq_lens(None) == pc.OK
+        assert ctx.scores() == 0
+        ctx.close()
