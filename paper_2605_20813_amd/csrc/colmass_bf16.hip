@@ -359,13 +359,26 @@ __device__ __forceinline__ TileRun group_run(int tiles, int split, int splits, i
 __device__ __forceinline__ int log2_units(float d) {
     return d == d ? (int)__builtin_amdgcn_fmed3f(d, -300.0f, 300.0f) : 0;
 }
-// Row pass: a segment's reference and sum on top of those of the segments before it.  References are whole numbers:
-// what is scaled is scaled by an exact power of two.
-__device__ __forceinline__ void add_segment(float& ref, float& sum, float seg_ref, float seg_sum) {
-    const int up = log2_units(seg_ref - ref);
-    sum = ldexpf(sum, up > 0 ? -up : 0) + ldexpf(seg_sum, up < 0 ? up : 0);
-    ref = up > 0 ? seg_ref : ref;
-}
+// The sum of the segments so far, and what its roundings have left out: one after the other twenty-four segments would
+// cost a sum as much precision (7e-8) as the weights of a segment.
+struct SegmentSum {
+    float sum = 0.f, rest = 0.f, ref = 0.f;
+    __device__ __forceinline__ void add(float v) {
+        const float next = sum + v, added = next - sum;
+        rest += (sum - (next - added)) + (v - added);
+        sum = next;
+    }
+    // row pass: a segment with a reference of its own.  References are whole numbers: what is scaled is scaled by an exact
+    // power of two.
+    __device__ __forceinline__ void add(float seg_ref, float v) {
+        const int up = log2_units(seg_ref - ref), down = up > 0 ? -up : 0;
+        sum = ldexpf(sum, down);
+        rest = ldexpf(rest, down);
+        ref = up > 0 ? seg_ref : ref;
+        add(ldexpf(v, up < 0 ? up : 0));
+    }
+    __device__ __forceinline__ float total() const { return sum + rest; }
+};
 // log2 of a row's sum: its exponent goes into the reference as a whole number and leaves a sum in [1, 2), so that the
 // logarithm that is rounded beside the reference is below one
 __device__ __forceinline__ float log2_of(float ref, float sum) {
@@ -507,7 +520,8 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
     // column pass with several query groups: rows until the running one ends (a run starts at a group's first row)
     int rows_to_group_end = p.group_size;
 
-    float all_ref[2] = {kNoReference, kNoReference}, all_sum[2] = {0.f, 0.f};      // of the segments that have ended
+    SegmentSum all[2];                      // of the segments that have ended
+    all[0].ref = all[1].ref = kNoReference;
     // The end of segment `seg`: its sum (row pass: and reference) into registers, or to memory, to be added up when all runs
     // have ended; accumulators start over.
     auto end_segment = [&] {
@@ -523,9 +537,9 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
                     else at[0] = v;
                 }
             } else if constexpr (ROWS) {
-                add_segment(all_ref[kb], all_sum[kb], w.ref[kb], v);
+                all[kb].add(w.ref[kb], v);
             } else {
-                all_sum[kb] += v;
+                all[kb].add(v);
             }
             w.acc_long[kb] = 0.f;
         }
@@ -678,8 +692,8 @@ __device__ __forceinline__ void score_pass(const ScoreParams& p) {
             for (int kb = 0; kb < 2; ++kb) {
                 const int row = y0 + kb * 32 + lq;
                 if (lh == 0 && row < n) {
-                    if (ROWS) p.lse[(int64_t)bh * p.n + row] = log2_of(all_ref[kb], all_sum[kb]);
-                    else p.scores[(int64_t)bh * p.n + row] = all_sum[kb] * (1.0f / (float)n);
+                    if (ROWS) p.lse[(int64_t)bh * p.n + row] = log2_of(all[kb].ref, all[kb].total());
+                    else p.scores[(int64_t)bh * p.n + row] = all[kb].total() * (1.0f / (float)n);
                 }
             }
         }
@@ -712,7 +726,7 @@ colmass_groups_runs_bf16_kernel(ScoreParams p) { score_pass<D, false, true, true
 
 // ---- the segments of heads that were cut into runs, added up in order.  One thread per row (row pass) or key (column
 // pass), y = the head; latency-bound: all loads go out at once, and the sums are scaled to the last reference in one
-// step (add_segment scales by exact powers of two: the same bits).
+// step (by exact powers of two: the same bits).
 // MOST: segments that a head may have
 template <bool ROWS, int MOST>
 __global__ void __launch_bounds__(NTHREADS) score_combine_kernel(ScoreParams p) {
@@ -731,18 +745,18 @@ __global__ void __launch_bounds__(NTHREADS) score_combine_kernel(ScoreParams p) 
         a[s] = first[from];
         if (ROWS) b[s] = second[from];
     }
-    float ref = kNoReference, sum = 0.f;
+    SegmentSum all;
+    all.ref = kNoReference;
     if (ROWS) {
 #pragma unroll
-        for (int s = 0; s < MOST; ++s) ref = fmaxf(ref, a[s]);
+        for (int s = 0; s < MOST; ++s) all.ref = fmaxf(all.ref, a[s]);
+#pragma unroll
+        for (int s = 0; s < MOST; ++s) a[s] = ldexpf(b[s], log2_units(a[s] - all.ref));
     }
 #pragma unroll
-    for (int s = 0; s < MOST; ++s) {
-        const float v = ROWS ? ldexpf(b[s], log2_units(a[s] - ref)) : a[s];
-        sum += s < segments ? v : 0.f;
-    }
-    if (ROWS) p.lse[at] = log2_of(ref, sum);
-    else p.scores[at] = sum * (1.0f / (float)n);
+    for (int s = 0; s < MOST; ++s) if (s < segments) all.add(a[s]);
+    if (ROWS) p.lse[at] = log2_of(all.ref, all.total());
+    else p.scores[at] = all.total() * (1.0f / (float)n);
 }
 
 dim3 grid_of(const ScoreParams& p, int splits) {
