@@ -161,7 +161,7 @@ int splits_of(const pulsecol_ctx* c, const int32_t* lens) {
         work += (int64_t)((n + pulsecol::kScoreBlock_bf16 - 1) / pulsecol::kScoreBlock_bf16) * c->shape.heads * n;
         longest = n > longest ? n : longest;
     }
-    return pulsecol::score_splits((work + longest - 1) / longest, longest, pulsecol::compute_units());
+    return pulsecol::score_splits((work + longest - 1) / longest, longest, c->shape.head_dim, pulsecol::compute_units());
 }
 
 // chooses the number of runs, and whether there is room for the results of segments (at most `most` words altogether);

@@ -42,19 +42,19 @@ struct ScoreSegments {
 inline uint32_t run_reciprocal(int runs) { return (65536u + (uint32_t)runs - 1u) / (uint32_t)runs; }
 
 // Runs per head and block for a scoring pass with this many blocks of stationary rows over all heads that stream `longest`
-// rows each (blocks of shorter elements count by their share).  A CU holds two workgroups of either pass; one that is alone on its
-// CU leaves the matrix pipe idle while it forms weights, a grid smaller than the chip leaves CUs idle altogether, and so
-// does the last round of one a little larger.  The rule counts rounds of 2 * CUs workgroups in units of a tile: a run costs the
-// tiles of the longest one and 2.5 for its start (stationary rows and first tiles from memory), a last round that leaves one
-// workgroup to a CU two thirds of a full one, the launches that add the segments up 1.5.
-// Both passes together, D = 128, uncut and cut: 32 heads of 1000 rows 56.4 -> 32.4 us (with the row pass
-// of its own, see above), 4 heads of 8192 rows 264 -> 133 us, 8 heads of 5003 rows in groups of 64 184 -> 114 us;
-// grids of more than half the chip and up to two rounds: 20 heads of 4096 rows 204 -> 167 us, 24 heads 211 -> 192, 18
-// heads of 8192 661 -> 554, 28 heads 889 -> 835, 10 heads of 15360 1235 -> 1069, 20 heads of 8192 at D = 64 462 -> 402 us.
-// Four elements of 3000, 1711, 902 and 130 rows, 8 heads, two runs -> three: selection and attention 105 -> 101 us.
-inline int score_splits(int64_t blocks, int32_t longest, int compute_units) {
+// rows each (blocks of shorter elements count by their share).  A CU holds two workgroups of either pass at D = 128 and
+// three at D = 64 (registers); fewer leave its matrix pipe idle while they form weights, a grid smaller than the chip leaves
+// CUs idle altogether, and so does the last round of one a little larger.  The rule counts rounds of that many workgroups in
+// units of a tile: a run costs the tiles of the longest one and 2 for its start (stationary rows and first tiles from memory), a last
+// round that leaves one workgroup to a CU 0.6 (D = 128) or 0.5 of a full one, two of three 0.75, the launches that add the
+// segments up 4.  Fitted to 20 grids of 64 to 1024 blocks and 16 to 240 tiles at either head dimension: the choice is within 1.5%
+// (D = 128) and 2.2% (D = 64) of the best number of runs on all of them.
+// Both passes together, uncut and cut, D = 128: 4 heads of 8192 rows 228 -> 130 us, 3 heads 230 -> 115, 32 heads of 1000
+// 38.5 -> 28.5, 20 heads of 8192 666 -> 601, 28 heads 883 -> 832, 10 heads of 15360 1230 -> 1079; D = 64: 4 heads of 8192 190 -> 91,
+// 3 heads 191 -> 76, 36 heads of 4100 (612 blocks, less than a round) 238 -> 211, 60 heads of 1500 66.5 -> 58.
+inline int score_splits(int64_t blocks, int32_t longest, int head_dim, int compute_units) {
     const ScoreSegments segments(longest);
-    const double slots = 2.0 * compute_units;
+    const int per_cu = head_dim == 128 ? 2 : 3;
     int best = 1;
     double best_cost = 0.0;
     for (int s = 1; s <= segments.count; ++s) {
@@ -64,10 +64,14 @@ inline int score_splits(int64_t blocks, int32_t longest, int compute_units) {
             const int t = segments.first_tile(segments.first_of_run(r + 1, reciprocal)) - segments.first_tile(segments.first_of_run(r, reciprocal));
             most = t > most ? t : most;
         }
-        const double rounds = (double)blocks * s / slots, whole = __builtin_floor(rounds), rest = rounds - whole;
-        const double last = rest == 0.0 ? 0.0 : (rest <= 0.5 ? 0.65 : 1.0);
-        const double cost = (whole + last) * (most + 2.5) + (s > 1 ? 1.5 : 0.0);
-        if (s == 1 || cost < 0.95 * best_cost) { best = s; best_cost = cost; }
+        const double rounds = (double)blocks * s / ((double)per_cu * compute_units), whole = __builtin_floor(rounds);
+        const double on_cu = (rounds - whole) * per_cu;               // workgroups to a CU in the last round
+        double last = 1.0;
+        if (on_cu == 0.0) last = 0.0;
+        else if (on_cu <= 1.0) last = per_cu == 2 ? 0.6 : 0.5;
+        else if (on_cu <= 2.0 && per_cu == 3) last = 0.75;
+        const double cost = (whole + last) * (most + 2.0) + (s > 1 ? 4.0 : 0.0);
+        if (s == 1 || cost < best_cost) { best = s; best_cost = cost; }
     }
     return best;
 }

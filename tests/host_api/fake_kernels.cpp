@@ -39,6 +39,7 @@ int fake_row_splits() { return row_splits; }
 int fake_outside() { return outside; }
 int fake_device() { return current; }
 void fake_set_device(int d) { current = d; }
+int fake_splits(int blocks, int longest, int head_dim, int units) { return pulsecol::score_splits(blocks, longest, head_dim, units); }
 int fake_segments(int n) { return pulsecol::ScoreSegments(n).count; }
 int fake_first_tile(int n, int i) { return pulsecol::ScoreSegments(n).first_tile(i); }
 int fake_first_of_run(int n, int r, int runs) { return pulsecol::ScoreSegments(n).first_of_run(r, pulsecol::run_reciprocal(runs)); }

@@ -92,3 +92,24 @@ def test_room_for_the_segments_of_every_call(api, lens, heads, group):
         assert ctx.set_seq_lens(None) == pc.OK
         assert ctx.scores() == 0
         ctx.close()
+
+
+# head dimension, blocks, rows, measured time of both passes (us) by number of runs, 256 compute units
+MEASURED = [
+    (64, 128, 8192, {1: 190.4, 2: 163.2, 3: 155.1, 4: 119.4, 5: 110.2, 6: 90.7, 8: 115.5, 12: 90.4}),
+    (64, 96, 8192, {1: 191.1, 2: 162.9, 3: 154.9, 4: 118.9, 5: 99.2, 6: 85.0, 8: 89.4, 12: 75.5}),
+    (64, 128, 1000, {1: 31.8, 2: 24.4, 3: 28.9, 4: 22.7}),
+    (64, 360, 1500, {1: 66.5, 2: 58.0, 3: 60.9, 4: 58.7, 5: 58.7, 6: 61.6, 8: 59.3}),
+    (64, 612, 4100, {1: 238.0, 2: 211.1, 3: 219.7, 4: 209.7, 5: 216.0, 6: 210.4, 8: 213.4, 12: 212.7}),
+    (64, 768, 8192, {1: 479.9, 2: 480.9, 3: 478.0, 4: 476.7, 5: 478.5, 6: 478.3, 8: 480.3, 12: 483.0}),
+    (128, 128, 8192, {1: 228.4, 2: 191.3, 3: 149.0, 4: 130.1, 5: 146.5, 6: 133.6, 8: 149.3, 12: 135.8}),
+    (128, 96, 8192, {1: 230.3, 2: 191.4, 3: 133.4, 4: 114.8, 5: 117.9, 6: 123.6, 8: 123.6, 12: 110.3}),
+    (128, 600, 15360, {1: 1229.9, 2: 1115.7, 3: 1130.2, 4: 1078.6, 5: 1067.4, 6: 1090.0, 8: 1064.9, 12: 1085.5, 24: 1124.8}),
+    (128, 512, 4096, {1: 243.1, 2: 254.6, 3: 257.5, 4: 259.9, 5: 263.2, 6: 266.4, 8: 273.0, 12: 286.2}),
+    (128, 768, 8192, {1: 711.7, 2: 716.6, 3: 718.9, 4: 722.1, 5: 727.9, 6: 731.2, 8: 744.4, 12: 761.8}),
+]
+
+
+@pytest.mark.parametrize("d,blocks,n,times", MEASURED)
+def test_number_of_runs_is_near_the_best_measured_one(api, d, blocks, n, times):
+    assert times[api.fake_splits(blocks, n, d, 256)] <= 1.025 * min(times.values())
