@@ -4,8 +4,8 @@
 // with one set per head.
 //
 // A workgroup = one query block of 32 * NW rows, 32 per wave.  Tiles of 32 gathered rows go straight from
-// global memory into one of three LDS slots per operand (direct-to-LDS loads, issued two iterations ahead
-// of their use), online softmax against a lazily raised reference.  Same MFMA orientation as the main
+// global memory into one of three LDS slots per operand (two for V in one form; direct-to-LDS loads, issued two
+// iterations ahead of their use), online softmax against a lazily raised reference.  Same MFMA orientation as the main
 // kernel: S^T = K_tile Q^T, O^T = V^T P^T, P in registers.
 //
 // Software pipeline: iteration t issues the matrix instructions of S(t+1) = K(t+1) Q^T and of
@@ -18,11 +18,12 @@
 // What bounds it: the matrix pipe under the power limit in the steady state (32 heads of 8192 rows, D = 128, groups of
 // 128: 0.47 us per tile and CU = 1.18 PFLOP/s, against 1.29 of the main kernel; with all-zero operands 1.49), and the
 // start and end of a block, some 3 us each at keep 10%.  Against the three-step form, inputs from memory: that shape
-// 139 -> 136 us, its groups of 64 170 -> 165, of 32 271 -> 232; one set per head, 32 heads of 4096: 42.1 -> 39.7,
-// 4 heads of 8192 37.5 -> 21.4; 64K rows: groups of 128 6.69 -> 6.56 ms, 2 heads in groups of 64 1.94 -> 0.54, 32 heads in
-// groups of 32 at 32K 3.55 -> 3.08.  Groups of 64 with D = 128 over long contexts lose a little: three slots per operand leave
-// a CU three workgroups of two waves where two slots left five, 32 heads of 32K 2.15 -> 2.17 ms, of 64K 8.50 -> 8.62 (16K and
-// D = 64: 0.573 -> 0.573, 0.295 -> 0.287).  A fourth slot per operand is slower where every group gathers its own rows (145 us:
+// 139 -> 136 us, its groups of 64 159 -> 143, of 32 271 -> 232; one set per head, 32 heads of 4096: 42.1 -> 39.7,
+// 4 heads of 8192 37.5 -> 21.4; 64K rows: groups of 128 6.69 -> 6.56 ms, 2 heads in groups of 64 1.98 -> 0.47, 32 heads in
+// groups of 32 at 32K 3.55 -> 3.08.  Groups of 64 with D = 128 have two V slots: with three a CU holds three workgroups
+// of two waves, which was slower than the three-step form at 8 heads of 8192 and over long contexts; with two it holds four.
+// 8 heads of 8192 rows three-step form / three V slots / two 40.6 / 47.1 / 37.7 us, 32 heads of 16K 579 / 582 / 528,
+// of 64K 8.60 / 8.69 / 7.63 ms.  A fourth slot per operand is slower where every group gathers its own rows (145 us:
 // more requests in flight, fewer of them served by the L2), and no faster elsewhere.
 //
 // Start and end of a query block: a workgroup works through a list of blocks, and requests what the next block needs
@@ -264,7 +265,11 @@ attn_bf16_group_kernel(AttnParams p) {
     constexpr int TILE_BYTES = W::TILE_BYTES;
     constexpr int RPC = W::RPC;
     constexpr int CH = W::CH;
-    constexpr int TEAM_BYTES = 2 * NBUF * TILE_BYTES;    // K slots, then V slots
+    // V slots: one fewer for the two-wave block at D = 128, whose V tiles are then requested one iteration ahead of their
+    // use: 40 KB of slots leave a CU four workgroups, 48 KB three.
+    constexpr int NBUF_V = NW == 2 && D == 128 ? 2 : NBUF;
+    constexpr bool LATE_V = NBUF_V == 2;
+    constexpr int TEAM_BYTES = (NBUF + NBUF_V) * TILE_BYTES;    // K slots, then V slots
     // Several blocks per workgroup, the next one's start under the end of the running one: for the 128-row block, two
     // workgroups to a CU.  (Smaller ones come three to a CU and cover each other, and have no registers for it.)
     constexpr bool LIST = KS == 1 && NW == 4;
@@ -386,6 +391,7 @@ attn_bf16_group_kernel(AttnParams p) {
         return slot * TILE_BYTES + wave * OWN;
     };
     static_assert(NW <= NBUF + 1, "K slots and one V slot");
+    static_assert(!LATE_V || (NW <= 2 && !LIST && KS == 1), "Q and O pass through two slots of an operand");
     // Q rows of a block: CH loads per part, RPC rows each, piece (lane % PIECES) ^ swizzle(row) of a row
     auto request_q = [&](const Block& k, int vslot) {
         const int lane = fresh_lane(), lrow = lane / PIECES;
@@ -431,7 +437,8 @@ attn_bf16_group_kernel(AttnParams p) {
             w.vaddr[db] = v0 + (uint32_t)(row0 * ROW_BYTES + inpiece + (((db * 4 + colpiece) ^ swizzle_v<PIECES>(row0)) << 4));
     }
     // ---- Loads.  Iteration t reads K(t+1) and V(t-1) and issues K(t+3) and V(t+1), which replace K(t) and V(t-2),
-    // both read in iteration t-1.  rows_a .. rows_d: row numbers of the tiles t+1 .. t+4 (V of t+1 now, K of t+3 now).
+    // both read in iteration t-1 (two V slots: V(t) and K(t+3); V(t) replaces V(t-2)).  rows_a .. rows_d: row numbers of
+    // the tiles t+1 .. t+4 (V of t+1 now, K of t+3 now); rows_0, two V slots: of tile t.
     int rows_0[CH], rows_a[CH], rows_b[CH], rows_c[CH], rows_d[CH];
     const byte* K;
     const byte* V;
@@ -571,15 +578,15 @@ attn_bf16_group_kernel(AttnParams p) {
 
     // Iteration t, U = t % NBUF: S(t) in s -> P(t) in P, S(t+1) in s_next, P(t-1) in P_prev.  K(t+1) and V(t-1) have
     // landed in every wave once this wave's loads of the iteration before are the only ones it still may have in
-    // flight (vector memory completes in issue order, and whatever this iteration issues comes later still) and all
-    // waves have said so at the barrier.  Loads are issued for tiles past the end as well (valid rows, slots never
+    // flight (two V slots: its K loads; vector memory completes in issue order, and whatever this iteration issues comes
+    // later still) and all waves have said so at the barrier.  Loads are issued for tiles past the end as well (valid rows, slots never
     // read), so the count in flight is the same at every iteration but the first, in front of which K(2) and V(0)
-    // stand in the place of two iterations' loads.
-    auto iterate = [&](auto u_c, auto qk_c, auto pv_c, int t, f32x16& s, f32x16& s_next, u32x4 (&P_prev)[2], u32x4 (&P)[2]) {
-        constexpr int U = decltype(u_c)::value;
+    // stand in the place of two iterations' loads.  E = (t - 1) % 2, the slot of V(t-1) where there are two.
+    auto iterate = [&](auto u_c, auto e_c, auto qk_c, auto pv_c, int t, f32x16& s, f32x16& s_next, u32x4 (&P_prev)[2], u32x4 (&P)[2]) {
+        constexpr int U = decltype(u_c)::value, E = decltype(e_c)::value;
         constexpr bool QK = decltype(qk_c)::value, PV = decltype(pv_c)::value;
-        constexpr int KOFF = (U + 1) % NBUF * TILE_BYTES, VOFF = (U + 2) % NBUF * TILE_BYTES;
-        wait_vmcnt_at_most<2 * CH>();
+        constexpr int KOFF = (U + 1) % NBUF * TILE_BYTES, VOFF = (LATE_V ? E : (U + 2) % NBUF) * TILE_BYTES;
+        wait_vmcnt_at_most<(LATE_V && PV ? 1 : 2) * CH>();
         memory_order_point();
         __builtin_amdgcn_s_barrier();
         memory_order_point();
@@ -588,39 +595,47 @@ attn_bf16_group_kernel(AttnParams p) {
         w.template request_first<QK, PV, KOFF, VOFF>(fr);
         memory_order_point();
         if constexpr (!QK) begin_next((t + 1) % NBUF);
+        if constexpr (!QK && LATE_V) {
+            issue_tile<CH>(lds_v + (t & 1) * TILE_BYTES, V, rows_0, voff, row_bytes, wave);             // V(t), the last one
+            memory_order_point();
+        }
         if constexpr (QK) {
             // (in front of this iteration's loads, so that the next iteration's wait covers the row numbers)
             load_rows(cur, t + 4, rows_d);
             memory_order_point();
+            // (V(0) of two slots went out in front of the first iteration)
+            if constexpr (LATE_V && PV) issue_tile<CH>(lds_v + (1 - E) * TILE_BYTES, V, rows_0, voff, row_bytes, wave);        // V(t)
             issue_tile<CH>(lds_k + U * TILE_BYTES, K, rows_c, koff, row_bytes, wave);                   // K(t+3)
-            issue_tile<CH>(lds_v + (U + 1) % NBUF * TILE_BYTES, V, rows_a, voff, row_bytes, wave);      // V(t+1)
+            if constexpr (!LATE_V) issue_tile<CH>(lds_v + (U + 1) % NBUF * TILE_BYTES, V, rows_a, voff, row_bytes, wave);      // V(t+1)
             memory_order_point();
         }
         w.template slots<QK, PV, true, KOFF, VOFF>(fr, s, s_next, P_prev, P, sm, std::make_integer_sequence<int, W::template count<QK, PV>()>{});
         w.close_tile(s, P, sm);
         if constexpr (QK) {
 #pragma unroll
-            for (int i = 0; i < CH; ++i) { rows_a[i] = rows_b[i]; rows_b[i] = rows_c[i]; rows_c[i] = rows_d[i]; }
+            for (int i = 0; i < CH; ++i) { if (LATE_V) rows_0[i] = rows_a[i]; rows_a[i] = rows_b[i]; rows_b[i] = rows_c[i]; rows_c[i] = rows_d[i]; }
         }
     };
     using Yes = std::true_type;
     using No = std::false_type;
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, 1>;
     if (last > 0) {
-        iterate(std::integral_constant<int, 0>{}, Yes{}, No{}, 0, sa, sb, pb, pa);
+        iterate(std::integral_constant<int, 0>{}, Odd{}, Yes{}, No{}, 0, sa, sb, pb, pa);
         if (last == 1) mask_tail(1, sb);
         for (int t = 1; t < last; t += 6) {
             // six iterations: the slots repeat after three, the roles of the registers after two
-            iterate(std::integral_constant<int, 1>{}, Yes{}, Yes{}, t, sb, sa, pa, pb);
+            iterate(std::integral_constant<int, 1>{}, Even{}, Yes{}, Yes{}, t, sb, sa, pa, pb);
             if (t + 1 >= last) break;
-            iterate(std::integral_constant<int, 2>{}, Yes{}, Yes{}, t + 1, sa, sb, pb, pa);
+            iterate(std::integral_constant<int, 2>{}, Odd{}, Yes{}, Yes{}, t + 1, sa, sb, pb, pa);
             if (t + 2 >= last) break;
-            iterate(std::integral_constant<int, 0>{}, Yes{}, Yes{}, t + 2, sb, sa, pa, pb);
+            iterate(std::integral_constant<int, 0>{}, Even{}, Yes{}, Yes{}, t + 2, sb, sa, pa, pb);
             if (t + 3 >= last) break;
-            iterate(std::integral_constant<int, 1>{}, Yes{}, Yes{}, t + 3, sa, sb, pb, pa);
+            iterate(std::integral_constant<int, 1>{}, Odd{}, Yes{}, Yes{}, t + 3, sa, sb, pb, pa);
             if (t + 4 >= last) break;
-            iterate(std::integral_constant<int, 2>{}, Yes{}, Yes{}, t + 4, sb, sa, pa, pb);
+            iterate(std::integral_constant<int, 2>{}, Even{}, Yes{}, Yes{}, t + 4, sb, sa, pa, pb);
             if (t + 5 >= last) break;
-            iterate(std::integral_constant<int, 0>{}, Yes{}, Yes{}, t + 5, sa, sb, pb, pa);
+            iterate(std::integral_constant<int, 0>{}, Odd{}, Yes{}, Yes{}, t + 5, sa, sb, pb, pa);
         }
         // ---- the last tile: S in sa, the tile before's P in pb, whichever iteration the loop ended with
         if (last & 1) {
@@ -631,10 +646,10 @@ attn_bf16_group_kernel(AttnParams p) {
         if (last > 1) mask_tail(last, sa);
         // slot 0 of the addresses becomes the slot of V(last - 1) as iteration 2 of an unrolled run reads it
 #pragma unroll
-        for (int db = 0; db < DB; ++db) w.vaddr[db] += (uint32_t)((last - 1) % NBUF) * TILE_BYTES;
-        iterate(std::integral_constant<int, 1>{}, No{}, Yes{}, last, sa, sb, pb, pa);
+        for (int db = 0; db < DB; ++db) w.vaddr[db] += (uint32_t)((last - 1) % NBUF_V) * TILE_BYTES;
+        iterate(std::integral_constant<int, 1>{}, Even{}, No{}, Yes{}, last, sa, sb, pb, pa);
 #pragma unroll
-        for (int db = 0; db < DB; ++db) w.vaddr[db] += (uint32_t)(last % NBUF - (last - 1) % NBUF) * TILE_BYTES;
+        for (int db = 0; db < DB; ++db) w.vaddr[db] += (uint32_t)(last % NBUF_V - (last - 1) % NBUF_V) * TILE_BYTES;
     } else {
         __builtin_amdgcn_s_barrier();                       // every wave has read K(0)
         memory_order_point();
@@ -655,7 +670,7 @@ attn_bf16_group_kernel(AttnParams p) {
     w.template slots<false, true, false, 0, 0>(fr, sa, sb, pa, pb, sm, std::make_integer_sequence<int, W::NPV>{});
 
 #pragma unroll
-    for (int db = 0; db < DB; ++db) w.vaddr[db] -= (uint32_t)(last % NBUF) * TILE_BYTES;       // the next block starts from slot 0 again
+    for (int db = 0; db < DB; ++db) w.vaddr[db] -= (uint32_t)(last % NBUF_V) * TILE_BYTES;       // the next block starts from slot 0 again
 
     // ---- epilogue: O = diag(l)^-1 acc; hand-over to the next block
     const int vslot = (last + 1) % NBUF;

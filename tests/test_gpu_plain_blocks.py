@@ -77,3 +77,23 @@ def test_two_teams_form_the_weights_that_one_team_forms(H, n, d, k, copies):
             torch.cuda.synchronize()
         outs.append(f64(O[0, :H]))
     assert np.linalg.norm(outs[0] - outs[1]) <= 5e-4 * np.linalg.norm(outs[1])
+
+
+@pytest.mark.parametrize("k", [1, 20, 33, 70, 100, 129, 170, 200, 230, 300])         # 1 to 10 tiles
+@pytest.mark.parametrize("d", [128, 64])
+def test_two_wave_blocks(d, k):
+    """Groups of 64 rows: at D = 128 two V slots instead of three, every tile count up to the second round of the unrolled
+    iterations, a ragged last group."""
+    H, n, G = 2, 333, 64
+    print(f"two-wave blocks d={d} k={k}", flush=True)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(d + k)
+    Q, K, V = (torch.randn(1, H, n, d, generator=g).to(torch.bfloat16) for _ in range(3))
+    U = -(-n // G)
+    idx = random_idx(n, k, H * U, seed=k).view(1, H, U, k)
+    with pc.Context(1, H, n, d, torch.bfloat16, group_size=G) as ctx:
+        O = ctx.attn(Q.to(DEV), K.to(DEV), V.to(DEV), idx.to(DEV))
+        torch.cuda.synchronize()
+    for h in range(H):
+        want = oracle.sparse_attention_masked(f64(Q[0, h]), f64(K[0, h]), f64(V[0, h]), idx[0, h].numpy(), group_size=G)
+        assert_close(O[0, h], want, "bf16", f"d={d} k={k} h={h}")
