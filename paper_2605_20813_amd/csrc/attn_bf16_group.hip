@@ -47,6 +47,7 @@ typedef unsigned char byte;
 constexpr int BN = 32;      // gathered rows per tile
 constexpr int NBUF = 3;     // LDS tile slots per operand: one being read, two on their way
 constexpr float kGrowthLimit = 256.0f;      // 2^kTau with kTau = 8, as in the main kernel
+constexpr float kNoReference = -1e30f;      // of a query whose first tile holds no finite logit: the tile adds nothing
 
 // s_waitcnt vmcnt(v) with the other counters left alone (gfx9 encoding: vmcnt in [3:0] and [15:14])
 template <int v>
@@ -236,7 +237,7 @@ struct GroupWave {
             if (m2 > ref + 1.0f) {
                 const float steps = ceilf(m2 - ref);
                 const float alpha = fast_exp2(-steps);
-                ref += steps;
+                ref = ref == kNoReference ? m2 : ref + steps;         // (no finite logit so far: alpha is zero)
                 l_run *= alpha;
                 mfma_settle(o_acc);
 #pragma unroll
@@ -564,7 +565,7 @@ attn_bf16_group_kernel(AttnParams p) {
         float mx = sa[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sa[r]);
-        w.ref = fmaxf(half_max(mx) * w.c2, -1e30f);
+        w.ref = fmaxf(half_max(mx) * w.c2, kNoReference);
     }
     // Two teams: both weigh against the reference that team 0 takes from the block's first tile, handed over behind the
     // next barrier.  A weight then has the same bits whichever team forms it, in this form of the kernel or in the one

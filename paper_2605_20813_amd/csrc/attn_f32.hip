@@ -279,7 +279,8 @@ __global__ void __launch_bounds__(64 * KS) attn_f32_split_kernel(AttnParams p) {
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
         mx = half_max(mx);
-        const float m_new = fmaxf(m_run, mx);
+        // (the bound: a tile without a finite logit, the first one of this wave, leaves the reference finite and adds nothing)
+        const float m_new = fmaxf(fmaxf(m_run, mx), -1e30f);
         const float alpha = exp2f((m_run - m_new) * c2);
         const float mc = m_new * c2;
         m_run = m_new;

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_2605_20813_amd import pulsecol as pc
-from parity_util import f64
+from parity_util import assert_close, f64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -84,3 +84,55 @@ def test_error_of_long_sums():
     rms = (sum(err) / len(err)) ** 0.5
     print("rms", rms)
     assert rms < 6e-8
+
+
+def one_component(k0, n, d, dtype):
+    Q, K = torch.zeros(1, 1, n, d), torch.zeros(1, 1, n, d)
+    Q[..., 0] = 1.0
+    K[0, 0, :, 0] = torch.as_tensor(k0, dtype=torch.float32)
+    g = torch.Generator(device="cpu")
+    g.manual_seed(n)
+    return Q.to(dtype), K.to(dtype), torch.randn(1, 1, n, d, generator=g).to(dtype)
+
+
+# (the 32-row fp32 kernels: wave w takes the tiles w, w + 4 or w + 8, ...)
+@pytest.mark.parametrize("first,last", [(32, 64), (0, 32), (64, 200), (224, 256), (0, 290)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_keys_without_a_finite_logit(d, first, last):
+    n = 300
+    print(f"f32 -inf logits d={d} {first}..{last}", flush=True)
+    k0 = np.random.default_rng(first).normal(size=n) * np.sqrt(d)
+    k0[first:last] = -np.inf
+    Q, K, V = one_component(k0, n, d, torch.float32)
+    z = f64(K[0, 0, :, 0]) / np.sqrt(d)
+    w = np.exp(z - z.max())
+    w /= w.sum()
+    with pc.Context(1, 1, n, d, torch.float32) as ctx:
+        q, k, v = Q.to(DEV), K.to(DEV), V.to(DEV)
+        sc = f64(ctx.scores(q, k))[0, 0, 0]
+        idx = torch.arange(n, dtype=torch.int32, device=DEV).view(1, 1, 1, n)
+        outs = [ctx.attn(q, k, v, idx), ctx.attn_dense(q, k, v)]
+    assert np.abs(sc - w).max() < 1e-5 * w.max()
+    for O in outs:
+        assert np.abs(f64(O[0, 0]) - w @ f64(V[0, 0])).max() < 1e-4
+
+
+@pytest.mark.parametrize("copies", [1, 130])                 # two teams, one team
+@pytest.mark.parametrize("G", [0, 32, 64, 128])
+def test_first_tile_without_a_finite_logit(G, copies):
+    """The plain bf16 attention kernel: the first 32 columns' logits are -inf, what follows lies beyond 2^127 as weights against zero."""
+    n, d, k = 256, 128, 160
+    print(f"-inf first tile G={G} copies={copies}", flush=True)
+    k0 = np.full(n, -np.inf)
+    k0[32:k] = (200.0 + np.random.default_rng(G).uniform(-3.0, 3.0, k - 32)) * np.sqrt(d)
+    Q, K, V = one_component(k0, n, d, torch.bfloat16)
+    z = f64(K[0, 0, :k, 0]) / np.sqrt(d)
+    w = np.exp(z - z.max())
+    w /= w.sum()
+    with pc.Context(1, copies, n, d, torch.bfloat16, group_size=G) as ctx:
+        ctx.set_attn_block(128)
+        idx = torch.arange(k, dtype=torch.int32, device=DEV).expand(1, copies, ctx.groups, k).contiguous()
+        O = ctx.attn(*(t.to(DEV).repeat(1, copies, 1, 1).contiguous() for t in (Q, K, V)), idx)
+    want = np.broadcast_to(w @ f64(V[0, 0, :k]), (n, d))
+    assert_close(O[0, 0], want, "bf16", "first head")
+    assert_close(O[0, -1], want, "bf16", "last head")
