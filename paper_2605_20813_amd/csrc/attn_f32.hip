@@ -344,18 +344,9 @@ __global__ void __launch_bounds__(64 * KS) attn_f32_split_kernel(AttnParams p) {
 template <int D, int MODE>
 hipError_t launch(const AttnParams& p, hipStream_t s) {
     const int64_t heads = (int64_t)p.batch * p.heads;
-    // Where workgroups of 128 rows leave CUs idle: 32-row workgroups, with eight waves to share the tiles where every CU
-    // has room for all of them at once.  The line: with 128 columns of V one split workgroup fills a CU, and a round of
-    // them costs 0.36 (gathered) or 0.27 (dense) of a 128-row workgroup's time -- two or three rounds; the lighter ones
-    // win up to a 128-row workgroup per CU, the gathered one with 64 columns up to seven eighths of that.
-    // Before / after, keep 20%: 2 heads of 256, D = 64, dense 26.0 / 10.6 us; 8 of 1500, D = 128, sparse 57.5 / 41.6,
-    // dense 221 / 123; 3 of 8000, D = 64, sparse 246 / 97; beyond the line, 10 of 2048, D = 128, sparse: 73 / 77.
-    const int64_t blocks = (int64_t)((p.n + 31) / 32) * heads, wide_blocks = (int64_t)((p.n + BM - 1) / BM) * heads;
-    const int64_t cus = compute_units();
-    const bool split = MODE == kLseOnly ? wide_blocks < cus
-                     : D == 128         ? blocks <= (MODE == kSparse ? 2 : 3) * cus
-                                        : (MODE == kSparse ? 8 * wide_blocks <= 7 * cus : wide_blocks < cus);
-    if (split) {
+    if (block_rows_f32((AttnMode)MODE, D, p.n, heads, compute_units()) == 32) {
+        // (eight waves to share the tiles where every CU has room for all workgroups at once)
+        const int64_t blocks = (int64_t)((p.n + 31) / 32) * heads;
         constexpr int MANY = D == 128 && MODE != kLseOnly ? 4 : 8;          // (eight waves have no registers for 128 columns of V)
         const dim3 grid = head_grid(heads, (p.n + 31) / 32);
         if (blocks <= compute_units()) hipLaunchKernelGGL((attn_f32_split_kernel<D, MODE, MANY>), grid, dim3(64 * MANY), 0, s, p);

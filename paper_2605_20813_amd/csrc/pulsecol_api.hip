@@ -219,7 +219,9 @@ pulsecol::AttnParams attn_params(pulsecol_ctx* c, const void* Q, const void* K, 
 //   D = 64   scheduled 37 + R (2.9 + 0.95 t)   plain 4 + R (1.9 + 1.15 t)
 // D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.9 / 68.1 us, 8K 120 / 133, 16K 437 / 387.
 int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
-    if (c->shape.dtype != PULSECOL_BF16) return pulsecol::kBlockM_f32;
+    if (c->shape.dtype != PULSECOL_BF16)
+        return pulsecol::block_rows_f32(pulsecol::kSparse, c->shape.head_dim, c->shape.seq, (int64_t)c->shape.batch * c->shape.heads,
+                                        pulsecol::compute_units());
     if (c->groups == 1) {
         if (c->attn_block != 0) return c->attn_block;
         const double blocks = (double)((c->shape.seq + 255) / 256) * c->shape.batch * c->shape.heads;
@@ -719,6 +721,8 @@ pulsecol_status pulsecol_attn_tile_shape(const pulsecol_ctx* ctx, int32_t k, int
     if (!ctx || !block_m || !block_n) return fail(nullptr, PULSECOL_ERR_INVALID_ARG, "pulsecol_attn_tile_shape: NULL pointer");
     if (k < 1 || k > ctx->shape.seq) return fail(nullptr, PULSECOL_ERR_INVALID_ARG, "pulsecol_attn_tile_shape: need 1 <= k <= seq");
     const bool bf = ctx->shape.dtype == PULSECOL_BF16;
+    DeviceGuard guard(ctx->device);               // the rules count the compute units of the context's device
+    if (guard.err != hipSuccess) return fail_hip(nullptr, guard.err, "pulsecol_attn_tile_shape: hipSetDevice");
     *block_m = sparse_block_m(ctx, k);
     *block_n = !bf ? pulsecol::kBlockN_f32 : (*block_m < pulsecol::kBlockM_bf16 ? 32 : pulsecol::kBlockN_bf16);
     return PULSECOL_OK;

@@ -89,6 +89,19 @@ constexpr int kBlockN_bf16 = 64;    // gathered columns per tile
 constexpr int kBlockM_f32 = 128;    // 4 waves x 32
 constexpr int kBlockN_f32 = 32;
 
+// fp32 attention kernels: query rows per workgroup, 32 where workgroups of 128 leave CUs idle.  The line: with 128 columns
+// of V one 32-row workgroup fills a CU, and a round of them costs 0.36 (gathered) or 0.27 (dense) of a 128-row workgroup's
+// time -- two or three rounds; the lighter ones win up to a 128-row workgroup per CU, the gathered one with 64 columns up to
+// seven eighths of that.  Before / after, keep 20%: 2 heads of 256, D = 64, dense 26.0 / 10.6 us; 8 of 1500, D = 128, sparse
+// 57.5 / 41.6, dense 221 / 123; 3 of 8000, D = 64, sparse 246 / 97; beyond the line, 10 of 2048, D = 128, sparse: 73 / 77.
+inline int block_rows_f32(AttnMode mode, int head_dim, int n, int64_t heads, int compute_units) {
+    const int64_t blocks = (int64_t)((n + 31) / 32) * heads, wide = (int64_t)((n + kBlockM_f32 - 1) / kBlockM_f32) * heads, cus = compute_units;
+    const bool split = mode == kLseOnly  ? wide < cus
+                     : head_dim == 128   ? blocks <= (mode == kSparse ? 2 : 3) * cus
+                     : (mode == kSparse) ? 8 * wide <= 7 * cus : wide < cus;
+    return split ? 32 : kBlockM_f32;
+}
+
 // grid of a kernel that places its workgroups with head_and_block
 inline dim3 head_grid(int64_t heads, int per_head) {
     const unsigned layers = (unsigned)((heads + 7) / 8);

@@ -113,3 +113,19 @@ MEASURED = [
 @pytest.mark.parametrize("d,blocks,n,times", MEASURED)
 def test_number_of_runs_is_near_the_best_measured_one(api, d, blocks, n, times):
     assert times[api.fake_splits(blocks, n, d, 256)] <= 1.025 * min(times.values())
+
+
+@pytest.mark.parametrize("device,heads,n,d,want", [
+    (MANY, 2, 256, 64, 32), (MANY, 8, 1500, 128, 32), (MANY, 8, 2048, 128, 32), (MANY, 9, 2048, 128, 128),
+    (MANY, 14, 2048, 64, 32), (MANY, 15, 2048, 64, 128), (FEW, 2, 2048, 128, 32), (FEW, 3, 2048, 128, 128),
+])
+def test_tile_shape_of_f32_calls(api, device, heads, n, d, want):
+    """The rows of the kernel that runs, by the compute units of the context's device, whichever is current."""
+    ctx = Ctx(api, device, 1, heads, n, d, torch.float32)
+    for current in (FEW, MANY):
+        api.fake_set_device(current)
+        m, k = ctypes.c_int32(), ctypes.c_int32()
+        assert api.pulsecol_attn_tile_shape(ctx.h, 100, ctypes.byref(m), ctypes.byref(k)) == pc.OK
+        assert (m.value, k.value) == (want, 32)
+        assert api.fake_device() == current
+    ctx.close()
