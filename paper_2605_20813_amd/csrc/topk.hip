@@ -213,7 +213,8 @@ constexpr uint32_t TKR_HALF_WIDTH_MIN = 1u << 12, TKR_HALF_WIDTH_MAX = 1u << 22;
 
 // ODD: rows whose length or alignment is not a multiple of 16 bytes.  Their loads are 16 bytes at 4-byte alignment, the
 // one that would reach behind the row is pulled back to end with it and its elements moved up when the row's turn comes;
-// the registers that are left over hold the key 0, below every score's.  632 rows of 5003 elements: 87 us in the streaming
+// the registers that are left over hold the key 0, below every score's (and equal to that of the NaN with all bits set,
+// behind which they come in index order).  632 rows of 5003 elements: 87 us in the streaming
 // kernel, 28 here.
 // COPY: the result goes to a second place as well (select keeps the pattern; a copy of 32 sets of 409 columns took 2 us
 // in a launch of its own, of 632 sets of 500 5 us).
@@ -425,16 +426,31 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
     }
 
     if (!bracketed) {
+        // What the row's last 16 bytes hold beside its elements (in one register group of one lane, told by its place: any
+        // key may be an element's): first the group's first element, so that the extremes are those of the elements, then
+        // the row's smallest key.  It follows every element in index order, so the selection (k_row <= n of them) never
+        // reaches it.
+        auto fill_behind_the_end = [&](bool smallest, uint32_t kmin) {
+#pragma unroll
+            for (int i = 0; i < V4; ++i) {
+                const int behind = first_r + i * 256 + 4 - n;
+                if (behind > 0 && behind < 4) {
+                    const uint32_t fill = smallest ? kmin : key[i][0];
+                    key[i][3] = fill;
+                    key[i][2] = behind >= 2 ? fill : key[i][2];
+                    key[i][1] = behind == 3 ? fill : key[i][1];
+                }
+            }
+        };
+        if (straddles) fill_behind_the_end(false, 0u);
         uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
 #pragma unroll
         for (int i = 0; i < V4; ++i) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (i < nv && (!VARLEN || !straddles || first_r + i * 256 + c < n)) {
+                if (i < nv) {
                     kmax = key[i][c] > kmax ? key[i][c] : kmax;
-                    // (odd rows: the key 0 of a register without an element becomes the largest number)
-                    const uint32_t low = ODD && !VARLEN ? key[i][c] - 1u : key[i][c];
-                    kmin = low < kmin ? low : kmin;
+                    kmin = key[i][c] < kmin ? key[i][c] : kmin;
                 }
             }
         }
@@ -448,17 +464,7 @@ __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int
             kmin = wave_b[w] < kmin ? wave_b[w] : kmin;
         }
         __syncthreads();                                   // wave_a / wave_b are reused below
-        if (ODD && !VARLEN) kmin += 1u;
-        if (straddles) {
-            // what the row's last 16 bytes hold beside its elements takes the row's smallest key: it
-            // follows every real element in index order, so the selection (k_row <= n real elements) never reaches it
-#pragma unroll
-            for (int i = 0; i < V4; ++i) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (VARLEN ? (i < nv && first_r + i * 256 + c >= n) : key[i][c] == 0u) key[i][c] = kmin;
-            }
-        }
+        if (straddles) fill_behind_the_end(true, kmin);
         // Bits above `hi` are the same in every key of the row.
         hi = 31 - __clz((int)(kmax ^ kmin));           // -1 if all keys are equal
         prefix = hi >= 31 ? 0u : ((kmax >> (hi + 1)) << (hi + 1));

@@ -69,3 +69,26 @@ def test_select_in_a_ragged_batch_of_odd_length(G):
                     assert (got[b, h, u, kb:] == -1).all()
                 else:
                     assert (got[b, h, u] == -1).all()
+
+
+@pytest.mark.parametrize("rows,n,k,offset", [(3, 5, 4, 0), (4, 1021, 1000, 0), (4, 1024, 1000, 1), (300, 5003, 500, 0), (300, 5004, 5000, 1),
+                                             (3, 32771, 32770, 0)])
+def test_odd_rows_with_every_bit_pattern(rows, n, k, offset):
+    """Scores of any bits, the NaN with all bits set among them (the smallest key there is): kept by key, the lower index first.  The
+    first pass over a row counts digits without a test, so its bounds have to be those of the elements."""
+    print(f"topk any bits rows={rows} n={n} k={k} offset={offset}", flush=True)
+    rng = np.random.default_rng(n + k)
+    bits = rng.uniform(0.5, 0.5001, (rows, n)).astype(np.float32).view(np.uint32)          # one exponent: few digits differ
+    lots = rng.random((rows, n)) < 0.02
+    bits[lots] = rng.integers(0, 2**32, int(lots.sum()), dtype=np.uint64).astype(np.uint32)
+    bits[:, [n // 2, n - 1]] = 0xFFFFFFFF
+    bits[::3, 0] = 0xFFFFFFFF
+    buf = torch.zeros(rows * n + offset, dtype=torch.int32, device=DEV)
+    buf[offset:] = torch.from_numpy(bits.view(np.int32).reshape(-1)).to(DEV)
+    scores = buf.view(torch.float32)[offset:].view(1, rows, 1, n)
+    with pc.Context(1, rows, n, 64, torch.bfloat16) as ctx:
+        idx = ctx.topk(scores, k)
+        torch.cuda.synchronize()
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(0x80000000)).astype(np.int64)
+    want = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1)
+    assert np.array_equal(idx.cpu().numpy().reshape(rows, k), want)
