@@ -437,13 +437,12 @@ pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens
     DeviceGuard guard(ctx->device);
     if (guard.err != hipSuccess) return fail_hip(ctx, guard.err, "pulsecol_set_seq_lens: hipSetDevice");
     // The lengths travel inside launch arguments, 64 at a time: nothing is read from the caller's array
-    // after this call returns, and nothing synchronises.  The kept counts start at the lengths.
+    // after this call returns, and nothing synchronises.  (The kept counts are formed by the calls that read them.)
     for (int32_t first = 0; first < B; first += 64) {
         pulsecol::VarlenChunk chunk{};
         const int32_t count = B - first < 64 ? B - first : 64;
         for (int32_t i = 0; i < count; ++i) chunk.v[i] = seq_lens[first + i];
-        hipError_t e = pulsecol::launch_varlen_store(ctx->varlen, first, count, chunk, (hipStream_t)stream);
-        if (e == hipSuccess) e = pulsecol::launch_varlen_store(ctx->varlen, B + first, count, chunk, (hipStream_t)stream);
+        const hipError_t e = pulsecol::launch_varlen_store(ctx->varlen, first, count, chunk, (hipStream_t)stream);
         if (e != hipSuccess) { ctx->varlen_on = false; return fail_hip(ctx, e, "pulsecol_set_seq_lens: storing the lengths"); }
     }
     ctx->varlen_on = true;

@@ -10,7 +10,7 @@ namespace {
 int current = 0;
 const int kUnits[2] = {64, 256};
 std::map<char*, size_t> blocks;
-int row_splits = 0, outside = 0, allocations = 0;
+int row_splits = 0, outside = 0, length_stores = 0;
 
 // counts accesses [p, p + bytes) that no allocation holds
 void touch(const void* p, size_t bytes) {
@@ -22,7 +22,7 @@ void touch(const void* p, size_t bytes) {
 }
 }  // namespace
 
-hipError_t hipMalloc(void** p, size_t bytes) { *p = std::malloc(bytes); blocks[(char*)*p] = bytes; ++allocations; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t bytes) { *p = std::malloc(bytes); blocks[(char*)*p] = bytes; return hipSuccess; }
 hipError_t hipFree(void* p) { blocks.erase((char*)p); std::free(p); return hipSuccess; }
 hipError_t hipMemset(void* p, int value, size_t bytes) { std::memset(p, value, bytes); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind, hipStream_t) { std::memcpy(to, from, bytes); return hipSuccess; }
@@ -38,6 +38,7 @@ extern "C" {
 int fake_row_splits() { return row_splits; }
 int fake_outside() { return outside; }
 int fake_device() { return current; }
+int fake_length_stores() { return length_stores; }
 void fake_set_device(int d) { current = d; }
 int fake_splits(int blocks, int longest, int head_dim, int units) { return pulsecol::score_splits(blocks, longest, head_dim, units); }
 int fake_segments(int n) { return pulsecol::ScoreSegments(n).count; }
@@ -66,6 +67,10 @@ hipError_t launch_attn_f32(const AttnParams&, int, AttnMode, hipStream_t) { retu
 hipError_t launch_topk(const TopkParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_block_sums(const float*, float*, int32_t, int32_t, int64_t, int32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_index_range_check(const int32_t*, int64_t, int32_t, int32_t*, const int32_t*, int32_t, int64_t, int32_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_varlen_store(int32_t*, int32_t, int32_t, const VarlenChunk&, hipStream_t) { return hipSuccess; }
+hipError_t launch_varlen_store(int32_t* varlen, int32_t first, int32_t count, const VarlenChunk&, hipStream_t) {
+    ++length_stores;
+    touch(varlen + first, (size_t)count * 4);
+    return hipSuccess;
+}
 hipError_t launch_varlen_kept_from_idx(int32_t*, int32_t, const int32_t*, int64_t, int32_t, hipStream_t) { return hipSuccess; }
 }  // namespace pulsecol

@@ -129,3 +129,13 @@ def test_tile_shape_of_f32_calls(api, device, heads, n, d, want):
         assert (m.value, k.value) == (want, 32)
         assert api.fake_device() == current
     ctx.close()
+
+
+@pytest.mark.parametrize("batch", [1, 64, 65, 200])
+def test_one_launch_stores_64_lengths(api, batch):
+    ctx = Ctx(api, FEW, batch, 1, 128, 64, torch.bfloat16)
+    stores, outside = api.fake_length_stores(), api.fake_outside()
+    assert ctx.set_seq_lens([100] * batch) == pc.OK
+    assert api.fake_length_stores() - stores == -(-batch // 64)
+    assert api.fake_outside() == outside
+    ctx.close()
