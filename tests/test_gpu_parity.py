@@ -241,11 +241,11 @@ def test_topk_is_bit_exact_on_identical_scores(rows, n, k, ties):
     assert np.array_equal(idx.cpu().numpy().reshape(rows, k), want)
 
 
-@pytest.mark.parametrize("n", [4096, 5001])
+@pytest.mark.parametrize("n", [4096, 5001, 65541])
 def test_topk_orders_signs_magnitudes_and_narrow_ranges(n):
     """Rows whose keys differ in the sign bit, in the exponent, or only in the last mantissa bits
-    (the radix select starts at the highest bit that differs inside the row); n = 5001 takes the
-    streaming kernel, n = 4096 the register-resident one."""
+    (the radix select starts at the highest bit that differs inside the row); n = 4096 and 5001 take the
+    register-resident kernel, aligned and not, n = 65541 the streaming one."""
     say(f"topk value ranges n={n}")
     g = torch.Generator().manual_seed(n)
     s = torch.empty(6, n)

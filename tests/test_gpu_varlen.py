@@ -111,7 +111,7 @@ def test_every_batch_element_matches_the_oracle_at_its_own_length(B, H, n, d, dt
 
 @pytest.mark.parametrize("n,k,lens", [
     (1000, 300, (1000, 431, 10)),          # the row held in registers (n a multiple of 4), lengths that are not
-    (1003, 300, (1003, 502, 299)),         # the streaming kernel (n not a multiple of 4)
+    (1003, 300, (1003, 502, 299)),         # ... rows whose starts are not aligned to 16 bytes
     (4096, 512, (4096, 4095, 2049)),       # several register groups per lane
 ])
 def test_topk_on_given_scores_and_ties_per_element(n, k, lens):
