@@ -165,7 +165,8 @@ PULSECOL_API pulsecol_status pulsecol_select(pulsecol_ctx* ctx, const void* Q, c
  * scores_out[b, h, u, j] = (1/|G_u|) sum_{i in G_u} softmax_j(q_i . k_j * scale), fp32 [B, H, U, seq].
  * Row sums of the softmax are accumulated in fp32 in a fixed order: results are
  * bit-identical from run to run.  bf16: the scores of a head follow from its own Q, K, length and group size alone; they are the
- * same bits whatever other heads and batch elements a context holds. */
+ * same bits whatever other heads and batch elements a context holds.  f32: small grids run in kernels that share the tiles of a
+ * block out among waves, so the last bits of a sum may differ between contexts of different size. */
 PULSECOL_API pulsecol_status pulsecol_scores(pulsecol_ctx* ctx, const void* Q, const void* K, float* scores_out,
                                 void* stream);
 

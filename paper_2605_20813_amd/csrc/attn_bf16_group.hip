@@ -15,9 +15,9 @@
 // the waves that share a SIMD fall into step and each pipe idles while the other works, whatever the
 // gathers do: with every column set pointing at a single row the kernel took five sixths of its time.)
 //
-// What bounds it: the matrix pipe under the power limit in the steady state (32 heads of 8192 rows, D = 128, groups of
-// 128: 0.47 us per tile and CU = 1.18 PFLOP/s, against 1.29 of the main kernel; with all-zero operands 1.49), and the
-// start and end of a block, some 3 us each at keep 10%.  Against the three-step form, inputs from memory: that shape
+// What bounds it: the matrix pipe under the power limit (32 heads of 8192 rows, D = 128, groups of 128, whole calls: 887
+// TFLOP/s on random operands, 1150 on all-zero ones) and the start and end of a block, some 3 us each at keep 10%
+// (the four-wave form spills four registers there).  Against the three-step form, inputs from memory: that shape
 // 139 -> 136 us, its groups of 64 159 -> 143, of 32 271 -> 232; one set per head, 32 heads of 4096: 42.1 -> 39.7,
 // 4 heads of 8192 37.5 -> 21.4; 64K rows: groups of 128 6.69 -> 6.56 ms, 2 heads in groups of 64 1.98 -> 0.47, 32 heads in
 // groups of 32 at 32K 3.55 -> 3.08.  Groups of 64 with D = 128 have two V slots: with three a CU holds three workgroups

@@ -30,11 +30,11 @@
 // group boundaries, and nothing is left to add.)
 //
 // What bounds it: two weights and a matrix instruction per 32 cycles of the matrix pipe, about as much as one wave
-// can issue, and over long runs the power limit (about 1.2 PFLOP/s).  The row pass used to be a mode of the 256-row
-// attention kernel, 62 KB of straight-line code that every launch fetches anew; this one is 22 KB,
-// 6 of them the raises, out of the way.  (Checking every block for one costs 0.3% at 64K, 0.8% at 4K; the ends of segments,
-// in both passes, nothing at 64K, 1.6% at 4K.)  D = 128, 32 heads:
-// 4096 rows 172 -> 128 us, 16384 rows 1877 -> 1842 us, 65536 rows 28.8 -> 28.9 ms.
+// can issue, and over long runs the power limit (both passes, 32 heads of 8192 rows: 1.12 PFLOP/s on random operands, 1.55 on
+// all-zero ones).  The row pass used to be a mode of the 256-row attention kernel, 62 KB of straight-line code that every
+// launch fetches anew; this one is 23 KB, 6 of them the raises, out of the way.  D = 128, 32 heads of 4096 rows: row
+// pass 172 us in that form, 126 with a reference that stays and runs of free length, 133 now (the check of every block
+// 2.5, the ends of segments the rest); column pass 132.  Both passes, 16384 rows: 3.72 ms (1% of it), 65536 rows 58.4 ms (nothing).
 #include <utility>
 
 #include "pulsecol_device.h"
