@@ -86,3 +86,30 @@ def test_columns_with_and_without_a_context():
         pc.select_noalloc(pc.make_shape(1, H, n, d, torch.float32), Q, K, keep, got)
         torch.cuda.synchronize()
         assert torch.equal(got, want), keep
+
+
+@pytest.mark.parametrize("d,G,copies", [(128, 0, (4, 32, 40)), (64, 0, (4, 32, 40)), (128, 256, (4, 40))])
+def test_masses_that_underflow_in_single_segments(d, G, copies):
+    """Some columns' masses over the first 700 queries lie far below 2^-90 and are formed again with the fp32 instruction; the other
+    segments and groups keep the sums that they have in every layout."""
+    n = 3000
+    print(f"f32 score invariance, small masses d={d} G={G}", flush=True)
+    Q, K = inputs(n, d, 3)
+    Q[..., 0] = 0.0
+    Q[:, :, :700, 0] = 4.0
+    K[..., 0] = 0.0
+    K[:, :, 100:200, 0] = -82.0 * d ** 0.5 / 4.0
+    check_copies(Q, K, G, copies)
+
+
+@pytest.mark.parametrize("d,G,copies", [(128, 0, (4, 32, 40)), (64, 0, (4, 32, 40)), (128, 256, (4, 40))])
+def test_large_and_infinite_numbers(d, G, copies):
+    n = 3000
+    print(f"f32 score invariance, large and infinite numbers d={d} G={G}", flush=True)
+    Q, K = inputs(n, d, 4)
+    Q[..., 0] = Q[..., 0].abs().clamp(0.5, 1.0)
+    K[:, :, 1000:1040, 0] = -float("inf")
+    K[:, :, 2500, 0] = -3.4e38
+    K[..., 1] *= 1e-30
+    Q[:, :, 300, 1] = 1e30
+    check_copies(Q, K, G, copies)
