@@ -230,7 +230,8 @@ struct ScoreWave {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 const float top = reference_of(s[kb]);
-                if (top > ref[kb]) {
+                // (by the row's own sums, of either half-wave: not by those of the rows that share the wave, which are others in blocks of 128)
+                if (half_max(sum[kb]) > kGrowthLimit && top > ref[kb]) {
                     // (a row without a finite logit so far has nothing to scale)
                     const float down = ref[kb] == kNoReference ? 0.f : fast_exp2(ref[kb] - top);
                     acc_short[kb][0] *= down;
