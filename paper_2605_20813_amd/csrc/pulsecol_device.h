@@ -49,6 +49,9 @@ __device__ __forceinline__ float half_sum(float x) {
     return __int_as_float(r[0]) + __int_as_float(r[1]);
 }
 
+// a value that all lanes share
+__device__ __forceinline__ float in_scalar_register(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
