@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2605_20813_amd import pulsecol as pc
-from parity_util import f64
+from parity_util import f64, random_idx
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -50,3 +50,54 @@ def test_scores_of_one_large_number(which):
         sc = f64(ctx.scores(Q.to(DEV), K.to(DEV)))[0, 0, 0]
     want = oracle.column_scores(f64(Q[0, 0]), f64(K[0, 0]))[0]
     assert (np.abs(sc - want) / want).max() < 2e-6
+
+
+SHAPES = [(2, 300, 128, 77), (2, 300, 64, 77), (40, 700, 128, 225), (70, 520, 64, 129)]       # workgroups of 32 rows, of 128
+
+
+def attention(Q, K, V, idx, scale=0.0):
+    """Sparse and dense attention and the row log-sum-exp, in 64 bits: (got, wanted) of the first and the last head."""
+    _, H, n, d = Q.shape
+    k = idx.shape[1]
+    with pc.Context(1, H, n, d, torch.float32, scale=scale) as ctx:
+        q, k_, v = Q.to(DEV), K.to(DEV), V.to(DEV)
+        O = ctx.attn(q, k_, v, idx.view(1, H, 1, k).to(DEV))
+        lse = torch.empty(1, H, n, device=DEV)
+        Od = ctx.attn_dense(q, k_, v, lse_out=lse)
+        torch.cuda.synchronize()
+    factor = scale * d ** 0.5 if scale else 1.0
+    for h in sorted({0, H - 1}):
+        qh, kh, vh, cols = f64(Q[0, h]) * factor, f64(K[0, h]), f64(V[0, h]), idx[h].numpy()
+        Z = oracle.attention_logits(qh, kh)
+        top = Z.max(axis=1)
+        yield [(f64(O[0, h]), oracle.dense_attention(qh, kh[cols], vh[cols])), (f64(Od[0, h]), oracle.dense_attention(qh, kh, vh)),
+               (f64(lse[0, h])[:, None], (top + np.log(np.exp(Z - top[:, None]).sum(axis=1)))[:, None])]
+
+
+def columns_off(got, want):
+    return (np.linalg.norm(got - want, axis=0) / np.linalg.norm(want, axis=0)).max()
+
+
+# (an output hangs on fewer weights than a score: twice the bound)
+@pytest.mark.parametrize("fq,fk,fs", FACTORS)
+@pytest.mark.parametrize("H,n,d,k", SHAPES)
+def test_attention_of_scaled_queries_and_keys(H, n, d, k, fq, fk, fs):
+    print(f"f32 range attention H={H} n={n} d={d} k={k} {fq} {fk} {fs}", flush=True)
+    Q, K, V = tensors(H, n, d, n + d + k)
+    for pairs in attention(Q * fq, K * fk, V, random_idx(n, k, H, seed=n), fs / d ** 0.5):
+        for got, want in pairs:
+            assert columns_off(got, want) < 4e-6
+
+
+@pytest.mark.parametrize("H,n,d,k", SHAPES)
+def test_attention_of_one_large_key(H, n, d, k):
+    """An element of one kept key beyond the range, against queries that are small there."""
+    print(f"f32 range attention, one large key H={H} n={n} d={d} k={k}", flush=True)
+    Q, K, V = tensors(H, n, d, n + d)
+    idx = random_idx(n, k, H, seed=n)
+    Q[..., 7] *= 2.0 ** -110
+    for h in range(H):
+        K[0, h, idx[h, k // 2].long(), 7] = 2.0 ** 110
+    for pairs in attention(Q, K, V, idx):
+        for got, want in pairs:
+            assert columns_off(got, want) < 4e-6
