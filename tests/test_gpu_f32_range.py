@@ -1,5 +1,5 @@
 """fp32 mode outside the range in which three bf16 parts carry a number: small numbers of Q and K against large ones of the other (or
-a large scale)."""
+a large scale), small V, large V under weights that are next to nothing."""
 
 import numpy as np
 import pytest
@@ -101,3 +101,40 @@ def test_attention_of_one_large_key(H, n, d, k):
     for pairs in attention(Q, K, V, idx):
         for got, want in pairs:
             assert columns_off(got, want) < 4e-6
+
+
+# One column of V small, one zero, the others ordinary.  Sums of numbers below 2^-126 are rounded to multiples of 2^-149: the fp32 instruction's
+# n / 2 times, by a third of one each, sqrt(n / 2) / 3 = 6 of them over 700 rows, and divided by the sum of the weights, ten and more; the
+# result once more.  Four allowed.
+@pytest.mark.parametrize("exponent", [-144, -141, -136, -133, -130, -126, -120, -100])
+@pytest.mark.parametrize("H,n,d,k", SHAPES)
+def test_small_values(H, n, d, k, exponent):
+    print(f"f32 range, small values H={H} n={n} d={d} k={k} 2^{exponent}", flush=True)
+    Q, K, V = tensors(H, n, d, n + d)
+    V[..., 3] = (1.0 + V[..., 3].abs()) * 2.0 ** exponent
+    V[..., 4] = 0.0
+    for pairs in attention(Q, K, V, random_idx(n, k, H, seed=n)):
+        for got, want in pairs[:2]:
+            assert (got[:, 4] == 0.0).all()
+            assert (np.abs(got[:, 3] - want[:, 3]) <= 2e-5 * want[:, 3] + 2.0 ** -147).all()
+
+
+# Logits of -87 units: 2^-24 of them times sqrt(d) is an error of 6e-5 of a weight.
+@pytest.mark.parametrize("H,n,d,k", SHAPES)
+@pytest.mark.parametrize("depth", [60.0, 72.0, 80.0, 87.0])
+def test_large_values_under_small_weights(H, n, d, k, depth):
+    """One key has all but e^-depth of the weight and values of order one; the others' values make up for theirs."""
+    print(f"f32 range, small weights H={H} n={n} d={d} k={k} {depth}", flush=True)
+    Q, K, V = tensors(H, n, d, n + d)
+    idx = random_idx(n, k, H, seed=n)
+    Q *= 0.1
+    Q[..., 0] = 1.0
+    K[..., 0] = -depth * d ** 0.5
+    V[..., 3] = (1.0 + V[..., 3].abs()) * float(np.exp(depth)) / n
+    for h in range(H):
+        first = idx[h, 0].long()
+        K[0, h, first] = 0.0
+        V[0, h, first, 3] = 0.5
+    for pairs in attention(Q, K, V, idx):
+        for got, want in pairs[:2]:
+            assert (np.abs(got[:, 3] / want[:, 3] - 1.0)).max() < 2e-4
