@@ -115,6 +115,13 @@ inline dim3 head_grid(int64_t heads, int per_head) {
     return dim3(8u * (unsigned)per_head, y, (layers + y - 1) / y);
 }
 
+// grid of a kernel with a workgroup per row: a launch takes fewer than 2^32 threads in x
+constexpr unsigned kRowsOfGrid = 1u << 20;
+inline dim3 row_grid(int32_t rows) {
+    const unsigned r = (unsigned)rows, x = r < kRowsOfGrid ? r : kRowsOfGrid;
+    return dim3(x, (r + x - 1) / x);
+}
+
 // compute units of the current device (cached per device; 256 if the runtime does not say)
 int compute_units();
 

@@ -761,7 +761,8 @@ __global__ void __launch_bounds__(64 * WAVES) topk_short_kernel(TopkParams p) {
     static_assert(BINS == 1 << LOG_BINS, "four parts per thread");
     __shared__ __attribute__((aligned(16))) uint32_t hist[BINS], found[4];
     __shared__ uint32_t exchange[2][WAVES][2], listed, few[64];
-    const int row = blockIdx.x;
+    const int row = (int)(blockIdx.y * kRowsOfGrid + blockIdx.x);
+    if (row >= p.rows) return;
     const int lane = threadIdx.x & 63;
     const int wave = WAVES > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
     const int first = wave * (64 * NK) + lane;
@@ -948,8 +949,8 @@ hipError_t launch_rows(const TopkParams& p, hipStream_t s) {
 
 template <int WAVES, int NK>
 hipError_t launch_short(const TopkParams& p, hipStream_t s) {
-    if (p.idx_copy != nullptr) hipLaunchKernelGGL((topk_short_kernel<WAVES, NK, true>), dim3(p.rows), dim3(64 * WAVES), 0, s, p);
-    else hipLaunchKernelGGL((topk_short_kernel<WAVES, NK, false>), dim3(p.rows), dim3(64 * WAVES), 0, s, p);
+    if (p.idx_copy != nullptr) hipLaunchKernelGGL((topk_short_kernel<WAVES, NK, true>), row_grid(p.rows), dim3(64 * WAVES), 0, s, p);
+    else hipLaunchKernelGGL((topk_short_kernel<WAVES, NK, false>), row_grid(p.rows), dim3(64 * WAVES), 0, s, p);
     return hipGetLastError();
 }
 
