@@ -44,6 +44,7 @@ __device__ __forceinline__ float half_max(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
     return fmaxf(__int_as_float(r[0]), __int_as_float(r[1]));
 }
+__device__ __forceinline__ float half_min(float x) { return -half_max(-x); }
 __device__ __forceinline__ float half_sum(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
     return __int_as_float(r[0]) + __int_as_float(r[1]);
