@@ -173,6 +173,7 @@ __global__ void __launch_bounds__(TK_THREADS) topk_kernel(TopkParams p) {
 // way the threshold is the exact k-th largest key: the estimate only decides how it is found.
 // The bracket's half width follows the estimate's error (see below); it doubles after a miss and
 // halves after an overflow.
+constexpr int V4 = 16;                               // loads of a thread: 65536 elements in 1024 threads
 constexpr int TKR_DIGIT = 13;
 constexpr int TKR_BINS = 1 << TKR_DIGIT;
 constexpr int TKR_BPT = TKR_BINS / TK_THREADS;       // histogram bins per thread
@@ -222,7 +223,7 @@ constexpr uint32_t TKR_HALF_WIDTH_MIN = 1u << 12, TKR_HALF_WIDTH_MAX = 1u << 22;
 // in a launch of its own, of 632 sets of 500 5 us).
 enum TopkRows { kPlainRows, kOddRows, kVarlenRows };
 
-template <int V4, TopkRows MODE, bool COPY>
+template <TopkRows MODE, bool COPY>
 __global__ void __launch_bounds__(TK_THREADS) topk_rows_kernel(TopkParams p, int rows_per_wg) {
     constexpr bool VARLEN = MODE == kVarlenRows, ODD = MODE != kPlainRows;
     constexpr int SEG = 256 * V4;
@@ -928,23 +929,22 @@ __global__ void __launch_bounds__(64 * WAVES) topk_short_kernel(TopkParams p) {
     else write(std::false_type{});
 }
 
-template <int V4, TopkRows MODE>
+template <TopkRows MODE>
 hipError_t launch_rows_as(const TopkParams& p, hipStream_t s) {
     // as many workgroups as the chip holds at a time (1024 threads at more than 64 registers: one
     // per CU); each walks over its run of consecutive rows
     const int resident = compute_units();
     const int rows_per_wg = (p.rows + resident - 1) / resident;
     const int grid = (p.rows + rows_per_wg - 1) / rows_per_wg;
-    if (p.idx_copy != nullptr) hipLaunchKernelGGL((topk_rows_kernel<V4, MODE, true>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
-    else hipLaunchKernelGGL((topk_rows_kernel<V4, MODE, false>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
+    if (p.idx_copy != nullptr) hipLaunchKernelGGL((topk_rows_kernel<MODE, true>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
+    else hipLaunchKernelGGL((topk_rows_kernel<MODE, false>), dim3(grid), dim3(TK_THREADS), 0, s, p, rows_per_wg);
     return hipGetLastError();
 }
 
-template <int V4>
 hipError_t launch_rows(const TopkParams& p, hipStream_t s) {
-    if (p.varlen != nullptr) return launch_rows_as<V4, kVarlenRows>(p, s);
-    if (p.n % 4 == 0 && p.stride % 4 == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15u) == 0) return launch_rows_as<V4, kPlainRows>(p, s);
-    return launch_rows_as<V4, kOddRows>(p, s);
+    if (p.varlen != nullptr) return launch_rows_as<kVarlenRows>(p, s);
+    if (p.n % 4 == 0 && p.stride % 4 == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15u) == 0) return launch_rows_as<kPlainRows>(p, s);
+    return launch_rows_as<kOddRows>(p, s);
 }
 
 template <int WAVES, int NK>
@@ -1028,7 +1028,7 @@ hipError_t launch_topk(const TopkParams& p, hipStream_t s) {
     if (p.n <= 8192) return launch_short<8, 16>(p, s);
     if (p.n <= 16384) return launch_short<16, 16>(p, s);
     if (p.n <= 32768) return launch_short<16, 32>(p, s);
-    if (p.n <= 65536) return launch_rows<16>(p, s);
+    if (p.n <= 65536) return launch_rows(p, s);
     hipLaunchKernelGGL(topk_kernel, dim3(p.rows), dim3(TK_THREADS), 0, s, p);
     return hipGetLastError();
 }
