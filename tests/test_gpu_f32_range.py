@@ -119,6 +119,24 @@ def test_small_values(H, n, d, k, exponent):
             assert (np.abs(got[:, 3] - want[:, 3]) <= 2e-5 * want[:, 3] + 2.0 ** -147).all()
 
 
+# A value that rounds to an infinity, in every place of a tile and in columns of every piece of it: seen by the largest magnitude of its column.
+@pytest.mark.parametrize("H,n,d,k", [(32, 260, 128, 65), (32, 200, 64, 64), (40, 700, 128, 225), (70, 520, 64, 129)])
+def test_one_huge_value_anywhere(H, n, d, k):
+    print(f"f32 range, one huge value H={H} n={n} d={d} k={k}", flush=True)
+    Q, K, V = tensors(H, n, d, n + d)
+    idx = random_idx(n, k, H, seed=n)
+    columns = [(11 * h + 3) % d for h in range(H)]
+    for h in range(H):
+        V[0, h, idx[h, (k - 1 - h) % k].long(), columns[h]] = 3.4e38
+    with pc.Context(1, H, n, d, torch.float32) as ctx:
+        O = ctx.attn(Q.to(DEV), K.to(DEV), V.to(DEV), idx.view(1, H, 1, k).to(DEV))
+        torch.cuda.synchronize()
+    for h in range(H):
+        cols = idx[h].numpy()
+        want = oracle.dense_attention(f64(Q[0, h]), f64(K[0, h])[cols], f64(V[0, h])[cols])
+        assert columns_off(f64(O[0, h]), want) < 2e-5, (h, columns[h])
+
+
 # Logits of -87 units: 2^-24 of them times sqrt(d) is an error of 6e-5 of a weight.
 @pytest.mark.parametrize("H,n,d,k", SHAPES)
 @pytest.mark.parametrize("depth", [60.0, 72.0, 80.0, 87.0])
