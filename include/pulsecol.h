@@ -71,17 +71,23 @@ typedef enum { PULSECOL_BF16 = 0, PULSECOL_F32 = 1 } pulsecol_dtype;
 typedef struct {
     int32_t batch;      /* >= 1 */
     int32_t heads;      /* >= 1: heads of Q and O (K and V: see kv_heads)                         */
-    int32_t seq;        /* n >= 1; bf16: n < 2^24                                                */
+    int32_t seq;        /* 1 <= n < 2^24                                                         */
     int32_t head_dim;   /* d_h: 64 or 128                                                        */
-    int32_t dtype;      /* pulsecol_dtype: storage type of Q, K, V, O.  bf16: bf16 MFMA with fp32 */
-                        /* accumulation and fp32 softmax; f32: fp32 throughout.                  */
+    int32_t dtype;      /* pulsecol_dtype: storage type of Q, K, V, O.  bf16: bf16 MFMA with fp32
+                         * accumulation and fp32 softmax.  f32: no operand is rounded below 24 bits, fp32 softmax
+                         * and sums; products on the bf16 MFMA, every number split into three parts.  What the
+                         * parts cannot carry is formed with the fp32 MFMA instead, in the same call at up to two and a
+                         * half times its time, by blocks of 32 rows or by workgroup: queries (scores: and keys) with a
+                         * nonzero element below 2^-109 or one above min(2^60, 2^96 / (scale log2 e)), infinities,
+                         * NaN and numbers that round to an infinity in bf16, column masses of a segment below 2^-90,
+                         * outputs below 2^-90 or next to nothing beside their column of V                      */
     int32_t group_size; /* queries per group (Sec. 3.3); 0 or >= seq: the whole head is one group
                          * (U = 1).  Otherwise U = ceil(seq / group_size) groups of consecutive
                          * rows; bf16: a multiple of 32 (multiples of 256 run in the main kernel,
                          * smaller ones -- the paper's 32 / 64 / 128 -- in the small-group kernel),
                          * f32: a multiple of 128; else PULSECOL_ERR_UNSUPPORTED                  */
     int64_t stride_b;   /* element strides of batch, head and sequence; 0 = packed.  Multiples of 16 bytes;
-                         * bf16: the sequence stride is below 2^24 bytes and one head spans less than
+                         * the sequence stride is below 2^24 bytes and one head spans less than
                          * 4 GiB (seq * stride_n), else PULSECOL_ERR_UNSUPPORTED                  */
     int64_t stride_h;
     int64_t stride_n;
@@ -104,7 +110,7 @@ PULSECOL_API pulsecol_status pulsecol_validate_shape(const pulsecol_shape* shape
 
 /* Create a context on HIP device `device`: copies `shape`, allocates the scratch
  * (4*B*H*seq bytes of row statistics, 4*B*H*U*seq bytes of scores, 4*B*H*U*k_max bytes for the
- * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 256 bytes of counters; bf16 shapes
+ * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 256 bytes of counters; shapes
  * whose grids leave part of the chip idle: partial results of the scoring passes, at most 64 MiB together with the
  * row statistics and the scores, and at most 16 MiB for the ragged lengths of a padded batch).
  * *out is set only on PULSECOL_OK. */
@@ -165,8 +171,9 @@ PULSECOL_API pulsecol_status pulsecol_select(pulsecol_ctx* ctx, const void* Q, c
  * scores_out[b, h, u, j] = (1/|G_u|) sum_{i in G_u} softmax_j(q_i . k_j * scale), fp32 [B, H, U, seq].
  * Row sums of the softmax are accumulated in fp32 in a fixed order: results are
  * bit-identical from run to run.  bf16: the scores of a head follow from its own Q, K, length and group size alone; they are the
- * same bits whatever other heads and batch elements a context holds.  f32: small grids run in kernels that share the tiles of a
- * block out among waves, so the last bits of a sum may differ between contexts of different size. */
+ * same bits whatever other heads and batch elements a context holds.  f32: the same, but contexts of up to
+ * 512 rows (D = 64: 768) whose blocks of 32 rows all find a CU run in kernels that share the tiles of a block out among waves, so the last
+ * bits of a sum may differ from those in larger ones. */
 PULSECOL_API pulsecol_status pulsecol_scores(pulsecol_ctx* ctx, const void* Q, const void* K, float* scores_out,
                                 void* stream);
 

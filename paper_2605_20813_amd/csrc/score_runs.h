@@ -129,8 +129,12 @@ inline int score_teams(int64_t blocks256, int64_t blocks128, int32_t longest, in
 inline bool score_blocks_small_f32(int n, int64_t heads, int head_dim, int compute_units) {
     return n <= (head_dim == 64 ? 768 : 512) && (int64_t)((n + 31) / 32) * heads <= compute_units;
 }
-// Runs in blocks of 128 rows: the rule above with what a tile of 96 (48) matrix instructions per wave costs.  Both passes, 1500 rows: 8
-// heads uncut / in 2 / 4 / 8 runs 113 / 70 / 67 / 63 us, 16 heads 114 / 114 / 104 / 110.
+// Runs in blocks of 128 rows: the rule above with what a tile of 96 (48) matrix instructions per wave costs, two workgroups counted to a CU at
+// either head dimension (at D = 64 it holds three, but with two its matrix pipe is busy: counted as three, with the costs above, the choice
+// is no nearer).  On 17 grids of 2 to 64 heads and 900 to 4100 rows the choice is within 8.4% of the best number of runs at D = 64, 1.1% on
+// average, and within 5.2% at D = 128, 0.6% on average, but for 2 heads of 3000 rows: in four runs 106 us, in twelve 78.  Both passes,
+// uncut / in 2 / 5 / 10 runs, us: D = 128, 8 heads of 1500 rows 112 / 72 / 64 / 71, 16 heads 116 / 117 / 111 / 123; D = 64 68 / 47 / 41 / 43,
+// 72 / 70 / 65 / 70.
 inline int score_splits_f32(int64_t blocks, int32_t longest, int compute_units) {
     return cheapest_runs(blocks, ScoreSegments(longest, true), RunCosts{2, 0.6, 1.0, 1.0, 1.5}, compute_units).count;
 }
