@@ -110,7 +110,7 @@ PULSECOL_API pulsecol_status pulsecol_validate_shape(const pulsecol_shape* shape
 
 /* Create a context on HIP device `device`: copies `shape`, allocates the scratch
  * (4*B*H*seq bytes of row statistics, 4*B*H*U*seq bytes of scores, 4*B*H*U*k_max bytes for the
- * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 256 bytes of counters; shapes
+ * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 2560 bytes of counters; shapes
  * whose grids leave part of the chip idle: partial results of the scoring passes, at most 64 MiB together with the
  * row statistics and the scores, and at most 16 MiB for the ragged lengths of a padded batch).
  * *out is set only on PULSECOL_OK. */

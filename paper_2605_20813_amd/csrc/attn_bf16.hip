@@ -746,23 +746,29 @@ struct AttnWave {
 // Work distribution.  The grid is a fixed set of workgroups (as many as fit the chip at once)
 // that take query blocks from eight queues, one per XCD: queue y holds the query blocks of the
 // heads 8*hh + y in order, so that at any time an XCD works on one or two heads whose gathered
-// K/V rows fit its L2, and a workgroup takes from the queue of the XCD it runs on (read from the
-// hardware's XCC id register, so nothing is assumed about the order in which workgroups are dealt
-// to the XCDs).  The XCDs of one chip do not run at the same speed (a few percent apart under this
+// K/V rows fit its L2.  The XCDs of one chip do not run at the same speed (a few percent apart under this
 // load): a workgroup whose queue is empty goes on with the next non-empty one instead of idling
 // until the slowest XCD is done.
-// Counters: work[y] = (launch stamp << 32) | next item of queue y.  The stamp is a number the host
-// gives every launch on a context; a counter that carries another stamp is whatever an earlier
-// launch left behind (finished, aborted, or never run) and is restarted by the first workgroup
-// that notices.  So a launch depends on no state of the launches before it, and nothing has to be
-// cleared between launches.
+// The first blocks are dealt by workgroup id, the k-th of queue y to workgroup 8*k + y (ids go round-robin over the XCDs);
+// the others are handed out by a counter per queue, from the queue of the XCD the workgroup runs on (read from the
+// hardware's XCC id register).  Nothing waits for a counter at the start of a launch, and at its end one look at all
+// eight counters tells what is left: an atomic round trip to memory takes about a microsecond, more where 32
+// workgroups ask for the same word, and when the first block came from the counters as well and a workgroup asked the empty
+// queues one after the other, a launch spent 10 us in front of its first load and 15 to 20 behind its last product
+// (32 heads of 4096 rows, keep 10%: 68 -> 42 us; 8 heads of 8192 rows, keep 20%, 80 -> 51).
+// The counters are zero between launches: the last workgroup to find every queue empty clears them (so a captured launch
+// can be replayed).
 struct WorkQueues {
-    unsigned long long* work;
-    uint32_t stamp;
+    uint32_t* work;
     int bh_total, nqb;
     const int32_t* varlen;      // per batch element: its own sequence length (variable-length batches), or nullptr
-    int heads;
+    int heads, workgroups;
     __device__ __forceinline__ int items(int y) const { return y < bh_total ? ((bh_total - y + 7) >> 3) * nqb : 0; }
+    // items of queue y that are dealt by workgroup id
+    __device__ __forceinline__ int dealt(int y) const {
+        const int all = items(y), ids = (workgroups - y + 7) >> 3;
+        return all < ids ? all : ids;
+    }
     // item j of queue q is a query block that lies wholly in the padding of its batch element
     __device__ __forceinline__ bool is_padding(int q, int j) const {
         if (varlen == nullptr) return false;
@@ -770,35 +776,45 @@ struct WorkQueues {
         const int qblk = j - head_block * nqb;
         return qblk * BM >= varlen[(head_block * 8 + q) / heads];
     }
+    // one lane: the next item of queue q (items(q) or more: there is none left)
     __device__ __forceinline__ int take(int q) const {
-        unsigned long long* const counter = work + q;
-        unsigned long long v = __hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while ((uint32_t)(v >> 32) != stamp) {
-            unsigned long long cur = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t)(cur >> 32) == stamp) {
-                v = __hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                continue;
-            }
-            // restart the counter at item 1 and keep item 0 (fails if another workgroup was faster, or
-            // has just added to the stale value: look again)
-            const unsigned long long fresh = ((unsigned long long)stamp << 32) | 1ull;
-            if (__hip_atomic_compare_exchange_strong(counter, &cur, fresh, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                return 0;
-        }
-        return (int)(uint32_t)v;
+        if (dealt(q) == items(q)) return items(q);
+        return dealt(q) + (int)__hip_atomic_fetch_add(work + q * kWorkStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // One thread: item j taken from queue q is good, or else the first item that the following
-    // queues still have; j = -1 when every queue has been found empty.
-    __device__ __forceinline__ void settle(int home, int& q, int& j) const {
+    // One wave: item j taken from queue q is good, or else the next one that it or the queues behind it still have; j = -1 when
+    // every queue has been found empty.
+    __device__ __forceinline__ void settle(int lane, int& q, int& j) const {
         for (;;) {
-            while (j >= items(q)) {
-                q = (q + 1) & 7;
-                if (q == home) { j = -1; return; }
-                j = take(q);
+            if (j < items(q)) {
+                if (!is_padding(q, j)) return;          // (nothing to do for a block of padding rows: on to the next item)
+            } else {
+                const int y = lane & 7;
+                bool some = dealt(y) < items(y);
+                if (some) some = dealt(y) + (int)__hip_atomic_load(work + y * kWorkStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < items(y);
+                const uint32_t left = (uint32_t)__ballot(some) & 0xFFu;
+                if (left == 0) { j = -1; return; }
+                q = (q + __builtin_ctz((left | left << 8) >> q)) & 7;
             }
-            if (!is_padding(q, j)) return;
-            j = take(q);            // nothing to do for a block of padding rows: on to the next item
+            int first = 0;
+            if (lane == 0) first = take(q);
+            j = __builtin_amdgcn_readfirstlane(first);
         }
+    }
+    // some items are handed out by the counters
+    __device__ __forceinline__ bool counted() const {
+        bool any = false;
+#pragma unroll
+        for (int y = 0; y < 8; ++y) any = any || dealt(y) < items(y);
+        return any;
+    }
+    // One lane of every workgroup that has found every queue empty, once: how many had before it
+    __device__ __forceinline__ int leave() const {
+        return (int)__hip_atomic_fetch_add(work + 8 * kWorkStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // ... and of the last of them: nobody looks at the counters any more
+    __device__ __forceinline__ void clear() const {
+#pragma unroll
+        for (int y = 0; y <= 8; ++y) __hip_atomic_store(work + y * kWorkStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 };
 
@@ -829,19 +845,32 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     asm volatile("" : : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.o), "s"(p.idx), "s"(p.lse), "s"(p.lse_base2),
                          "s"(p.td.sb), "s"(p.td.sh), "s"(p.td.sn), "s"(p.td_kv.sb), "s"(p.td_kv.sh), "s"(p.td_kv.sn),
                          "s"(p.kv_heads), "s"(p.batch), "s"(p.heads), "s"(p.n), "s"(p.ns), "s"(p.groups),
-                         "s"(p.group_size), "s"(p.scale), "s"(p.work), "s"(p.work_stamp), "s"(p.varlen), "s"(p.idx_stride));
+                         "s"(p.group_size), "s"(p.scale), "s"(p.work), "s"(p.varlen), "s"(p.idx_stride));
     const int nqb = (p.n + BM - 1) / BM;
-    const WorkQueues queues{p.work, p.work_stamp, p.batch * p.heads, nqb, p.varlen, p.heads};
+    const WorkQueues queues{p.work, p.batch * p.heads, nqb, p.varlen, p.heads, (int)gridDim.x};
     __shared__ int32_t lds_item[2];          // the workgroup's next item: queue, index in the queue
-    const int home = xcc_id();
-    if (threadIdx.x == 0) {
-        int q = home, j = queues.take(home);
-        queues.settle(home, q, j);
-        lds_item[0] = q;
-        lds_item[1] = j;
+    int cur_q = (int)blockIdx.x & 7, cur_j = (int)blockIdx.x >> 3;
+    int from_q = xcc_id();                   // the queue that the item after this one is taken from
+    int left_before = -1;                    // workgroups that had left when this one did
+    // wave 0: settles on an item and leaves it for the others
+    auto settle_item = [&](int q, int j) {
+        queues.settle((int)threadIdx.x, q, j);
+        if (threadIdx.x == 0) {
+            lds_item[0] = q;
+            lds_item[1] = j;
+        }
+    };
+    // behind a barrier
+    auto read_item = [&] {
+        from_q = cur_q = __builtin_amdgcn_readfirstlane(lds_item[0]);
+        cur_j = __builtin_amdgcn_readfirstlane(lds_item[1]);
+        if (cur_j < 0 && threadIdx.x == 0 && queues.counted()) left_before = queues.leave();
+    };
+    if (cur_j >= queues.items(cur_q) || queues.is_padding(cur_q, cur_j)) {
+        if (threadIdx.x < 64) settle_item(cur_q, cur_j);
+        __syncthreads();
+        read_item();
     }
-    __syncthreads();
-    int cur_q = __builtin_amdgcn_readfirstlane(lds_item[0]), cur_j = __builtin_amdgcn_readfirstlane(lds_item[1]);
 
     // the geometry that requesting a query block's first loads needs
     W wq;
@@ -1079,7 +1108,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     // that have nothing left to do, and early enough for the answer to be there when the output
     // tile has been staged (nothing else is in flight in between).
     int early_j = 0;
-    if (threadIdx.x == 0) early_j = queues.take(cur_q);
+    if (threadIdx.x == 0) early_j = queues.take(from_q);
     w.general_step(nhalf - 1, lds_k, lds_v, SB, SA, PA, PB);
 
     w.pv_all(lds_v + (((nhalf - 1) >> 1) % NBUF_V) * TILE_BYTES, (nhalf - 1) & 1, PB);
@@ -1111,15 +1140,9 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     // block's stores.  (The taken index is read in front of every store: its wait would cover
     // them too.)
     const int next_j = __builtin_amdgcn_readfirstlane(early_j);       // meaningful in wave 0 only
-    if (threadIdx.x == 0) {
-        int q = cur_q, j = next_j;
-        queues.settle(home, q, j);
-        lds_item[0] = q;
-        lds_item[1] = j;
-    }
+    if (threadIdx.x < 64) settle_item(from_q, next_j);
     __syncthreads();
-    cur_q = __builtin_amdgcn_readfirstlane(lds_item[0]);
-    cur_j = __builtin_amdgcn_readfirstlane(lds_item[1]);
+    read_item();
     const bool more = cur_j >= 0;
     if (more) request_rows(cur_q, cur_j);
     constexpr int PIECES = W::PIECES, ROW_BYTES = W::ROW_BYTES, RPC = W::ROWS_PER_CHUNK;
@@ -1181,7 +1204,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
         if (q0 + r < n) *(u32x4*)(obase + t * group_stride) = rows_out[t];
     }
   }
-
+    if (left_before == (int)gridDim.x - 1) queues.clear();
 }
 
 template <int D, int MODE>

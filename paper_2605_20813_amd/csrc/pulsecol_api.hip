@@ -37,8 +37,7 @@ struct pulsecol_ctx {
     int32_t cached_k = 0;           // 0 = nothing cached
     int32_t k_max = 0;              // columns per group the cache has room for
     int32_t* bad_count = nullptr;   // one device counter for the validation mode (first word of a small block)
-    unsigned long long* work = nullptr;   // work counters of the bf16 attention kernels (same block)
-    uint32_t work_stamp = 0;        // stamp of the last launch that used them (every launch takes the next one)
+    uint32_t* work = nullptr;       // work counters of the bf16 attention kernels (same block)
     bool validate = false;          // check column numbers in front of every pulsecol_attn
     int32_t* varlen = nullptr;      // [2 * batch] device words of variable-length batches: lengths, kept counts
     bool varlen_on = false;         // pulsecol_set_seq_lens has given per-element lengths
@@ -225,21 +224,19 @@ pulsecol::AttnParams attn_params(pulsecol_ctx* c, const void* Q, const void* K, 
     p.scale = c->scale;
     p.varlen = c->varlen_on ? c->varlen : nullptr;
     p.work = c->work;
-    if (++c->work_stamp == 0) c->work_stamp = 1;       // freshly cleared counters carry stamp 0
-    p.work_stamp = c->work_stamp;
     return p;
 }
 
 // Query rows per workgroup of the column-sparse kernel a call with ns kept columns runs in.  Group-wise
 // sets: the largest block that divides the group size.  One set per head: the hand-scheduled kernel
-// with 256-row blocks, except for short jobs, where its fixed costs (one workgroup per CU, a long
-// start-up per launch and per query block) outweigh its faster steady state and the plain kernel
+// with 256-row blocks, except for short jobs, where the start and end of a block (one workgroup per CU: nothing else covers
+// them) outweigh its faster steady state and the plain kernel
 // with 128-row blocks, two to a CU, finishes first.  The rule is a two-line cost model per head dimension
-// (microseconds; R = 256-row blocks per CU, t = 64-column tiles), fitted to launches of 2 to 32 heads at 1K to 32K
-// context and keep 5 to 25%; on those it picks the slower kernel only where the two are within 6% of each other.
-//   D = 128  scheduled 40 + R (2.6 + 1.55 t)   plain 5 + R (3.2 + 1.92 t)
-//   D = 64   scheduled 37 + R (2.9 + 0.95 t)   plain 4 + R (1.9 + 1.15 t)
-// D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.9 / 68.1 us, 8K 120 / 133, 16K 437 / 387.
+// (microseconds; R = 256-row blocks per CU, r = rounds of them, t = 64-column tiles), fitted to launches of 4 to 32 heads at 1K to 32K
+// context and keep 5 to 20%; on those it picks the slower kernel only where the two are within 5% of each other.
+//   D = 128  scheduled 2 + r (10 + 1.46 t)     plain 5 + R (3.2 + 1.92 t)
+//   D = 64   scheduled 2 + r (6.5 + 0.93 t)    plain 4 + R (1.9 + 1.15 t)
+// D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.9 / 42.4 us, 8K 124 / 117, 16K 430 / 365; 8 heads of 8K, keep 20%, 58 / 51.
 int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
     if (c->shape.dtype != PULSECOL_BF16)
         return pulsecol::block_rows_f32(pulsecol::kSparse, c->shape.head_dim, c->shape.seq, (int64_t)c->shape.batch * c->shape.heads,
@@ -250,7 +247,9 @@ int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
         const double R = blocks / (double)pulsecol::compute_units();
         const double t = (double)((ns + 63) / 64);
         const bool wide = c->shape.head_dim == 128;
-        const double scheduled = wide ? 40.0 + R * (2.6 + 1.55 * t) : 37.0 + R * (2.9 + 0.95 * t);
+        // whole blocks are handed out, by a queue: with many to a CU the last round is half empty on average
+        const double r = std::fmin(std::ceil(R), R + 0.5);
+        const double scheduled = wide ? 2.0 + r * (10.0 + 1.46 * t) : 2.0 + r * (6.5 + 0.93 * t);
         const double plain = wide ? 5.0 + R * (3.2 + 1.92 * t) : 4.0 + R * (1.9 + 1.15 * t);
         return plain < scheduled ? 128 : pulsecol::kBlockM_bf16;
     }
@@ -407,11 +406,13 @@ pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape,
     hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, score_words(c, kMostFloats, kPaddedFloats) * sizeof(float)) : e1;
     c->k_max = shape->max_keep_ratio > 0.0 ? pulsecol_num_keep(shape->seq, shape->max_keep_ratio) : shape->seq;
     hipError_t e3 = e2 == hipSuccess ? hipMalloc((void**)&c->cached_idx, rows * c->groups * (size_t)c->k_max * sizeof(int32_t)) : e2;
-    static_assert(64 + pulsecol::kWorkCounters * sizeof(unsigned long long) <= 256, "counter block");
+    // the validation mode's counter in a line of its own, then the attention kernels', which are zero between launches
+    constexpr size_t kCounterBytes = (pulsecol::kWorkStride + pulsecol::kWorkWords) * sizeof(uint32_t);
     if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->varlen, 2 * (size_t)shape->batch * sizeof(int32_t));
-    if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->bad_count, 256);
-    if (e3 == hipSuccess) e3 = hipMemset(c->bad_count, 0, 256);
-    if (e3 == hipSuccess) c->work = reinterpret_cast<unsigned long long*>(c->bad_count + 16);
+    if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->bad_count, kCounterBytes);
+    if (e3 == hipSuccess) e3 = hipMemset(c->bad_count, 0, kCounterBytes);
+    if (e3 == hipSuccess) e3 = hipStreamSynchronize(nullptr);         // (streams that do not wait for the default one)
+    if (e3 == hipSuccess) c->work = reinterpret_cast<uint32_t*>(c->bad_count) + pulsecol::kWorkStride;
     if (e3 != hipSuccess) {
         if (c->lse) (void)hipFree(c->lse);
         if (c->scores) (void)hipFree(c->scores);

@@ -28,18 +28,17 @@ struct AttnParams {
     int32_t groups;          // U query groups per head (1 = the whole head)
     int32_t group_size;      // rows per group, a multiple of the kernel's query block (unused when U = 1)
     float scale;             // logit scale
-    // bf16 kernel with 256-row query blocks only: kWorkCounters 64-bit words of device memory through
-    // which its workgroups hand out the query blocks, and a stamp that differs from the one of the last
-    // launch that used the same words (any contents are fine: counters with another stamp are restarted)
-    unsigned long long* work;
-    uint32_t work_stamp;
+    // bf16 kernel with 256-row query blocks only: kWorkWords words of device memory through which its workgroups hand
+    // out the query blocks, zero between launches (a launch clears what it used)
+    uint32_t* work;
     // variable-length batches: device array [2 * batch] -- per batch element its own sequence length
     // (<= n), then the number of leading entries of its column sets that count (<= ns); nullptr: every
     // element has n rows and ns columns.  Rows and key positions beyond an element's length are padding.
     const int32_t* varlen;
 };
 
-constexpr int kWorkCounters = 8;
+// eight counters and the number of workgroups that are done, each in a memory line of its own
+constexpr int kWorkStride = 64, kWorkWords = 9 * kWorkStride;
 
 struct ScoreParams {
     const void* q;
