@@ -47,6 +47,9 @@ typedef unsigned char byte;
 constexpr int BN = 32;      // gathered rows per tile
 constexpr int NBUF = 3;     // LDS tile slots per operand: one being read, two on their way
 constexpr float kGrowthLimit = 256.0f;      // 2^kTau with kTau = 8, as in the main kernel
+// log2 units by which a reference is set above the maximum that it is taken from: the first tile's alone is outgrown in
+// most of the next tiles by some lane of a wave (attn_bf16.hip)
+constexpr float kHeadroom = 8.0f;
 constexpr float kNoReference = -1e30f;      // of a query whose first tile holds no finite logit: the tile adds nothing
 
 // s_waitcnt vmcnt(v) with the other counters left alone (gfx9 encoding: vmcnt in [3:0] and [15:14])
@@ -235,9 +238,9 @@ struct GroupWave {
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
             const float m2 = half_max(mx) * c2;              // same value in both half-waves
             if (m2 > ref + 1.0f) {
-                const float steps = ceilf(m2 - ref);
+                const float steps = ceilf(m2 - ref) + kHeadroom;
                 const float alpha = fast_exp2(-steps);
-                ref = ref == kNoReference ? m2 : ref + steps;         // (no finite logit so far: alpha is zero)
+                ref = ref == kNoReference ? m2 + kHeadroom : ref + steps;         // (no finite logit so far: alpha is zero)
                 l_run *= alpha;
                 mfma_settle(o_acc);
 #pragma unroll
@@ -549,7 +552,7 @@ attn_bf16_group_kernel(AttnParams p) {
     u32x4 pa[2], pb[2];
     typename W::Sums sm{0.f, 0.f, 0.f};
     const int last = tiles - 1;
-    // ---- S(0), which sets the reference: the maximum of the first tile
+    // ---- S(0), which sets the reference: from the maximum of the first tile
     if (newer_stores == NW * CH) wait_vmcnt_at_most<3 * CH + NW * CH>();
     else wait_vmcnt_at_most<3 * CH>();
     memory_order_point();
@@ -565,7 +568,7 @@ attn_bf16_group_kernel(AttnParams p) {
         float mx = sa[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sa[r]);
-        w.ref = fmaxf(half_max(mx) * w.c2, kNoReference);
+        w.ref = fmaxf(half_max(mx) * w.c2 + kHeadroom, kNoReference);
     }
     // Two teams: both weigh against the reference that team 0 takes from the block's first tile, handed over behind the
     // next barrier.  A weight then has the same bits whichever team forms it, in this form of the kernel or in the one
