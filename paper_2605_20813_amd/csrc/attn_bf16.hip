@@ -66,9 +66,12 @@ constexpr float kGrowthLimit = 256.0f;   // 2^kTau
 // Log2 units by which a reference is set above the maximum that it is taken from.  The first 32 kept keys say little about the
 // largest logit of a row: against their maximum alone some lane of a wave outgrew its reference in most of the first
 // tiles of a block, at some 2000 ticks for all four waves.  Weights, sums and accumulators are floats that all carry the same
-// power of two, so that only weights below 2^-118 of the largest are lost.  Not in the dense kernel, whose reference goes into the
-// row log-sum-exp and is rounded with it.
-template <int MODE> constexpr float headroom() { return MODE == kDense ? 0.0f : 8.0f; }
+// power of two, so that only weights below 2^-118 of the largest are lost.  A whole number, so that a weight is rounded to
+// sixteen bits as it was.  The dense kernel's reference goes into the row log-sum-exp (rms error against 64 bits, 2 heads of 4096 rows,
+// 4.5e-7 -> 3.8e-7, of 8192 4.6e-7 -> 4.0e-7, of 3001 with logits three times as steep 1.22e-6 -> 1.24e-6).
+// 0 / 3 / 5 / 8 units: 64K keep 10% 5348 / 5187 / 5123 / 5107 us, 32K keep 20% 2698 / 2609 / 2559 / 2546, refresh_dense of 16K 5089 /
+// 5011 / 4959 / 4934.
+constexpr float kHeadroom = 8.0f;
 
 typedef unsigned char byte;
 
@@ -503,9 +506,9 @@ struct AttnWave {
             const float m2 = half_tile_max(S[qb]) * c2;        // same value in both half-waves
             if (m2 > mc[qb] + 1.0f) {
                 const bool first = mc[qb] == -INFINITY;
-                const float steps = first ? 0.f : ceilf(m2 - mc[qb]) + headroom<MODE>();
+                const float steps = first ? 0.f : ceilf(m2 - mc[qb]) + kHeadroom;
                 const float alpha = first ? 0.f : fast_exp2(-steps);
-                mc[qb] = first ? m2 + headroom<MODE>() : mc[qb] + steps;
+                mc[qb] = first ? m2 + kHeadroom : mc[qb] + steps;
                 l_run[qb] *= alpha;
                 // one block at a time, pinned inside this branch: the accumulator passes through
                 // VGPRs, and all of it at once does not fit beside the rest of the loop's registers
@@ -1064,7 +1067,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     // The first half-tile sets the softmax reference directly (it is no less than the maximum seen so far, so no term
     // can overflow), which keeps the first step off the slow reference-update path.
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) w.mc[qb] = w.half_tile_max(SA[qb]) * w.c2 + headroom<MODE>();
+    for (int qb = 0; qb < 2; ++qb) w.mc[qb] = w.half_tile_max(SA[qb]) * w.c2 + kHeadroom;
 
     // j = 0: S(0) in SA -> P(0) in PA, S(1) in SB
     w.general_step(0, lds_k, lds_v, SA, SB, PB, PA);
