@@ -233,10 +233,11 @@ pulsecol::AttnParams attn_params(pulsecol_ctx* c, const void* Q, const void* K, 
 // them) outweigh its faster steady state and the plain kernel
 // with 128-row blocks, two to a CU, finishes first.  The rule is a two-line cost model per head dimension
 // (microseconds; R = 256-row blocks per CU, r = rounds of them, t = 64-column tiles), fitted to launches of 4 to 32 heads at 1K to 32K
-// context and keep 5 to 20%; on those it picks the slower kernel only where the two are within 5% of each other.
-//   D = 128  scheduled 2 + r (10 + 1.46 t)     plain 5 + R (3.2 + 1.92 t)
-//   D = 64   scheduled 2 + r (6.5 + 0.93 t)    plain 4 + R (1.9 + 1.15 t)
-// D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.9 / 42.4 us, 8K 124 / 117, 16K 430 / 365; 8 heads of 8K, keep 20%, 58 / 51.
+// context and keep 5 to 20%; on those it picks the slower kernel only where the two are within 3% of each other.
+//   D = 128  scheduled 2 + r (9.4 + 1.46 t)    plain 1 + R (6.2 + 1.9 t)
+//   D = 64   scheduled 2 + r (6.5 + 0.93 t)    plain 1.5 + R (2.6 + 1.19 t)
+// D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.7 / 42.9 us, 8K 123 / 115, 16K 434 / 365, keep 5% 243 / 223; 8 heads of 8K, keep
+// 20%, 58 / 51.
 int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
     if (c->shape.dtype != PULSECOL_BF16)
         return pulsecol::block_rows_f32(pulsecol::kSparse, c->shape.head_dim, c->shape.seq, (int64_t)c->shape.batch * c->shape.heads,
@@ -249,8 +250,8 @@ int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
         const bool wide = c->shape.head_dim == 128;
         // whole blocks are handed out, by a queue: with many to a CU the last round is half empty on average
         const double r = std::fmin(std::ceil(R), R + 0.5);
-        const double scheduled = wide ? 2.0 + r * (10.0 + 1.46 * t) : 2.0 + r * (6.5 + 0.93 * t);
-        const double plain = wide ? 5.0 + R * (3.2 + 1.92 * t) : 4.0 + R * (1.9 + 1.15 * t);
+        const double scheduled = wide ? 2.0 + r * (9.4 + 1.46 * t) : 2.0 + r * (6.5 + 0.93 * t);
+        const double plain = wide ? 1.0 + R * (6.2 + 1.9 * t) : 1.5 + R * (2.6 + 1.19 * t);
         return plain < scheduled ? 128 : pulsecol::kBlockM_bf16;
     }
     for (int bm : {256, 128, 64}) if (c->shape.group_size % bm == 0) return bm;
