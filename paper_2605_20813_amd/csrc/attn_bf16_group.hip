@@ -48,7 +48,8 @@ constexpr int BN = 32;      // gathered rows per tile
 constexpr int NBUF = 3;     // LDS tile slots per operand: one being read, two on their way
 constexpr float kGrowthLimit = 256.0f;      // 2^kTau with kTau = 8, as in the main kernel
 // log2 units by which a reference is set above the maximum that it is taken from: the first tile's alone is outgrown in
-// most of the next tiles by some lane of a wave (attn_bf16.hip)
+// most of the next tiles by some lane of a wave (attn_bf16.hip).  32 heads of 4096 rows, keep 10%, 37.6 -> 35.3 us, 4 heads of 8192
+// 20.4 -> 18.6, groups of 128 at 32 heads of 8192 138.6 -> 132.7.
 constexpr float kHeadroom = 8.0f;
 constexpr float kNoReference = -1e30f;      // of a query whose first tile holds no finite logit: the tile adds nothing
 
