@@ -33,7 +33,9 @@
  *   - Every function returns a pulsecol_status; nothing aborts or throws, and nothing is
  *     printed unless the environment variable PULSECOL_LOG is set (then every failure goes
  *     to stderr as well).  On failure no kernel has been launched.  pulsecol_last_error gives a text for the last failure on a
- *     context.  Two calls on one context must not overlap in time (they share scratch).
+ *     context.  Two calls on one context must not overlap in time (they share scratch), whatever their streams, replays of
+ *     captured calls among them: the outputs of calls that do are unspecified, those of later ones are not affected once a
+ *     pattern selected meanwhile has been selected again.
  *   - NaN / Inf in the inputs give unspecified values, never a fault.
  */
 #ifndef PULSECOL_H
@@ -110,7 +112,7 @@ PULSECOL_API pulsecol_status pulsecol_validate_shape(const pulsecol_shape* shape
 
 /* Create a context on HIP device `device`: copies `shape`, allocates the scratch
  * (4*B*H*seq bytes of row statistics, 4*B*H*U*seq bytes of scores, 4*B*H*U*k_max bytes for the
- * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 2560 bytes of counters; shapes
+ * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 18688 bytes of counters; shapes
  * whose grids leave part of the chip idle: partial results of the scoring passes, at most 64 MiB together with the
  * row statistics and the scores, and at most 16 MiB for the ragged lengths of a padded batch).
  * *out is set only on PULSECOL_OK. */

@@ -765,8 +765,9 @@ struct AttnWave {
 // workgroups ask for the same word, and when the first block came from the counters as well and a workgroup asked the empty
 // queues one after the other, a launch spent 10 us in front of its first load and 15 to 20 behind its last product
 // (32 heads of 4096 rows, keep 10%: 68 -> 42 us; 8 heads of 8192 rows, keep 20%, 80 -> 51).
-// The counters are zero between launches: the last workgroup to find every queue empty clears them (so a captured launch
-// can be replayed).
+// The counters are zero when a launch starts, and it does not matter how it leaves them: the host gives every launch a set
+// that an earlier one, or a fill in front of a captured one, has cleared.  (A launch that had to find them as the one before it
+// left them would skip blocks for good after two that overlapped.)
 struct WorkQueues {
     uint32_t* work;
     int bh_total, nqb;
@@ -809,23 +810,15 @@ struct WorkQueues {
             j = __builtin_amdgcn_readfirstlane(first);
         }
     }
-    // some items are handed out by the counters
-    __device__ __forceinline__ bool counted() const {
-        bool any = false;
-#pragma unroll
-        for (int y = 0; y < 8; ++y) any = any || dealt(y) < items(y);
-        return any;
-    }
-    // One lane of every workgroup that has found every queue empty, once: how many had before it
-    __device__ __forceinline__ int leave() const {
-        return (int)__hip_atomic_fetch_add(work + 8 * kWorkStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // ... and of the last of them: nobody looks at the counters any more
-    __device__ __forceinline__ void clear() const {
-#pragma unroll
-        for (int y = 0; y <= 8; ++y) __hip_atomic_store(work + y * kWorkStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
 };
+
+// counter i of a set of counters at zero
+__device__ __forceinline__ void clear_counter(uint32_t* work, int i) {
+    __hip_atomic_store(work + i * kWorkStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__global__ void work_clear_kernel(uint32_t* work, int counters) {
+    for (int i = (int)threadIdx.x; i < counters; i += 64) clear_counter(work, i);
+}
 
 // the XCD this wave runs on: bits 3:0 of the XCC id hardware register
 __device__ __forceinline__ int xcc_id() { return __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7; }
@@ -854,13 +847,12 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     asm volatile("" : : "s"(p.q), "s"(p.k), "s"(p.v), "s"(p.o), "s"(p.idx), "s"(p.lse), "s"(p.lse_base2),
                          "s"(p.td.sb), "s"(p.td.sh), "s"(p.td.sn), "s"(p.td_kv.sb), "s"(p.td_kv.sh), "s"(p.td_kv.sn),
                          "s"(p.kv_heads), "s"(p.batch), "s"(p.heads), "s"(p.n), "s"(p.ns), "s"(p.groups),
-                         "s"(p.group_size), "s"(p.scale), "s"(p.work), "s"(p.varlen), "s"(p.idx_stride));
+                         "s"(p.group_size), "s"(p.scale), "s"(p.work), "s"(p.work_next), "s"(p.varlen), "s"(p.idx_stride));
     const int nqb = (p.n + BM - 1) / BM;
     const WorkQueues queues{p.work, p.batch * p.heads, nqb, p.varlen, p.heads, (int)gridDim.x};
     __shared__ int32_t lds_item[2];          // the workgroup's next item: queue, index in the queue
     int cur_q = (int)blockIdx.x & 7, cur_j = (int)blockIdx.x >> 3;
     int from_q = xcc_id();                   // the queue that the item after this one is taken from
-    int left_before = -1;                    // workgroups that had left when this one did
     // wave 0: settles on an item and leaves it for the others
     auto settle_item = [&](int q, int j) {
         queues.settle((int)threadIdx.x, q, j);
@@ -873,7 +865,6 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     auto read_item = [&] {
         from_q = cur_q = __builtin_amdgcn_readfirstlane(lds_item[0]);
         cur_j = __builtin_amdgcn_readfirstlane(lds_item[1]);
-        if (cur_j < 0 && threadIdx.x == 0 && queues.counted()) left_before = queues.leave();
     };
     if (cur_j >= queues.items(cur_q) || queues.is_padding(cur_q, cur_j)) {
         if (threadIdx.x < 64) settle_item(cur_q, cur_j);
@@ -1213,7 +1204,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
         if (q0 + r < n) *(u32x4*)(obase + t * group_stride) = rows_out[t];
     }
   }
-    if (left_before == (int)gridDim.x - 1) queues.clear();
+    if (blockIdx.x == 0 && threadIdx.x < kWorkCounters && p.work_next != nullptr) clear_counter(p.work_next, (int)threadIdx.x);
 }
 
 template <int D, int MODE>
@@ -1237,6 +1228,11 @@ int compute_units() {
         cached[dev] = (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
     }
     return cached[dev];
+}
+
+hipError_t launch_work_clear(uint32_t* work, int sets, hipStream_t s) {
+    hipLaunchKernelGGL(work_clear_kernel, dim3(1), dim3(64), 0, s, work, sets * kWorkCounters);
+    return hipGetLastError();
 }
 
 hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, AttnMode mode, hipStream_t s) {

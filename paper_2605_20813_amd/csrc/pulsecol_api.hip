@@ -37,7 +37,10 @@ struct pulsecol_ctx {
     int32_t cached_k = 0;           // 0 = nothing cached
     int32_t k_max = 0;              // columns per group the cache has room for
     int32_t* bad_count = nullptr;   // one device counter for the validation mode (first word of a small block)
-    uint32_t* work = nullptr;       // work counters of the bf16 attention kernels (same block)
+    // Work counters of the 256-row bf16 attention kernel (same block): kWorkSets sets that launches use in turn, each of them clearing
+    // the one that is furthest from its own turn, and a set for captured launches.
+    uint32_t* work = nullptr;
+    uint32_t work_turn = 0;
     bool validate = false;          // check column numbers in front of every pulsecol_attn
     int32_t* varlen = nullptr;      // [2 * batch] device words of variable-length batches: lengths, kept counts
     bool varlen_on = false;         // pulsecol_set_seq_lens has given per-element lengths
@@ -223,7 +226,6 @@ pulsecol::AttnParams attn_params(pulsecol_ctx* c, const void* Q, const void* K, 
     p.groups = c->groups; p.group_size = c->shape.group_size;
     p.scale = c->scale;
     p.varlen = c->varlen_on ? c->varlen : nullptr;
-    p.work = c->work;
     return p;
 }
 
@@ -258,11 +260,36 @@ int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
     return 32;
 }
 
-hipError_t launch_attn(const pulsecol_ctx* c, const pulsecol::AttnParams& p, pulsecol::AttnMode mode, hipStream_t s) {
-    if (mode == pulsecol::kSparse && c->shape.dtype == PULSECOL_BF16 && sparse_block_m(c, p.ns) < pulsecol::kBlockM_bf16)
+// The 256-row bf16 kernel, with counters that are zero when it starts whatever became of the launches before it: a set that the
+// fourth launch before this one has cleared.  (Up to four launches that overlap, which the interface forbids, share nothing; and no launch
+// leaves anything behind for more than four others.)  A captured launch runs as often as its graph does: its set
+// is cleared by a fill in front of it.
+constexpr int kWorkSets = 8;
+hipError_t launch_scheduled(pulsecol_ctx* c, pulsecol::AttnParams p, pulsecol::AttnMode mode, hipStream_t s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {          // (the launch itself says what is wrong)
+        capture = hipStreamCaptureStatusNone;
+        (void)hipGetLastError();
+    }
+    const bool captured = capture != hipStreamCaptureStatusNone;
+    hipError_t e = hipSuccess;
+    if (captured) {
+        p.work = c->work + kWorkSets * pulsecol::kWorkWords;
+        e = pulsecol::launch_work_clear(p.work, 1, s);
+    } else {
+        p.work = c->work + c->work_turn % kWorkSets * pulsecol::kWorkWords;
+        p.work_next = c->work + (c->work_turn + kWorkSets / 2) % kWorkSets * pulsecol::kWorkWords;
+    }
+    if (e == hipSuccess) e = pulsecol::launch_attn_bf16(p, c->shape.head_dim, mode, s);
+    if (e == hipSuccess && !captured) ++c->work_turn;
+    return e;
+}
+
+hipError_t launch_attn(pulsecol_ctx* c, const pulsecol::AttnParams& p, pulsecol::AttnMode mode, hipStream_t s) {
+    if (c->shape.dtype != PULSECOL_BF16) return pulsecol::launch_attn_f32(p, c->shape.head_dim, mode, s);
+    if (mode == pulsecol::kSparse && sparse_block_m(c, p.ns) < pulsecol::kBlockM_bf16)
         return pulsecol::launch_attn_bf16_group(p, c->shape.head_dim, sparse_block_m(c, p.ns), s);
-    return c->shape.dtype == PULSECOL_BF16 ? pulsecol::launch_attn_bf16(p, c->shape.head_dim, mode, s)
-                                           : pulsecol::launch_attn_f32(p, c->shape.head_dim, mode, s);
+    return launch_scheduled(c, p, mode, s);
 }
 
 pulsecol_status check_ptrs(pulsecol_ctx* ctx, std::initializer_list<const void*> tensors, const char* who) {
@@ -407,8 +434,8 @@ pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape,
     hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, score_words(c, kMostFloats, kPaddedFloats) * sizeof(float)) : e1;
     c->k_max = shape->max_keep_ratio > 0.0 ? pulsecol_num_keep(shape->seq, shape->max_keep_ratio) : shape->seq;
     hipError_t e3 = e2 == hipSuccess ? hipMalloc((void**)&c->cached_idx, rows * c->groups * (size_t)c->k_max * sizeof(int32_t)) : e2;
-    // the validation mode's counter in a line of its own, then the attention kernels', which are zero between launches
-    constexpr size_t kCounterBytes = (pulsecol::kWorkStride + pulsecol::kWorkWords) * sizeof(uint32_t);
+    // the validation mode's counter in a line of its own, then the attention kernels'
+    constexpr size_t kCounterBytes = (pulsecol::kWorkStride + (kWorkSets + 1) * pulsecol::kWorkWords) * sizeof(uint32_t);
     if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->varlen, 2 * (size_t)shape->batch * sizeof(int32_t));
     if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->bad_count, kCounterBytes);
     if (e3 == hipSuccess) e3 = hipMemset(c->bad_count, 0, kCounterBytes);
@@ -682,7 +709,7 @@ pulsecol_status pulsecol_attn_block(pulsecol_ctx* ctx, const void* Q, const void
     }
     pulsecol::AttnParams p = attn_params(ctx, Q, K, V, O, block_idx, kb * pulsecol::kBlockN_bf16, nullptr, 0);
     p.idx_stride = kb;
-    const hipError_t e = pulsecol::launch_attn_bf16(p, ctx->shape.head_dim, pulsecol::kBlock, (hipStream_t)stream);
+    const hipError_t e = launch_scheduled(ctx, p, pulsecol::kBlock, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(ctx, e, "block-sparse attention kernel");
     return PULSECOL_OK;
 }

@@ -29,16 +29,18 @@ struct AttnParams {
     int32_t group_size;      // rows per group, a multiple of the kernel's query block (unused when U = 1)
     float scale;             // logit scale
     // bf16 kernel with 256-row query blocks only: kWorkWords words of device memory through which its workgroups hand
-    // out the query blocks, zero between launches (a launch clears what it used)
+    // out the query blocks, zero when the launch starts and left as they are when it ends; and as many that the launch
+    // sets to zero for a later one (nullptr: none)
     uint32_t* work;
+    uint32_t* work_next;
     // variable-length batches: device array [2 * batch] -- per batch element its own sequence length
     // (<= n), then the number of leading entries of its column sets that count (<= ns); nullptr: every
     // element has n rows and ns columns.  Rows and key positions beyond an element's length are padding.
     const int32_t* varlen;
 };
 
-// eight counters and the number of workgroups that are done, each in a memory line of its own
-constexpr int kWorkStride = 64, kWorkWords = 9 * kWorkStride;
+// eight counters, each in a memory line of its own
+constexpr int kWorkCounters = 8, kWorkStride = 64, kWorkWords = kWorkCounters * kWorkStride;
 
 struct ScoreParams {
     const void* q;
@@ -125,6 +127,8 @@ inline dim3 row_grid(int32_t rows) {
 int compute_units();
 
 hipError_t launch_attn_bf16(const AttnParams& p, int head_dim, AttnMode mode, hipStream_t s);
+// the counters of `sets` consecutive sets of kWorkWords words at zero
+hipError_t launch_work_clear(uint32_t* work, int sets, hipStream_t s);
 // column-sparse attention with query blocks of block_m = 32, 64 or 128 rows (small query groups)
 hipError_t launch_attn_bf16_group(const AttnParams& p, int head_dim, int block_m, hipStream_t s);
 hipError_t launch_attn_f32(const AttnParams& p, int head_dim, AttnMode mode, hipStream_t s);

@@ -171,7 +171,11 @@ def select_noalloc(shape: Shape, Q, K, keep_ratio: float, idx_out):
 
 
 class Context:
-    """Owns one pulsecol_ctx.  Tensors are [B, H, n, d] on the context's device."""
+    """Owns one pulsecol_ctx.  Tensors are [B, H, n, d] on the context's device.
+
+    Calls run on the current stream.  Two calls on one context (replays of captured ones among them) must not overlap: a
+    program that changes streams between them orders the streams itself.
+    """
 
     def __init__(self, batch, heads, seq, head_dim, dtype, group_size=0, strides=(0, 0, 0), scale=0.0, device=0,
                  kv_heads=0, kv_strides=(0, 0, 0), max_keep_ratio=0.0):

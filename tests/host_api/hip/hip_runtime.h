@@ -16,6 +16,7 @@ struct dim3 {
 };
 typedef void* hipStream_t;
 enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorInvalidSymbol = 13 };
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1, hipStreamCaptureStatusInvalidated = 2 };
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3 };
 
 hipError_t hipMalloc(void** p, size_t bytes);
@@ -23,6 +24,7 @@ hipError_t hipFree(void* p);
 hipError_t hipMemset(void* p, int value, size_t bytes);
 hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind kind, hipStream_t s);
 hipError_t hipStreamSynchronize(hipStream_t s);
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);
 hipError_t hipGetDevice(int* d);
 hipError_t hipSetDevice(int d);
 hipError_t hipGetDeviceCount(int* n);

@@ -139,3 +139,56 @@ def test_one_launch_stores_64_lengths(api, batch):
     assert api.fake_length_stores() - stores == -(-batch // 64)
     assert api.fake_outside() == outside
     ctx.close()
+
+
+class Scheduled(Ctx):
+    """A context whose attention calls run in the 256-row kernel."""
+
+    def __init__(self, api, **kw):
+        super().__init__(api, MANY, 1, 2, 1024, 128, torch.bfloat16, **kw)
+        assert api.pulsecol_set_attn_block(self.h, 256) == pc.OK
+
+    def call(self, i=0):
+        fake = ctypes.c_void_p(1 << 20)
+        if i % 3 == 0:
+            return self.api.pulsecol_attn(self.h, fake, fake, fake, fake, 100, fake, None)
+        if i % 3 == 1:
+            return self.api.pulsecol_attn_dense(self.h, fake, fake, fake, fake, None, None)
+        return self.api.pulsecol_attn_block(self.h, fake, fake, fake, fake, 4, fake, None)
+
+
+def test_every_launch_finds_its_counters_at_zero(api):
+    """Whatever the launches before it left: direct calls, replays of captured ones in between, launches that failed."""
+    ctx = Scheduled(api)
+    stale, outside, launched = api.fake_stale(), api.fake_outside(), api.fake_scheduled()
+    for i in range(20):
+        assert ctx.call(i) == pc.OK
+    api.fake_capture(1)
+    for i in range(3):
+        assert ctx.call(i) == pc.OK
+    api.fake_capture(0)
+    for i in range(20):
+        api.fake_replay()
+        if i % 3:
+            assert ctx.call(i) == pc.OK
+        if i % 4 == 1:
+            api.fake_fail_after(0)
+            assert ctx.call(i) == pc.ERR_HIP
+            api.fake_fail_after(-1)
+    assert api.fake_scheduled() - launched == 20 + 3 * 20 + 13
+    assert api.fake_stale() == stale and api.fake_outside() == outside
+    ctx.close()
+
+
+def test_a_context_used_under_capture_first(api):
+    ctx = Scheduled(api)
+    stale = api.fake_stale()
+    api.fake_capture(1)
+    assert ctx.call() == pc.OK
+    api.fake_capture(0)
+    for i in range(10):
+        assert ctx.call(i) == pc.OK
+    for _ in range(3):
+        api.fake_replay()
+    assert api.fake_stale() == stale
+    ctx.close()
