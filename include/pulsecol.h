@@ -115,7 +115,7 @@ PULSECOL_API pulsecol_status pulsecol_validate_shape(const pulsecol_shape* shape
  * cached pattern with k_max = pulsecol_num_keep(seq, max_keep_ratio), 18688 bytes of counters; shapes
  * whose grids leave part of the chip idle: partial results of the scoring passes, at most 64 MiB together with the
  * row statistics and the scores, and at most 16 MiB for the ragged lengths of a padded batch).
- * *out is set only on PULSECOL_OK. */
+ * Enqueues nothing and waits for nothing.  *out is set only on PULSECOL_OK. */
 PULSECOL_API pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape, int device);
 
 /* Validation mode (off by default; on at creation if the environment variable

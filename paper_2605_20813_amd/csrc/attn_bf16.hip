@@ -786,10 +786,14 @@ struct WorkQueues {
         const int qblk = j - head_block * nqb;
         return qblk * BM >= varlen[(head_block * 8 + q) / heads];
     }
-    // one lane: the next item of queue q (items(q) or more: there is none left)
+    // items of queue q that its counter hands out.  (A counter is compared with them unsigned: whatever it holds, an item lies in its
+    // queue and a launch ends.)
+    __device__ __forceinline__ uint32_t counted(int q) const { return (uint32_t)(items(q) - dealt(q)); }
+    // one lane: the next item of queue q (items(q): there is none left)
     __device__ __forceinline__ int take(int q) const {
-        if (dealt(q) == items(q)) return items(q);
-        return dealt(q) + (int)__hip_atomic_fetch_add(work + q * kWorkStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (counted(q) == 0u) return items(q);
+        const uint32_t before = __hip_atomic_fetch_add(work + q * kWorkStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return before < counted(q) ? dealt(q) + (int)before : items(q);
     }
     // One wave: item j taken from queue q is good, or else the next one that it or the queues behind it still have; j = -1 when
     // every queue has been found empty.
@@ -799,8 +803,8 @@ struct WorkQueues {
                 if (!is_padding(q, j)) return;          // (nothing to do for a block of padding rows: on to the next item)
             } else {
                 const int y = lane & 7;
-                bool some = dealt(y) < items(y);
-                if (some) some = dealt(y) + (int)__hip_atomic_load(work + y * kWorkStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < items(y);
+                bool some = counted(y) != 0u;
+                if (some) some = __hip_atomic_load(work + y * kWorkStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < counted(y);
                 const uint32_t left = (uint32_t)__ballot(some) & 0xFFu;
                 if (left == 0) { j = -1; return; }
                 q = (q + __builtin_ctz((left | left << 8) >> q)) & 7;

@@ -41,6 +41,7 @@ struct pulsecol_ctx {
     // the one that is furthest from its own turn, and a set for captured launches.
     uint32_t* work = nullptr;
     uint32_t work_turn = 0;
+    bool work_cleared = false;      // the first launch that is not captured has cleared the sets for those behind it
     bool validate = false;          // check column numbers in front of every pulsecol_attn
     int32_t* varlen = nullptr;      // [2 * batch] device words of variable-length batches: lengths, kept counts
     bool varlen_on = false;         // pulsecol_set_seq_lens has given per-element lengths
@@ -261,9 +262,10 @@ int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
 }
 
 // The 256-row bf16 kernel, with counters that are zero when it starts whatever became of the launches before it: a set that the
-// fourth launch before this one has cleared.  (Up to four launches that overlap, which the interface forbids, share nothing; and no launch
-// leaves anything behind for more than four others.)  A captured launch runs as often as its graph does: its set
-// is cleared by a fill in front of it.
+// fourth launch before this one has cleared, or a fill in front of the context's first one.  (Cleared when the context is made they would
+// have to be waited for: nothing orders that against the stream of the first call.)  Launches that overlap, which the interface
+// forbids, leave nothing behind for more than four others.  A captured launch runs as often as its graph does: its set is
+// cleared by a fill in front of it.
 constexpr int kWorkSets = 8;
 hipError_t launch_scheduled(pulsecol_ctx* c, pulsecol::AttnParams p, pulsecol::AttnMode mode, hipStream_t s) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -277,6 +279,8 @@ hipError_t launch_scheduled(pulsecol_ctx* c, pulsecol::AttnParams p, pulsecol::A
         p.work = c->work + kWorkSets * pulsecol::kWorkWords;
         e = pulsecol::launch_work_clear(p.work, 1, s);
     } else {
+        if (!c->work_cleared) e = pulsecol::launch_work_clear(c->work, kWorkSets, s);
+        c->work_cleared = e == hipSuccess;
         p.work = c->work + c->work_turn % kWorkSets * pulsecol::kWorkWords;
         p.work_next = c->work + (c->work_turn + kWorkSets / 2) % kWorkSets * pulsecol::kWorkWords;
     }
@@ -434,12 +438,10 @@ pulsecol_status pulsecol_create(pulsecol_ctx** out, const pulsecol_shape* shape,
     hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&c->scores, score_words(c, kMostFloats, kPaddedFloats) * sizeof(float)) : e1;
     c->k_max = shape->max_keep_ratio > 0.0 ? pulsecol_num_keep(shape->seq, shape->max_keep_ratio) : shape->seq;
     hipError_t e3 = e2 == hipSuccess ? hipMalloc((void**)&c->cached_idx, rows * c->groups * (size_t)c->k_max * sizeof(int32_t)) : e2;
-    // the validation mode's counter in a line of its own, then the attention kernels'
+    // the validation mode's counter in a line of its own, then the attention kernels'; cleared by the launches that use them
     constexpr size_t kCounterBytes = (pulsecol::kWorkStride + (kWorkSets + 1) * pulsecol::kWorkWords) * sizeof(uint32_t);
     if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->varlen, 2 * (size_t)shape->batch * sizeof(int32_t));
     if (e3 == hipSuccess) e3 = hipMalloc((void**)&c->bad_count, kCounterBytes);
-    if (e3 == hipSuccess) e3 = hipMemset(c->bad_count, 0, kCounterBytes);
-    if (e3 == hipSuccess) e3 = hipStreamSynchronize(nullptr);         // (streams that do not wait for the default one)
     if (e3 == hipSuccess) c->work = reinterpret_cast<uint32_t*>(c->bad_count) + pulsecol::kWorkStride;
     if (e3 != hipSuccess) {
         if (c->lse) (void)hipFree(c->lse);

@@ -14,7 +14,7 @@ namespace {
 int current = 0;
 const int kUnits[2] = {64, 256};
 std::map<char*, size_t> blocks;
-int row_splits = 0, outside = 0, length_stores = 0, stale = 0, scheduled = 0, fail_after = -1;
+int row_splits = 0, outside = 0, length_stores = 0, stale = 0, scheduled = 0, fail_after = -1, waits = 0;
 bool capturing = false;
 std::vector<std::function<void()>> graph;
 
@@ -35,11 +35,16 @@ void touch(const void* p, size_t bytes) {
 }
 }  // namespace
 
-hipError_t hipMalloc(void** p, size_t bytes) { *p = std::malloc(bytes); blocks[(char*)*p] = bytes; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t bytes) {
+    *p = std::malloc(bytes);
+    std::memset(*p, 0xA5, bytes);
+    blocks[(char*)*p] = bytes;
+    return hipSuccess;
+}
 hipError_t hipFree(void* p) { blocks.erase((char*)p); std::free(p); return hipSuccess; }
-hipError_t hipMemset(void* p, int value, size_t bytes) { std::memset(p, value, bytes); return hipSuccess; }
+hipError_t hipMemset(void* p, int value, size_t bytes) { ++waits; std::memset(p, value, bytes); return hipSuccess; }
 hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind, hipStream_t) { std::memcpy(to, from, bytes); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { ++waits; return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* status) {
     *status = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
@@ -56,6 +61,7 @@ int fake_row_splits() { return row_splits; }
 int fake_outside() { return outside; }
 int fake_device() { return current; }
 int fake_stale() { return stale; }
+int fake_waits() { return waits; }            // host waits, and work on the default stream
 int fake_scheduled() { return scheduled; }
 void fake_fail_after(int launches) { fail_after = launches; }
 void fake_capture(int on) { capturing = on != 0; if (on) graph.clear(); }

@@ -192,3 +192,19 @@ def test_a_context_used_under_capture_first(api):
         api.fake_replay()
     assert api.fake_stale() == stale
     ctx.close()
+
+
+def test_create_waits_for_nothing(api):
+    """Nothing on the default stream and no wait, in the creation of a context and in its first calls."""
+    waits, stale = api.fake_waits(), api.fake_stale()
+    ctx = Scheduled(api)
+    assert api.fake_waits() == waits
+    api.fake_fail_after(0)                       # the fill in front of the first launch fails, then the launch behind it
+    assert ctx.call() == pc.ERR_HIP
+    api.fake_fail_after(1)
+    assert ctx.call() == pc.ERR_HIP
+    api.fake_fail_after(-1)
+    for i in range(10):
+        assert ctx.call(i) == pc.OK
+    assert api.fake_waits() == waits and api.fake_stale() == stale
+    ctx.close()
