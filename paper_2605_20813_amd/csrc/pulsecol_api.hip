@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "attn_choice.h"
 #include "pulsecol_kernels.h"
 
 struct pulsecol_ctx {
@@ -45,6 +46,7 @@ struct pulsecol_ctx {
     bool validate = false;          // check column numbers in front of every pulsecol_attn
     int32_t* varlen = nullptr;      // [2 * batch] device words of variable-length batches: lengths, kept counts
     bool varlen_on = false;         // pulsecol_set_seq_lens has given per-element lengths
+    pulsecol::AttnJob job{};        // what an attention call has to do with the present lengths
     int attn_block = 0;             // 0: the cost model picks the one-set-per-head kernel; 256 / 128: the caller has
     std::string last_error;
 };
@@ -139,6 +141,7 @@ void derive_from_shape(pulsecol_ctx* c, const pulsecol_shape* shape, int device)
     c->td.sh = shape->stride_h ? shape->stride_h : (int64_t)shape->seq * c->td.sn;
     c->td.sb = shape->stride_b ? shape->stride_b : (int64_t)shape->heads * c->td.sh;
     c->kv_heads = shape->kv_heads ? shape->kv_heads : shape->heads;
+    c->job = pulsecol::attn_job(shape->batch, shape->heads, shape->seq, nullptr);
     if (kv_follows_q(shape)) {
         c->td_kv = c->td;
     } else {
@@ -231,31 +234,14 @@ pulsecol::AttnParams attn_params(pulsecol_ctx* c, const void* Q, const void* K, 
 }
 
 // Query rows per workgroup of the column-sparse kernel a call with ns kept columns runs in.  Group-wise
-// sets: the largest block that divides the group size.  One set per head: the hand-scheduled kernel
-// with 256-row blocks, except for short jobs, where the start and end of a block (one workgroup per CU: nothing else covers
-// them) outweigh its faster steady state and the plain kernel
-// with 128-row blocks, two to a CU, finishes first.  The rule is a two-line cost model per head dimension
-// (microseconds; R = 256-row blocks per CU, r = rounds of them, t = 64-column tiles), fitted to launches of 4 to 32 heads at 1K to 32K
-// context and keep 5 to 20%; on those it picks the slower kernel only where the two are within 3% of each other.
-//   D = 128  scheduled 2 + r (9.4 + 1.46 t)    plain 1 + R (6.2 + 1.9 t)
-//   D = 64   scheduled 2 + r (6.5 + 0.93 t)    plain 1.5 + R (2.6 + 1.19 t)
-// D = 128, 32 heads, keep 10%, plain / scheduled: 4K 38.7 / 42.9 us, 8K 123 / 115, 16K 434 / 365, keep 5% 243 / 223; 8 heads of 8K, keep
-// 20%, 58 / 51.
+// sets: the largest block that divides the group size.  One set per head: attn_choice.h.
 int sparse_block_m(const pulsecol_ctx* c, int32_t ns) {
     if (c->shape.dtype != PULSECOL_BF16)
         return pulsecol::block_rows_f32(pulsecol::kSparse, c->shape.head_dim, c->shape.seq, (int64_t)c->shape.batch * c->shape.heads,
                                         pulsecol::compute_units());
     if (c->groups == 1) {
         if (c->attn_block != 0) return c->attn_block;
-        const double blocks = (double)((c->shape.seq + 255) / 256) * c->shape.batch * c->shape.heads;
-        const double R = blocks / (double)pulsecol::compute_units();
-        const double t = (double)((ns + 63) / 64);
-        const bool wide = c->shape.head_dim == 128;
-        // whole blocks are handed out, by a queue: with many to a CU the last round is half empty on average
-        const double r = std::fmin(std::ceil(R), R + 0.5);
-        const double scheduled = wide ? 2.0 + r * (9.4 + 1.46 * t) : 2.0 + r * (6.5 + 0.93 * t);
-        const double plain = wide ? 1.0 + R * (6.2 + 1.9 * t) : 1.5 + R * (2.6 + 1.19 * t);
-        return plain < scheduled ? 128 : pulsecol::kBlockM_bf16;
+        return pulsecol::plain_attn_is_faster(c->job, ns, c->shape.head_dim, pulsecol::compute_units()) ? 128 : pulsecol::kBlockM_bf16;
     }
     for (int bm : {256, 128, 64}) if (c->shape.group_size % bm == 0) return bm;
     return 32;
@@ -479,6 +465,7 @@ pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens
     if (!ctx) return fail(nullptr, PULSECOL_ERR_INVALID_ARG, "pulsecol_set_seq_lens: ctx is NULL");
     if (!seq_lens) {
         ctx->varlen_on = false;
+        ctx->job = pulsecol::attn_job(ctx->shape.batch, ctx->shape.heads, ctx->shape.seq, nullptr);
         ctx->plan = ctx->fixed_plan;                 // what the scratch was sized for
         return PULSECOL_OK;
     }
@@ -498,6 +485,7 @@ pulsecol_status pulsecol_set_seq_lens(pulsecol_ctx* ctx, const int32_t* seq_lens
         if (e != hipSuccess) { ctx->varlen_on = false; return fail_hip(ctx, e, "pulsecol_set_seq_lens: storing the lengths"); }
     }
     ctx->varlen_on = true;
+    ctx->job = pulsecol::attn_job(B, ctx->shape.heads, ctx->shape.seq, seq_lens);
     ctx->plan = score_plan(ctx, seq_lens);
     if (!ctx->room) ctx->plan.splits = 1;
     ctx->cached_k = 0;            // a cached pattern belongs to the lengths it was selected with

@@ -208,3 +208,40 @@ def test_create_waits_for_nothing(api):
         assert ctx.call(i) == pc.OK
     assert api.fake_waits() == waits and api.fake_stale() == stale
     ctx.close()
+
+
+# head dimension, heads, rows, kept columns, measured time (us) of the plain and of the scheduled kernel on 256 compute units; the elements'
+# lengths of a padded batch
+ATTN_MEASURED = [
+    (128, 1, 39360, 9840, 228.6, 174.3, None), (128, 1, 49088, 4908, 131.2, 104.8, None), (128, 1, 49088, 9817, 244.4, 195.7, None),
+    (64, 1, 39360, 7872, 126.4, 102.5, None), (128, 2, 19648, 2947, 75.6, 61.8, None), (128, 24, 6848, 1712, 154.2, 127.2, None),
+    (128, 10, 22976, 1148, 145.2, 124.7, None), (128, 4, 9664, 2416, 62.4, 53.8, None), (64, 2, 24512, 4902, 84.3, 71.3, None),
+    (128, 2, 49088, 12272, 557.7, 482.4, None), (64, 6, 27328, 4099, 216.7, 194.3, None), (128, 10, 13760, 3440, 245.0, 223.7, None),
+    (128, 1, 72128, 10819, 448.5, 413.1, None), (128, 1, 98240, 6876, 313.1, 282.3, None), (128, 32, 3520, 880, 64.5, 57.4, None),
+    (64, 4, 16320, 1632, 34.7, 37.8, None), (64, 4, 16320, 816, 20.3, 26.4, None), (128, 4, 14784, 739, 28.8, 33.2, None),
+    (64, 4, 14784, 1034, 23.6, 30.3, None), (128, 8, 4032, 403, 14.5, 18.9, None), (64, 8, 4032, 403, 9.1, 12.8, None),
+    (128, 32, 4096, 409, 38.7, 42.9, None), (128, 32, 8192, 819, 123.0, 115.0, None), (128, 32, 16384, 1638, 434.0, 365.0, None),
+    (64, 4, 10827, 2165, 153.3, 101.9, (10827, 5415, 5175, 3807, 9992, 2743, 7407, 3696)), (128, 2, 4310, 1077, 36.0, 32.1, (4310, 2469, 2806, 3779, 1801, 651, 385, 920)),
+    (128, 8, 7689, 768, 41.1, 45.3, (7689, 3711, 497)), (64, 2, 10501, 1575, 46.5, 39.5, (10501, 9044, 10285, 2197)),
+    (64, 8, 6190, 309, 23.8, 33.9, (6190, 5853, 1304, 5174)), (128, 32, 1467, 73, 43.8, 56.4, (1467, 1319, 1466, 798, 873, 835, 381, 1139)),
+]
+
+
+@pytest.mark.parametrize("d,heads,n,k,plain,scheduled,lens", ATTN_MEASURED)
+def test_the_kernel_of_an_attention_call_is_near_the_better_one(api, d, heads, n, k, plain, scheduled, lens):
+    api.fake_set_device(FEW)                     # the rule counts the compute units of the context's device
+    ctx = Ctx(api, MANY, len(lens) if lens else 1, heads, n, d, torch.bfloat16)
+    m, c = ctypes.c_int32(), ctypes.c_int32()
+    times = {128: plain, 256: scheduled}
+
+    def chosen():
+        assert api.pulsecol_attn_tile_shape(ctx.h, k, ctypes.byref(m), ctypes.byref(c)) == pc.OK
+        return times[m.value]
+
+    whole = chosen()
+    if lens:
+        assert ctx.set_seq_lens(lens) == pc.OK
+    assert chosen() <= 1.1 * min(plain, scheduled)       # (what the rule leaves on all but 0.5% of the calls that it was fitted to)
+    assert ctx.set_seq_lens(None) == pc.OK       # back to full lengths
+    assert chosen() == whole
+    ctx.close()
