@@ -189,6 +189,7 @@ PULSECOL_API pulsecol_status pulsecol_topk(pulsecol_ctx* ctx, const float* score
  * group u, O_i = softmax over the k logits {q_i . k_j * scale : j in idx[b,h,u,:]} applied to
  * the same rows of V -- equal to the masked form softmax(Z + M(S)) V of Sec. 3.1.  Online
  * softmax over tiles of gathered K/V rows; nothing of size seq x seq or seq x k is written.
+ * bf16 (dense and block-sparse attention too): weights below 2^-117 of the largest one of a row count as zero.
  * 1 <= k <= seq.  O has the layout and dtype of Q. */
 PULSECOL_API pulsecol_status pulsecol_attn(pulsecol_ctx* ctx, const void* Q, const void* K, const void* V,
                               const int32_t* idx, int32_t k, void* O, void* stream);

@@ -29,7 +29,7 @@
 // (staged through LDS) and the first K tile, and the last tile still goes through a scheduled
 // iteration.  The reference maximum is raised
 // lazily and after the fact: P is formed against the current reference, and only when a
-// lane's row sum of the half-tile exceeds 2^kTau (or is not finite) does the wave take the
+// lane's row sum of the half-tile exceeds kAttnGrowthLimit (or is not finite) does the wave take the
 // slow path that finds the true maximum, moves the reference by a whole number of log2
 // units, rescales l and the accumulator by that exact power of two and recomputes P.  The
 // result is exact either way (numerator and denominator carry the same factor); the fast
@@ -47,6 +47,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "attn_reference.h"
 #include "pulsecol_device.h"
 #include "pulsecol_kernels.h"
 
@@ -61,17 +62,6 @@ constexpr int NBUF = 4;            // LDS tile slots for K and for V: tile t liv
 constexpr int NBUF_K = NBUF;
 constexpr int NBUF_V = NBUF;
 constexpr int PRO_TILES = 3;       // K tiles requested by the prologue (the loop loads tile PRO_TILES first)
-constexpr float kTau = 8.0f;       // log2 of the growth allowed before the reference max is raised
-constexpr float kGrowthLimit = 256.0f;   // 2^kTau
-// Log2 units by which a reference is set above the maximum that it is taken from.  The first 32 kept keys say little about the
-// largest logit of a row: against their maximum alone some lane of a wave outgrew its reference in most of the first
-// tiles of a block, at some 2000 ticks for all four waves.  Weights, sums and accumulators are floats that all carry the same
-// power of two, so that only weights below 2^-118 of the largest are lost.  A whole number, so that a weight is rounded to
-// sixteen bits as it was.  The dense kernel's reference goes into the row log-sum-exp (rms error against 64 bits, 2 heads of 4096 rows,
-// 4.5e-7 -> 3.8e-7, of 8192 4.6e-7 -> 4.0e-7, of 3001 with logits three times as steep 1.22e-6 -> 1.24e-6).
-// 0 / 3 / 5 / 8 units: 64K keep 10% 5348 / 5187 / 5123 / 5107 us, 32K keep 20% 2698 / 2609 / 2559 / 2546, refresh_dense of 16K 5089 /
-// 5011 / 4959 / 4934.
-constexpr float kHeadroom = 8.0f;
 
 typedef unsigned char byte;
 
@@ -490,8 +480,7 @@ struct AttnWave {
     template <bool SCHEDULED>
     __device__ __forceinline__ void exp_end(ExpPipe& ep, const f32x16 (&S)[2], bf16x8 (&P)[2][2]) {
         if (!SCHEDULED) {
-            const float limit = __builtin_amdgcn_exp2f(kTau);
-            ep.bad = __ballot(!(ep.rs[0] <= limit) || !(ep.rs[1] <= limit));
+            ep.bad = __ballot(!(ep.rs[0] <= kAttnGrowthLimit) || !(ep.rs[1] <= kAttnGrowthLimit));
         }
         if (__builtin_expect(ep.bad != 0ull, 0)) fix_reference(ep, S, P);
         l_run[0] += ep.rs[0];
@@ -506,9 +495,9 @@ struct AttnWave {
             const float m2 = half_tile_max(S[qb]) * c2;        // same value in both half-waves
             if (m2 > mc[qb] + 1.0f) {
                 const bool first = mc[qb] == -INFINITY;
-                const float steps = first ? 0.f : ceilf(m2 - mc[qb]) + kHeadroom;
+                const float steps = first ? 0.f : ceilf(m2 - mc[qb]) + kAttnHeadroom;
                 const float alpha = first ? 0.f : fast_exp2(-steps);
-                mc[qb] = first ? m2 + kHeadroom : mc[qb] + steps;
+                mc[qb] = first ? m2 + kAttnHeadroom : mc[qb] + steps;
                 l_run[qb] *= alpha;
                 // one block at a time, pinned inside this branch: the accumulator passes through
                 // VGPRs, and all of it at once does not fit beside the rest of the loop's registers
@@ -705,7 +694,7 @@ struct AttnWave {
             // integer maximum needs no canonicalising copies of its operands.)
             if (s == NS - 2) {
                 const uint32_t r0 = __builtin_bit_cast(uint32_t, ep.rs[0]), r1 = __builtin_bit_cast(uint32_t, ep.rs[1]);
-                ep.bad = __ballot((r0 > r1 ? r0 : r1) > __builtin_bit_cast(uint32_t, kGrowthLimit));
+                ep.bad = __ballot((r0 > r1 ? r0 : r1) > __builtin_bit_cast(uint32_t, kAttnGrowthLimit));
             }
             fence();
         }
@@ -760,9 +749,11 @@ struct AttnWave {
 // until the slowest XCD is done.
 // The first blocks are dealt by workgroup id, the k-th of queue y to workgroup 8*k + y (ids go round-robin over the XCDs);
 // the others are handed out by a counter per queue, from the queue of the XCD the workgroup runs on (read from the
-// hardware's XCC id register).  Nothing waits for a counter at the start of a launch, and at its end one look at all
-// eight counters tells what is left: an atomic round trip to memory takes about a microsecond, more where 32
-// workgroups ask for the same word, and when the first block came from the counters as well and a workgroup asked the empty
+// hardware's XCC id register).  Where every queue holds a block for each of its workgroups, nothing waits for a counter at the start of
+// a launch.  (With fewer than eight heads, other numbers that are no multiple of eight in a launch of a few rounds, or blocks of
+// padding, the workgroups of the short queues ask a counter first, all of them that of the next queue that holds something: some 3 us, half the chip with four
+// heads.)  At its end one look at all eight counters tells what is left: an atomic round trip to memory takes about a microsecond, more where
+// many workgroups ask for the same word, and when the first block came from the counters as well and a workgroup asked the empty
 // queues one after the other, a launch spent 10 us in front of its first load and 15 to 20 behind its last product
 // (32 heads of 4096 rows, keep 10%: 68 -> 42 us; 8 heads of 8192 rows, keep 20%, 80 -> 51).
 // The counters are zero when a launch starts, and it does not matter how it leaves them: the host gives every launch a set
@@ -1062,7 +1053,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
     // The first half-tile sets the softmax reference directly (it is no less than the maximum seen so far, so no term
     // can overflow), which keeps the first step off the slow reference-update path.
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) w.mc[qb] = w.half_tile_max(SA[qb]) * w.c2 + kHeadroom;
+    for (int qb = 0; qb < 2; ++qb) w.mc[qb] = w.half_tile_max(SA[qb]) * w.c2 + kAttnHeadroom;
 
     // j = 0: S(0) in SA -> P(0) in PA, S(1) in SB
     w.general_step(0, lds_k, lds_v, SA, SB, PB, PA);

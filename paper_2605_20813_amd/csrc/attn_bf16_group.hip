@@ -36,6 +36,7 @@
 // workgroup each.
 #include <utility>
 
+#include "attn_reference.h"
 #include "pulsecol_device.h"
 #include "pulsecol_kernels.h"
 
@@ -46,11 +47,6 @@ typedef unsigned char byte;
 
 constexpr int BN = 32;      // gathered rows per tile
 constexpr int NBUF = 3;     // LDS tile slots per operand: one being read, two on their way
-constexpr float kGrowthLimit = 256.0f;      // 2^kTau with kTau = 8, as in the main kernel
-// log2 units by which a reference is set above the maximum that it is taken from: the first tile's alone is outgrown in
-// most of the next tiles by some lane of a wave (attn_bf16.hip).  32 heads of 4096 rows, keep 10%, 37.6 -> 35.3 us, 4 heads of 8192
-// 20.4 -> 18.6, groups of 128 at 32 heads of 8192 138.6 -> 132.7.
-constexpr float kHeadroom = 8.0f;
 constexpr float kNoReference = -1e30f;      // of a query whose first tile holds no finite logit: the tile adds nothing
 
 // s_waitcnt vmcnt(v) with the other counters left alone (gfx9 encoding: vmcnt in [3:0] and [15:14])
@@ -233,15 +229,15 @@ struct GroupWave {
     // accumulator scaled by that exact power of two, P recomputed.  Every product that adds an earlier tile's P to
     // the accumulator has been issued.
     __device__ __forceinline__ void close_tile(const f32x16& s, u32x4 (&P)[2], Sums sm) {
-        if (__builtin_expect(__ballot(!(sm.rs <= kGrowthLimit)) != 0ull, 0)) {
+        if (__builtin_expect(__ballot(!(sm.rs <= kAttnGrowthLimit)) != 0ull, 0)) {
             float mx = s[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
             const float m2 = half_max(mx) * c2;              // same value in both half-waves
             if (m2 > ref + 1.0f) {
-                const float steps = ceilf(m2 - ref) + kHeadroom;
+                const float steps = ceilf(m2 - ref) + kAttnHeadroom;
                 const float alpha = fast_exp2(-steps);
-                ref = ref == kNoReference ? m2 + kHeadroom : ref + steps;         // (no finite logit so far: alpha is zero)
+                ref = ref == kNoReference ? m2 + kAttnHeadroom : ref + steps;         // (no finite logit so far: alpha is zero)
                 l_run *= alpha;
                 mfma_settle(o_acc);
 #pragma unroll
@@ -569,7 +565,7 @@ attn_bf16_group_kernel(AttnParams p) {
         float mx = sa[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sa[r]);
-        w.ref = fmaxf(half_max(mx) * w.c2 + kHeadroom, kNoReference);
+        w.ref = fmaxf(half_max(mx) * w.c2 + kAttnHeadroom, kNoReference);
     }
     // Two teams: both weigh against the reference that team 0 takes from the block's first tile, handed over behind the
     // next barrier.  A weight then has the same bits whichever team forms it, in this form of the kernel or in the one

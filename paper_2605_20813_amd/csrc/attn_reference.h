@@ -1,0 +1,23 @@
+// The softmax reference of the bf16 attention kernels, scheduled and plain (attn_bf16.hip, attn_bf16_group.hip): a weight is
+// exp2(logit - reference) in log2 units, and both kernels take the reference by the same rule, so that a column set that names every key gives
+// the weights of dense attention.  It is taken from the maximum of the first 32 keys and raised, from the maximum of the running ones and
+// by a whole number of units, where the sum of 16 weights of a lane exceeds kAttnGrowthLimit.
+//
+// Headroom.  The first 32 kept keys say little about the largest logit of a row: against their maximum alone some lane of a wave outgrew its
+// reference in most of the first tiles of a block, at some 2000 ticks for all four waves of the scheduled kernel.  Sums and accumulators are
+// floats that carry the same power of two as the weights, so only small weights are lost: below 2^-117 of a row's largest (a raise leaves the
+// reference up to nine units above the maximum), 2^-125 without headroom.  A whole number, so that a weight is rounded to sixteen bits as without, but for the fp32
+// rounding of reference and shifted logit.  That rounding goes into the row log-sum-exp of dense attention: rms error against 64 bits without / with
+// headroom, 1000 to 8192 rows of unit logits 3.6 to 4.9e-7 / 2.9 to 4.1e-7, three times as steep 0.9 to 1.41e-6 / 1.0 to 1.44e-6, 64 rows of these at D = 64
+// 5.2e-7 / 6.0e-7, 17 rows of unit logits 1.7e-7 / 2.0e-7, two keys 0.6e-7 / 2.1e-7.  Outputs are as far from 64 bits as without (differences below 0.02%).
+// 0 / 3 / 5 / 8 units, us: scheduled kernel, 64K rows, keep 10%, 5348 / 5187 / 5123 / 5107, 32K, keep 20%, 2698 / 2609 / 2559 / 2546, refresh_dense of 16K 5089 /
+// 5011 / 4959 / 4934.  0 / 8 units: plain kernel, 32 heads of 4096 rows, keep 10%, 37.6 / 35.3, 4 heads of 8192 20.4 / 18.6, groups of 128 at 32
+// heads of 8192 138.6 / 132.7.
+#pragma once
+
+namespace pulsecol {
+
+constexpr float kAttnGrowthLimit = 256.0f;
+constexpr float kAttnHeadroom = 8.0f;
+
+}  // namespace pulsecol
