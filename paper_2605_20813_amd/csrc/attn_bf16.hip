@@ -50,6 +50,7 @@
 #include "attn_reference.h"
 #include "pulsecol_device.h"
 #include "pulsecol_kernels.h"
+#include "score_sums.h"
 
 namespace pulsecol {
 namespace {
@@ -1121,7 +1122,7 @@ __global__ void __launch_bounds__(NTHREADS) attn_bf16_kernel(AttnParams p) {
         l_tot[qb] = half_sum(w.l_run[qb]);
         const int row = q0 + qb * 32 + w.lq;
         if (p.lse != nullptr && w.lh == 0 && row < n)
-            p.lse[(int64_t)bh * p.n + row] = (w.mc[qb] + fast_log2(l_tot[qb])) * (p.lse_base2 ? 1.0f : kLn2);
+            p.lse[(int64_t)bh * p.n + row] = log2_of(w.mc[qb], l_tot[qb]) * (p.lse_base2 ? 1.0f : kLn2);
     }
     constexpr int OUT_GROUPS = 64 / W::ROWS_PER_CHUNK;
     const int out_lrow = w.lane / W::PIECES, out_lpiece = w.lane % W::PIECES;
