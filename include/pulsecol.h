@@ -34,8 +34,8 @@
  *     printed unless the environment variable PULSECOL_LOG is set (then every failure goes
  *     to stderr as well).  On failure no kernel has been launched.  pulsecol_last_error gives a text for the last failure on a
  *     context.  Two calls on one context must not overlap in time (they share scratch), whatever their streams, replays of
- *     captured calls among them: the outputs of calls that do are unspecified, those of later ones are not affected once a
- *     pattern selected meanwhile has been selected again.
+ *     captured calls among them: the outputs of calls that do, and of up to four calls behind them, are unspecified; nothing lasts
+ *     longer but a pattern that was cached meanwhile.
  *   - NaN / Inf in the inputs give unspecified values, never a fault.
  */
 #ifndef PULSECOL_H
